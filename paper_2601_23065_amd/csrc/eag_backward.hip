@@ -308,7 +308,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
   src.item = 0;
   src.gR1 = src.gO = src.gW = d3(0.0, 0.0, 0.0);
   src.G = src.prefix = 0.0;
-  run_segments<Q_RADIANCE, true>(tc, src, work, hw * n_cams * sp.spp, hitlist, nullptr);
+  run_segments<Q_RADIANCE, true, false>(tc, src, work, hw * n_cams * sp.spp, hitlist, nullptr);
   // (the runner's loop ends for the whole wave at once)
   if ((threadIdx.x & 63) == 0 && s_wcur[2 * wv + 1] < (unsigned)gr.n_chunks)
     gr.chunk_used[s_wcur[2 * wv + 1]] = s_wcur[2 * wv];
@@ -434,7 +434,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
   src.gN = src.gR = src.gP = d3(0.0, 0.0, 0.0);
   src.gD = src.gA = src.Tm = src.G = src.prefix = 0.0;
   src.has_R = src.has_P = false;
-  run_segments<Q_ALL, true>(tc, src, work, hw * n_cams, hitlist, nullptr);
+  run_segments<Q_ALL, true, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
   if ((threadIdx.x & 63) == 0 && s_wcur[2 * wv + 1] < (unsigned)gr.n_chunks)
     gr.chunk_used[s_wcur[2 * wv + 1]] = s_wcur[2 * wv];
 }
@@ -528,7 +528,7 @@ k_stage0_bwd(TraceCtx tc, const CamBatch cams, int64_t hw, int32_t n_cams, SbPar
   src.wcur = s_wcur + 2 * wv;
   src.gN = src.gR = d3(0.0, 0.0, 0.0);
   src.gD = src.gA = src.gE = src.Tm = src.G = src.prefix = 0.0;
-  run_segments<Q_ALL, true>(tc, src, work, hw * n_cams, hitlist, nullptr);
+  run_segments<Q_ALL, true, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
   if ((threadIdx.x & 63) == 0 && s_wcur[2 * wv + 1] < (unsigned)gr.n_chunks)
     gr.chunk_used[s_wcur[2 * wv + 1]] = s_wcur[2 * wv];
 }

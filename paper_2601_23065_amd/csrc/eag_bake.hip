@@ -83,7 +83,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) k_zero_bounce(TraceCtx tc, const 
   src.sp = sp;
   src.rgb = rgb;
   src.item = 0;
-  run_segments<Q_RADIANCE, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
+  run_segments<Q_RADIANCE, false, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
 }
 
 struct RadianceAdjSource {
@@ -128,7 +128,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) k_zero_bounce_adj_r(TraceCtx tc, 
   src.gr = gr;
   src.n = n;
   src.dl = v3(0.f, 0.f, 0.f);
-  run_segments<Q_RADIANCE, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
+  run_segments<Q_RADIANCE, false, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
 }
 
 __global__ void __launch_bounds__(256) k_bake_loss(const float* rgb, const float* target, int64_t m, double inv_count,

@@ -465,11 +465,13 @@ __global__ void __launch_bounds__(256) k_refit_level(int64_t n, const float* box
   }
 }
 
-__global__ void k_records(eag_surfels s, const int32_t* perm, Record* recs) {
+// (inv: written with the records of a build; null in a refit, which keeps the order)
+__global__ void k_records(eag_surfels s, const int32_t* perm, Record* recs, int32_t* inv) {
   const int64_t n = s.n;
   const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (j >= n) return;
   const int64_t i = perm[j];
+  if (inv) inv[i] = (int32_t)j;
   float4* r = reinterpret_cast<float4*>(recs + j);
   r[0] = make_float4(s.pos[i], s.pos[n + i], s.pos[2 * n + i], s.opacity[i]);
   r[1] = make_float4(s.rot[i], s.rot[n + i], s.rot[2 * n + i], s.rot[3 * n + i]);
@@ -721,6 +723,7 @@ BvhLayout bvh_layout(void* base, int64_t n) {
   l.nodes4 = c.take<Node4>(n > 1 ? n - 1 : 1);
   l.recs = c.take<Record>(n);
   l.perm = c.take<int32_t>(n);
+  l.inv = c.take<int32_t>(n);
   l.leaf_parent = c.take<int32_t>(n);
   l.node_parent = c.take<int32_t>(n > 1 ? n - 1 : 1);
   l.levels = c.take<int32_t>(PLOC_LEVELS + 1);
@@ -734,6 +737,7 @@ void bvh_attach(eag_bvh* b, const BvhLayout& l) {
   b->nodes4 = l.nodes4;
   b->recs = l.recs;
   b->perm = l.perm;
+  b->inv = l.inv;
   b->leaf_parent = l.leaf_parent;
   b->node_parent = l.node_parent;
   b->levels = l.levels;
@@ -756,7 +760,7 @@ static void geometry_pass(const eag_surfels* s, eag_bvh* b, const BuildWs& w, hi
 
 void build_bvh(const eag_surfels* s, eag_bvh* b, void* ws, size_t ws_bytes, hipStream_t st) {
   const int64_t n = s->n;
-  if (!b->hdr || !b->nodes || !b->nodes4 || !b->recs || !b->perm || !b->leaf_parent || !b->node_parent || !b->levels)
+  if (!b->hdr || !b->nodes || !b->nodes4 || !b->recs || !b->perm || !b->inv || !b->leaf_parent || !b->node_parent || !b->levels)
     fail(EAG_ERR_INTERNAL, "bvh handle without its device arrays");
   BuildWs w = build_ws(ws, n);
   if (ws_bytes < w.bytes) fail(EAG_ERR_WORKSPACE_TOO_SMALL, "build workspace too small");
@@ -780,7 +784,7 @@ void build_bvh(const eag_surfels* s, eag_bvh* b, void* ws, size_t ws_bytes, hipS
   } else {
     hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, st, b->leaf_parent, (int64_t)1);
   }
-  hipLaunchKernelGGL(k_records, dim3(blocks(n)), dim3(256), 0, st, *s, b->perm, b->recs);
+  hipLaunchKernelGGL(k_records, dim3(blocks(n)), dim3(256), 0, st, *s, b->perm, b->recs, b->inv);
   if (n > 1)
     hipLaunchKernelGGL(k_depth, dim3(blocks(n)), dim3(256), 0, st, n, b->leaf_parent, b->node_parent, b->hdr);
   check_hip(hipGetLastError(), "build launch");
@@ -809,7 +813,8 @@ void refit_bvh(const eag_surfels* s, eag_bvh* b, void* ws, size_t ws_bytes, hipS
   // topology is unchanged
   hipLaunchKernelGGL(k_reset_bounds, dim3(1), dim3(64), 0, st, h);
   hipLaunchKernelGGL(k_boxes, dim3(blocks(n)), dim3(256), 0, st, *s, 3.0f, w.box, h);
-  hipLaunchKernelGGL(k_records, dim3(blocks(n)), dim3(256), 0, st, *s, b->perm, b->recs);
+  hipLaunchKernelGGL(k_records, dim3(blocks(n)), dim3(256), 0, st, *s, b->perm, b->recs,
+                     (int32_t*)nullptr);
   if (n > 1) {
     // iteration by iteration of the clustering that made the tree
     const unsigned g = std::min<unsigned>(blocks(n), 1024u);

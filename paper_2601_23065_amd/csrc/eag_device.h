@@ -142,18 +142,39 @@ __device__ __forceinline__ D3 cosine_dir(D3 n, double u0, double u1) {
 }
 
 // ---------------------------------------------------------------------------
-// Order key: (bucket, original index, sorted position) packed into 64 bits,
-// bucket = floor(t / dq) (dq a power of two) or the float bits of t when
-// dq == 0. Ordering keys as integers orders hits by (bucket, index); the
-// sorted position rides along so that the blending pass can address the
-// record directly.
+// Order key: (bucket, original index) packed into 64 bits, bucket =
+// floor(t / dq) (dq a power of two) or the float bits of t when dq == 0.
+// Ordering keys as integers orders hits by (bucket, index); the sorted
+// position that addresses the record comes from the tree's inverse
+// permutation when the hit is blended. At most 32 + 23 bits are used, and bit
+// 62 is set, so that every key is also the bit pattern of a positive normal
+// double and doubles order like the keys: v_min_f64 and v_max_f64 compare and
+// move a key in one instruction each, where a 64-bit integer comparison takes
+// five with its four selects.
 // ---------------------------------------------------------------------------
+constexpr uint64_t KEY_BIAS = 0x4000000000000000ull;
+constexpr uint64_t KEY_NONE = 0x7ff0000000000000ull;   // +inf: above every key
+
+// (Written as instructions: from fmin the compiler makes a third one per
+// operand that quiets a NaN no key can be.)
+__device__ __forceinline__ uint64_t key_min(uint64_t a, uint64_t b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(__longlong_as_double((long long)a)), "v"(__longlong_as_double((long long)b)));
+  return (uint64_t)__double_as_longlong(r);
+}
+__device__ __forceinline__ uint64_t key_max(uint64_t a, uint64_t b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(__longlong_as_double((long long)a)), "v"(__longlong_as_double((long long)b)));
+  return (uint64_t)__double_as_longlong(r);
+}
+
 struct TraceCtx {
   const Node4* nodes;
   const Record* recs;
   const Attr* attrs;
+  const int32_t* inv;      // sorted position of each surfel
   int32_t root;            // >= 0: internal node index; < 0: single leaf ~root
-  int32_t idx_bits;        // bits of an index (both index fields)
+  int32_t idx_bits;        // bits of an index
   uint32_t max_bucket;     // largest representable bucket
   double inv_dq;           // 1 / dq, or 0 for exact-t keys
   double dq;               // the depth quantum (a power of two, so b * dq == b / inv_dq exactly), or 0
@@ -177,7 +198,10 @@ static_assert(HL_CAP % 8 == 0 && HL_STRIDE == 1, "hit-list scan reads 8 contiguo
 __device__ __noinline__ void report_key_range(unsigned int* status) {
   if (status) __hip_atomic_fetch_or(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-__device__ __forceinline__ uint64_t make_key(const TraceCtx& tc, double t, uint32_t idx, uint32_t pos) {
+__device__ __forceinline__ uint64_t pack_key(const TraceCtx& tc, uint32_t bucket, uint32_t idx) {
+  return ((uint64_t)bucket << tc.idx_bits) | (uint64_t)idx | KEY_BIAS;
+}
+__device__ __forceinline__ uint64_t make_key(const TraceCtx& tc, double t, uint32_t idx) {
   uint32_t bucket;
   if (tc.inv_dq > 0.0) {
     const double b = floor(t * tc.inv_dq);
@@ -185,36 +209,32 @@ __device__ __forceinline__ uint64_t make_key(const TraceCtx& tc, double t, uint3
   } else {
     bucket = __float_as_uint((float)t);
   }
-  return ((uint64_t)bucket << (2 * tc.idx_bits)) | ((uint64_t)idx << tc.idx_bits) | (uint64_t)pos;
+  return pack_key(tc, bucket, idx);
 }
-__device__ __forceinline__ uint64_t make_key_b(const TraceCtx& tc, uint32_t bucket, uint32_t idx, uint32_t pos) {
-  bucket = bucket >= tc.max_bucket ? tc.max_bucket : bucket;
-  return ((uint64_t)bucket << (2 * tc.idx_bits)) | ((uint64_t)idx << tc.idx_bits) | (uint64_t)pos;
-}
-__device__ __forceinline__ uint32_t key_pos(const TraceCtx& tc, uint64_t k) {
-  return (uint32_t)(k & ((1ull << tc.idx_bits) - 1));
+__device__ __forceinline__ uint64_t make_key_b(const TraceCtx& tc, uint32_t bucket, uint32_t idx) {
+  return pack_key(tc, bucket >= tc.max_bucket ? tc.max_bucket : bucket, idx);
 }
 __device__ __forceinline__ uint32_t key_idx(const TraceCtx& tc, uint64_t k) {
-  return (uint32_t)((k >> tc.idx_bits) & ((1ull << tc.idx_bits) - 1));
+  return (uint32_t)k & ((1u << tc.idx_bits) - 1u);
 }
 __device__ __forceinline__ uint32_t key_bucket(const TraceCtx& tc, uint64_t k) {
-  return (uint32_t)(k >> (2 * tc.idx_bits));
+  return (uint32_t)(k >> tc.idx_bits);   // (the bias lies above the 32 bits kept)
 }
 // first key of the bucket after k's (saturating at the last bucket, which the
 // hit list then never claims to cover)
 __device__ __forceinline__ uint64_t next_bucket_key(const TraceCtx& tc, uint64_t k) {
   const uint32_t b = key_bucket(tc, k);
-  return make_key_b(tc, b < tc.max_bucket ? b + 1u : tc.max_bucket, 0u, 0u);
+  return make_key_b(tc, b < tc.max_bucket ? b + 1u : tc.max_bucket, 0u);
 }
 // smallest t that can carry the given key's bucket (for culling)
 __device__ __forceinline__ float key_tlo(const TraceCtx& tc, uint64_t k) {
-  const uint32_t b = (uint32_t)(k >> (2 * tc.idx_bits));
+  const uint32_t b = key_bucket(tc, k);
   if (tc.inv_dq > 0.0) return (float)((double)b * tc.dq);
   return __uint_as_float(b);
 }
 // largest t whose bucket does not exceed the key's bucket
 __device__ __forceinline__ float key_thi(const TraceCtx& tc, uint64_t k) {
-  const uint32_t b = (uint32_t)(k >> (2 * tc.idx_bits));
+  const uint32_t b = key_bucket(tc, k);
   if (tc.inv_dq > 0.0) return (float)((double)(b + 1u) * tc.dq);
   return __uint_as_float(b);
 }
@@ -229,8 +249,16 @@ __device__ __forceinline__ float key_thi(const TraceCtx& tc, uint64_t k) {
 // evaluation could not settle, so a float screen in front of it only added
 // instructions.
 // ---------------------------------------------------------------------------
+// Element i of an array of at most 4 GiB (2^23 surfels: 1 GiB of nodes at
+// most). A 32-bit byte offset beside a uniform base is an addressing mode of
+// its own; a 64-bit one costs each lane its address arithmetic and registers.
+template <class T>
+__device__ __forceinline__ const T* elem(const T* base, uint32_t i) {
+  return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (uint32_t)(i * (uint32_t)sizeof(T)));
+}
+
 __device__ __forceinline__ Record load_record(const Record* recs, uint32_t pos) {
-  const float4* p = reinterpret_cast<const float4*>(recs + pos);
+  const float4* p = reinterpret_cast<const float4*>(elem(recs, pos));
   Record r;
   r.p_sigma = p[0];
   r.q = p[1];
@@ -334,16 +362,17 @@ struct TravStack {
   }
 };
 
-// Accept a candidate key into the sorted k-buffer (ascending; empty = ~0):
-// one compare-exchange per entry carries the larger key down the buffer.
-// Returns the key that falls off the end (the old last entry, or the
-// candidate itself when it is not below it).
+// Accept a candidate key into the sorted k-buffer (ascending; empty =
+// KEY_NONE). Entry j becomes the median of entry j - 1, entry j and the key,
+// which in a sorted buffer is max(entry j - 1, min(entry j, key)): two
+// instructions per entry, none waiting for another entry's. Returns the key
+// that falls off the end (the old last entry, or the candidate itself when it
+// is not below it).
 __device__ __forceinline__ uint64_t kbuf_insert(uint64_t (&kk)[KBUF], uint64_t key) {
 #pragma unroll
   for (int j = 0; j < KBUF; ++j) {
-    const bool lt = key < kk[j];
-    const uint64_t lo = lt ? key : kk[j];
-    key = lt ? kk[j] : key;
+    const uint64_t lo = key_min(kk[j], key);
+    key = key_max(kk[j], key);
     kk[j] = lo;
   }
   return key;
@@ -351,9 +380,8 @@ __device__ __forceinline__ uint64_t kbuf_insert(uint64_t (&kk)[KBUF], uint64_t k
 
 // Compare-exchange: afterwards a <= b.
 __device__ __forceinline__ void cswap_key(uint64_t& a, uint64_t& b) {
-  const bool lt = b < a;
-  const uint64_t lo = lt ? b : a;
-  b = lt ? a : b;
+  const uint64_t lo = key_min(a, b);
+  b = key_max(a, b);
   a = lo;
 }
 
@@ -376,7 +404,7 @@ __device__ __forceinline__ void sort8_keys(uint64_t (&e)[8]) {
 static_assert(KBUF == 16, "the merge network is built for a 16-entry k-buffer");
 __device__ __forceinline__ void kbuf_merge8(uint64_t (&kk)[KBUF], const uint64_t (&e)[8]) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) kk[8 + i] = e[7 - i] < kk[8 + i] ? e[7 - i] : kk[8 + i];
+  for (int i = 0; i < 8; ++i) kk[8 + i] = key_min(e[7 - i], kk[8 + i]);
 #pragma unroll
   for (int st = 8; st >= 1; st >>= 1) {
 #pragma unroll
@@ -421,11 +449,21 @@ struct Seg {
   D3 N;
   double D, T;
   Acc R0, R1, R2, E, P0, P1, P2;
-  uint64_t last;      // keys must exceed this once have_last
-  bool have_last;
+  uint64_t last;      // keys must exceed this (0 before the first round: below every key)
   bool done;
   int nl;             // entries in the hit list
   uint64_t lhi;       // 0: list unusable; else it holds every hit key in (last, lhi)
+};
+
+// A segment with its statistics, kept only where the caller reads them: they
+// cost a register each, and registers are what the runner's waves have least of.
+template <bool DACC, bool STATS>
+struct SegStats : Seg<DACC> {
+  static constexpr bool kStats = false;
+};
+template <bool DACC>
+struct SegStats<DACC, true> : Seg<DACC> {
+  static constexpr bool kStats = true;
   int32_t nhits, rounds, tests, visits;
 };
 
@@ -434,23 +472,21 @@ struct Seg {
 // every lane of the wave has a leaf waiting; then the postponed leaves are
 // tested, so that the costly surfel test runs for many lanes at once.
 struct Round {
-  uint64_t kk[KBUF];  // ascending; empty = ~0
+  uint64_t kk[KBUF];  // ascending; empty = KEY_NONE
   int cnt;
-  uint64_t floor_key; // keys taken must exceed this (when have_floor)
-  bool have_floor;
+  uint64_t floor_key; // keys taken must exceed this
   uint64_t cut_key;   // hit list entries must be below this
   float t_cut;        // boxes entered beyond this cannot hold a key < kk[KBUF-1]
   float tlo0;         // boxes ending before this cannot hold a key > floor_key
   bool over;          // the hit list overflowed this round
   bool partial;       // list keys below lhi only: blend them, then traverse beyond lhi if still open
-  uint64_t plast;     // largest key of a partial round
   bool trav;          // internal nodes remain (ref, then the stack)
   int ref;            // next internal node
   int np;             // postponed leaves
 };
 
-template <bool DACC>
-__device__ __forceinline__ void seg_begin(Seg<DACC>& s, D3 O, D3 W) {
+template <class S>
+__device__ __forceinline__ void seg_begin(S& s, D3 O, D3 W) {
   s.O = O;
   s.W = W;
   const float wx = (float)W.x, wy = (float)W.y, wz = (float)W.z;
@@ -463,27 +499,25 @@ __device__ __forceinline__ void seg_begin(Seg<DACC>& s, D3 O, D3 W) {
   s.T = 1.0;
   s.R0 = s.R1 = s.R2 = s.E = s.P0 = s.P1 = s.P2 = 0;
   s.last = 0;
-  s.have_last = false;
   s.done = false;
   s.nl = 0;
   s.lhi = 0;
-  s.nhits = s.rounds = s.tests = s.visits = 0;
+  if constexpr (S::kStats) s.nhits = s.rounds = s.tests = s.visits = 0;
 }
 
 // Start a round. Returns true when it must traverse (r.trav / r.np are set
 // up and the stack is empty), false when the hit list alone decides it.
-template <bool DACC>
-__device__ __forceinline__ bool round_begin(const TraceCtx& tc, Seg<DACC>& s, Round& r, TravStack& st, int* pend) {
-  ++s.rounds;
+template <class S>
+__device__ __forceinline__ bool round_begin(const TraceCtx& tc, S& s, Round& r, TravStack& st, int* pend) {
+  if constexpr (S::kStats) ++s.rounds;
 #pragma unroll
-  for (int j = 0; j < KBUF; ++j) r.kk[j] = ~0ull;
+  for (int j = 0; j < KBUF; ++j) r.kk[j] = KEY_NONE;
   r.cnt = 0;
   r.floor_key = s.last;
-  r.have_floor = s.have_last;
   r.over = false;
   r.partial = false;
   bool traverse = true;
-  if (s.lhi != 0) {
+  if (s.lhi > s.last + 1) {
     // keys in (last, lhi) from the list (entries at or below last were
     // blended by earlier rounds and are skipped, not removed)
     // (loaded 8 at a time: entries up to HL_CAP are this lane's, those past
@@ -500,9 +534,9 @@ __device__ __forceinline__ bool round_begin(const TraceCtx& tc, Seg<DACC>& s, Ro
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        // branch-free: a key outside (last, lhi) enters the merge as ~0
+        // branch-free: a key outside (last, lhi) enters the merge as KEY_NONE
         const bool in = j + u < s.nl && e[u] > s.last && e[u] < s.lhi;
-        e[u] = in ? e[u] : ~0ull;
+        e[u] = in ? e[u] : KEY_NONE;
         w += in ? 1 : 0;
       }
       sort8_keys(e);
@@ -511,26 +545,22 @@ __device__ __forceinline__ bool round_begin(const TraceCtx& tc, Seg<DACC>& s, Ro
     if (w == 0) s.nl = 0;
     // every key in range is below the buffer's last entry until it is full
     r.cnt = w > KBUF ? KBUF : w;
-    r.plast = 0;
-#pragma unroll
-    for (int j = 0; j < KBUF; ++j) r.plast = j < r.cnt ? r.kk[j] : r.plast;
-    if (r.cnt == KBUF || s.lhi == ~0ull) {
+    if (r.cnt == KBUF || s.lhi == KEY_NONE) {
       traverse = false;
     } else if (r.cnt > 0) {
       // Every key >= lhi follows these, so they can be blended first; the
       // segment often ends among them, and then nothing beyond lhi is needed.
       traverse = false;
       r.partial = true;
-    } else if (s.lhi - 1 > r.floor_key) {
-      r.floor_key = s.lhi - 1;
-      r.have_floor = true;
+    } else {
+      r.floor_key = s.lhi - 1;   // (above last)
     }
   } else {
-    s.nl = 0;
+    s.nl = 0;   // no list, or every key it covers is blended (last = lhi - 1)
   }
-  r.cut_key = r.cnt == KBUF ? next_bucket_key(tc, r.kk[KBUF - 1]) : ~0ull;
+  r.cut_key = r.cnt == KBUF ? next_bucket_key(tc, r.kk[KBUF - 1]) : KEY_NONE;
   r.t_cut = r.cnt == KBUF ? key_thi(tc, r.kk[KBUF - 1]) * 1.000002f + 1e-6f : __builtin_inff();
-  const float t_floor = r.have_floor ? key_tlo(tc, r.floor_key) : 0.0f;
+  const float t_floor = key_tlo(tc, r.floor_key);   // (0 for floor 0)
   r.tlo0 = fmaxf((float)tc.t_min, t_floor) * 0.99999f - 1e-6f;
   st.sp = 0;
   r.ref = tc.root;
@@ -545,10 +575,10 @@ __device__ __forceinline__ bool round_begin(const TraceCtx& tc, Seg<DACC>& s, Ro
 
 // Visit internal node r.ref: leaves the ray reaches are postponed, internal
 // children are visited nearest first (the others pushed farthest first).
-template <bool DACC>
-__device__ __forceinline__ void node_visit(const TraceCtx& tc, Seg<DACC>& s, Round& r, TravStack& st, int* pend) {
-  ++s.visits;
-  const Node4* nd = tc.nodes + r.ref;
+template <class S>
+__device__ __forceinline__ void node_visit(const TraceCtx& tc, S& s, Round& r, TravStack& st, int* pend) {
+  if constexpr (S::kStats) ++s.visits;
+  const Node4* nd = elem(tc.nodes, (uint32_t)r.ref);
   const int4 cr = nd->ref;
   const float4* bb = nd->b;
   const float4 b0 = bb[0], b1 = bb[1], b2 = bb[2], b3 = bb[3], b4 = bb[4], b5 = bb[5];
@@ -606,12 +636,11 @@ __device__ __forceinline__ void node_visit(const TraceCtx& tc, Seg<DACC>& s, Rou
 }
 
 // The order key of a postponed leaf (its record already loaded) for the ray
-// (O, W) in a round whose keys must exceed floor_key (when have_floor); ~0
-// when the surfel is missed or its key cannot enter the round. cutlim: keys
+// (O, W) in a round whose keys must exceed floor_key; KEY_NONE when the surfel is missed or its key cannot enter the round. cutlim: keys
 // at or above it are dropped (the k-buffer's last key, or the hit list's
 // cut, a bucket's first key; any larger value is also correct).
-__device__ __forceinline__ uint64_t leaf_key(const TraceCtx& tc, const Record& rec, uint32_t pos, D3 O, D3 W,
-                                             bool have_floor, uint64_t floor_key, uint64_t cutlim) {
+__device__ __forceinline__ uint64_t leaf_key(const TraceCtx& tc, const Record& rec, D3 O, D3 W, uint64_t floor_key,
+                                             uint64_t cutlim) {
   // The surfel test in double precision, straight-line. The columns of the
   // rotation of the unnormalised quaternion are |q|^2 (t_u, t_v, n): the
   // distance t = ((p - O).n) / (W.n) needs no normalisation, and the ellipse
@@ -633,24 +662,24 @@ __device__ __forceinline__ uint64_t leaf_key(const TraceCtx& tc, const Record& r
   // (multiplied through by s_u^2 s_v^2, all positive: no division)
   const bool hit = fabs(den) > 1e-12 * q2n && rec.p_sigma.w > 0.0f && t > tc.t_min &&
                    up * up * sv2 + vp * vp * su2 <= tc.k2 * q2n * q2n * su2 * sv2;
-  const uint64_t key = make_key(tc, t, rec_index(rec), pos);
-  const bool qual = hit && !(have_floor && key <= floor_key);
+  const uint64_t key = make_key(tc, t, rec_index(rec));
+  const bool qual = hit && key > floor_key;
   // A hit in the last bucket may stand for a farther one that the key
   // saturated into it, whose order among the others is then unknown: the
   // launch reports it (a rare branch; never taken within the range).
   if (qual && tc.inv_dq > 0.0 && key_bucket(tc, key) >= tc.max_bucket) report_key_range(tc.status);
-  return qual && key < cutlim ? key : ~0ull;
+  return qual && key < cutlim ? key : KEY_NONE;
 }
 
 // Take a qualifying key into the round. The list needs only keys beyond the
 // round's final KBUF-th key: a key goes there when the k-buffer rejects it
 // or later evicts it.
-template <bool DACC>
-__device__ __forceinline__ void take_key(const TraceCtx& tc, Seg<DACC>& s, Round& r, uint64_t key) {
+template <class S>
+__device__ __forceinline__ void take_key(const TraceCtx& tc, S& s, Round& r, uint64_t key) {
   // The insert runs without a branch: a key not below the last entry passes
   // through the chain unchanged and comes back as the spill.
   const bool ins = key < r.kk[KBUF - 1];
-  const uint64_t spill = kbuf_insert(r.kk, key);   // ~0 while the buffer is not full
+  const uint64_t spill = kbuf_insert(r.kk, key);   // KEY_NONE while the buffer is not full
   r.cnt += ins ? 1 : 0;
   if (ins && r.cnt >= KBUF) {
     r.cnt = KBUF;
@@ -663,18 +692,16 @@ __device__ __forceinline__ void take_key(const TraceCtx& tc, Seg<DACC>& s, Round
   }
 }
 
-template <bool DACC>
 __device__ __forceinline__ uint64_t round_cutlim(const TraceCtx& tc, const Round& r) {
   return tc.hl ? r.cut_key : r.kk[KBUF - 1];
 }
 
 // Test one postponed leaf of this lane's own ray and take its key.
-template <bool DACC>
-__device__ __forceinline__ void leaf_eval(const TraceCtx& tc, Seg<DACC>& s, Round& r, const Record& rec,
-                                          uint32_t pos) {
-  ++s.tests;
-  const uint64_t key = leaf_key(tc, rec, pos, s.O, s.W, r.have_floor, r.floor_key, round_cutlim<DACC>(tc, r));
-  if (key != ~0ull) take_key(tc, s, r, key);
+template <class S>
+__device__ __forceinline__ void leaf_eval(const TraceCtx& tc, S& s, Round& r, const Record& rec) {
+  if constexpr (S::kStats) ++s.tests;
+  const uint64_t key = leaf_key(tc, rec, s.O, s.W, r.floor_key, round_cutlim(tc, r));
+  if (key != KEY_NONE) take_key(tc, s, r, key);
 }
 
 // Test postponed leaves, most recent first. The next leaf's record is loaded
@@ -683,35 +710,29 @@ __device__ __forceinline__ void leaf_eval(const TraceCtx& tc, Seg<DACC>& s, Roun
 // LEAF_MIN_LANES lanes of the wave still hold leaves, and keeps the rest for
 // its next leaf phase; a lane whose traversal has ended tests all of them.
 constexpr int LEAF_MIN_LANES = 16;
-template <bool DACC>
-__device__ __forceinline__ void leaf_phase(const TraceCtx& tc, Seg<DACC>& s, Round& r, int* pend) {
+template <class S>
+__device__ __forceinline__ void leaf_phase(const TraceCtx& tc, S& s, Round& r, int* pend) {
   if (r.np <= 0) return;
-  uint32_t pos = (uint32_t)pend[(--r.np) * TRACE_BLOCK];
-  Record rec = load_record(tc.recs, pos);
+  Record rec = load_record(tc.recs, (uint32_t)pend[(--r.np) * TRACE_BLOCK]);
   while (true) {
     const bool more = r.np > 0 && !(r.trav && __popcll(__ballot(r.np > 0)) < LEAF_MIN_LANES);
-    uint32_t npos = 0;
     Record nrec;
-    if (more) {
-      npos = (uint32_t)pend[(--r.np) * TRACE_BLOCK];
-      nrec = load_record(tc.recs, npos);
-    }
-    leaf_eval(tc, s, r, rec, pos);
+    if (more) nrec = load_record(tc.recs, (uint32_t)pend[(--r.np) * TRACE_BLOCK]);
+    leaf_eval(tc, s, r, rec);
     if (!more) break;
-    pos = npos;
     rec = nrec;
   }
 }
 
 // After a traversal round: what the hit list now covers.
-template <bool DACC>
-__device__ __forceinline__ void round_end_traversal(const TraceCtx& tc, Seg<DACC>& s, const Round& r) {
-  if (tc.hl) s.lhi = r.over ? 0ull : (r.cnt == KBUF ? r.cut_key : ~0ull);
+template <class S>
+__device__ __forceinline__ void round_end_traversal(const TraceCtx& tc, S& s, const Round& r) {
+  if (tc.hl) s.lhi = r.over ? 0ull : (r.cnt == KBUF ? r.cut_key : KEY_NONE);
 }
 
 // Traverse one round to completion for this lane.
-template <bool DACC>
-__device__ __forceinline__ void traverse_round(const TraceCtx& tc, Seg<DACC>& s, Round& r, TravStack& st,
+template <class S>
+__device__ __forceinline__ void traverse_round(const TraceCtx& tc, S& s, Round& r, TravStack& st,
                                                int* pend) {
   while (true) {
     while (r.trav && r.np <= PEND - 4) {
@@ -724,37 +745,40 @@ __device__ __forceinline__ void traverse_round(const TraceCtx& tc, Seg<DACC>& s,
   round_end_traversal(tc, s, r);
 }
 
-// Blend the round's hits in key order (the buffer is shifted down one entry
-// per hit, which keeps its indexing static); t and alpha are recomputed from
-// the record with the same double-precision test. Sets s.done after the
-// first hit with T < T_min or when the round returned fewer than KBUF hits.
+// Blend the round's hits in key order; t and alpha are recomputed from the
+// record with the same double-precision test. Sets s.done after the first hit
+// with T < T_min or when the round returned fewer than KBUF hits. The sorted
+// positions of all the round's hits are fetched at once (their latency is
+// paid once a round), and shifted down one entry per hit, which keeps the
+// indexing static.
 // on_hit(pos, t, alpha, w, T_before, O, W) is called for every blended hit; if
 // hit_out is non-null, up to max_hits blended surfel indices are written.
-template <int QMODE, bool DACC, class HitFn>
-__device__ __forceinline__ void blend_round(const TraceCtx& tc, Seg<DACC>& s, Round& r, HitFn& on_hit,
+template <int QMODE, class S, class HitFn>
+__device__ __forceinline__ void blend_round(const TraceCtx& tc, S& s, Round& r, HitFn& on_hit,
                                            int32_t* hit_out, int max_hits) {
-  using Acc = typename Seg<DACC>::Acc;
-  const uint64_t round_last = r.partial ? r.plast : r.kk[KBUF - 1];
+  using Acc = typename S::Acc;
+  // a partial round holds every key below lhi
+  const uint64_t round_last = r.partial ? s.lhi - 1 : r.kk[KBUF - 1];
+  uint32_t at_pos[KBUF];
+#pragma unroll
+  for (int m = 0; m < KBUF; ++m) at_pos[m] = (uint32_t)*elem(tc.inv, m < r.cnt ? key_idx(tc, r.kk[m]) : 0u);
   // the next hit's record and attributes are loaded while the current one
   // is blended
   Record rec;
   Attr at;
   if (r.cnt > 0) {
-    const uint32_t p0 = key_pos(tc, r.kk[0]);
-    rec = load_record(tc.recs, p0);
-    at = tc.attrs[p0];
+    rec = load_record(tc.recs, at_pos[0]);
+    at = *elem(tc.attrs, at_pos[0]);
   }
   for (int j = 0; j < r.cnt && !s.done; ++j) {
-    const uint64_t key = r.kk[0];
+    const uint32_t pos = at_pos[0];
 #pragma unroll
-    for (int m = 0; m < KBUF - 1; ++m) r.kk[m] = r.kk[m + 1];
-    const uint32_t pos = key_pos(tc, key);
+    for (int m = 0; m < KBUF - 1; ++m) at_pos[m] = at_pos[m + 1];
     Record nrec;
     Attr nat;
     if (j + 1 < r.cnt) {
-      const uint32_t np = key_pos(tc, r.kk[0]);
-      nrec = load_record(tc.recs, np);
-      nat = tc.attrs[np];
+      nrec = load_record(tc.recs, at_pos[0]);
+      nat = *elem(tc.attrs, at_pos[0]);
     }
     // t, u, v and the unit normal from the columns of the unnormalised
     // quaternion's rotation, |q|^2 (t_u, t_v, n): no square root, and one
@@ -788,19 +812,18 @@ __device__ __forceinline__ void blend_round(const TraceCtx& tc, Seg<DACC>& s, Ro
     s.R0 += wf * at.r.x;
     s.R1 += wf * at.r.y;
     s.R2 += wf * at.r.z;
-    if (hit_out && s.nhits < max_hits) hit_out[s.nhits] = (int32_t)key_idx(tc, key);
+    if constexpr (S::kStats) {
+      if (hit_out && s.nhits < max_hits) hit_out[s.nhits] = (int32_t)rec_index(rec);
+    }
     on_hit(pos, t, a, w, s.T, s.O, s.W);
-    ++s.nhits;
+    if constexpr (S::kStats) ++s.nhits;
     s.T *= (1.0 - a);
     if (s.T < tc.T_min) s.done = true;
     rec = nrec;
     at = nat;
   }
   if (r.cnt < KBUF && !r.partial) s.done = true;
-  if (!s.done) {
-    s.last = round_last;
-    s.have_last = true;
-  }
+  if (!s.done) s.last = round_last;
 }
 
 // A whole segment for this lane. Must be called from a TRACE_BLOCK-thread
@@ -816,7 +839,7 @@ __device__ SegOut trace_segment_cb(const TraceCtx& tc, D3 O, D3 W, HitFn& on_hit
   st.ovf = s_ovf;
   st.sp = 0;
   int* pend = s_pend + threadIdx.x;   // this lane's queue of postponed leaves
-  Seg<DACC> s;
+  SegStats<DACC, true> s;
   seg_begin(s, O, W);
   while (!s.done) {
     Round r;

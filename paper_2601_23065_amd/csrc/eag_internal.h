@@ -73,7 +73,8 @@ struct eag_bvh {
   int32_t n_nodes4;       // synced
   int32_t depth4;         // synced
   eag::Record* recs;
-  int32_t* perm;
+  int32_t* perm;          // surfel at each sorted position
+  int32_t* inv;           // sorted position of each surfel
   int32_t* leaf_parent;
   int32_t* node_parent;
   int32_t* levels;        // internal nodes made before each clustering iteration
@@ -124,6 +125,7 @@ struct BvhLayout {
   Node4* nodes4;
   Record* recs;
   int32_t* perm;
+  int32_t* inv;
   int32_t* leaf_parent;
   int32_t* node_parent;
   int32_t* levels;

@@ -68,7 +68,7 @@ struct PathSource {
   __device__ __forceinline__ bool finish(const Seg<false>& s, D3& O, D3& W) {
     const PtSlot& S = L->s[slot];
     const double A = 1.0 - s.T;
-    if (s.nhits == 0 || !(A > 0.0)) return false;
+    if (!(A > 0.0)) return false;   // (A > 0: some hit was blended)
     const bool emit = s.E > S.tau_E;
     if ((S.flags & EAG_ADDITIVE_EMISSION) || emit) {
       int64_t* acc = S.accum + (int64_t)pix * 3;
@@ -95,7 +95,8 @@ struct PathSource {
   }
 };
 
-__global__ void __launch_bounds__(TRACE_BLOCK) k_path_trace(TraceCtx tc, PtLaunch L,
+template <bool STATS>
+__global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(2))) k_path_trace(TraceCtx tc, PtLaunch L,
                                                             unsigned long long* work_counter,
                                                             unsigned long long* counters, uint64_t* hitlist) {
   PathSource src;
@@ -104,7 +105,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) k_path_trace(TraceCtx tc, PtLaunc
   src.pix = src.sample = 0;
   src.depth = 0;
   src.beta = v3(1.f, 1.f, 1.f);
-  run_segments<Q_ALL, false>(tc, src, work_counter, L.n_work, hitlist, counters);
+  run_segments<Q_ALL, false, STATS>(tc, src, work_counter, L.n_work, hitlist, counters);
 }
 
 __global__ void k_zero_u64(unsigned long long* p, int n) {
@@ -133,7 +134,9 @@ void launch_path_trace(const TraceCtx& tc, const PtLaunch& L, unsigned long long
                        unsigned long long* counters, uint64_t* hitlist, hipStream_t st) {
   const unsigned blocks = (unsigned)(runner_lanes() / TRACE_BLOCK);
   hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, st, work_counter, 1);
-  hipLaunchKernelGGL(k_path_trace, dim3(blocks), dim3(TRACE_BLOCK), 0, st, tc, L, work_counter, counters, hitlist);
+  // the statistics cost registers: a kernel of its own without them
+  hipLaunchKernelGGL(counters ? k_path_trace<true> : k_path_trace<false>, dim3(blocks), dim3(TRACE_BLOCK), 0, st, tc, L,
+                     work_counter, counters, hitlist);
   check_hip(hipGetLastError(), "path_trace launch");
 }
 

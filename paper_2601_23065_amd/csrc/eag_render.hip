@@ -48,7 +48,7 @@ struct CameraSource {
     st.A = 0.0;
     st.branch = 0.0f;
     V3 L = v3(0.f, 0.f, 0.f);
-    if (s.nhits > 0 && A > 0.0) {
+    if (A > 0.0) {   // (A > 0: some hit was blended)
       const double nl = sqrt(dot(s.N, s.N));
       st.Nt = (1.0 / nl) * s.N;
       st.Dt = s.D / A;
@@ -82,7 +82,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) k_sb_camera(TraceCtx tc, const Ca
   src.state = state;
   src.rgb = rgb;
   src.item = 0;
-  run_segments<Q_ALL, true>(tc, src, work, hw * n_cams, hitlist, nullptr);
+  run_segments<Q_ALL, true, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
 }
 
 // One (pixel, sample) secondary segment per work item; a pixel whose camera
@@ -140,7 +140,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) k_sb_secondary(
   src.state = state;
   src.r1 = r1;
   src.item = 0;
-  run_segments<Q_RADIANCE, true>(tc, src, work, hw * n_cams * sp.spp, hitlist, nullptr);
+  run_segments<Q_RADIANCE, true, false>(tc, src, work, hw * n_cams * sp.spp, hitlist, nullptr);
 }
 
 __global__ void k_sb_resolve(int64_t n_pix, SbParams sp, const float* state, const double* r1, float* rgb) {

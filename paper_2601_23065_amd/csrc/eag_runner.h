@@ -68,7 +68,8 @@ __device__ __forceinline__ auto bind_lds_stack(Src& src, int* col, int) -> declt
 template <class Src>
 __device__ __forceinline__ void bind_lds_stack(Src&, int*, long) {}
 
-template <int QMODE, bool DACC, class Src>
+// STATS: the counters are written (counters may not be null then).
+template <int QMODE, bool DACC, bool STATS, class Src>
 __device__ __forceinline__ void run_segments(const TraceCtx& tc, Src& src, unsigned long long* work_counter,
                                              int64_t n_work, uint64_t* hitlist, unsigned long long* counters) {
   enum { ST_IDLE = 0, ST_ROUND = 1, ST_TRAV = 2, ST_BLEND = 3 };
@@ -87,7 +88,7 @@ __device__ __forceinline__ void run_segments(const TraceCtx& tc, Src& src, unsig
   tcl.hl = hitlist ? hitlist + ((int64_t)blockIdx.x * TRACE_BLOCK + threadIdx.x) * HL_CAP : nullptr;
 
   int stage = ST_IDLE;
-  Seg<DACC> s;
+  SegStats<DACC, STATS> s;
   seg_begin(s, d3(0.0, 0.0, 0.0), d3(0.0, 0.0, 1.0));
   Round r;
   r.cnt = 0;
@@ -112,8 +113,10 @@ __device__ __forceinline__ void run_segments(const TraceCtx& tc, Src& src, unsig
         if (wid < n_work && src.start(wid, tcl, O, W)) {
           seg_begin(s, O, W);
           stage = ST_ROUND;
-          ++rs.items;
-          ++rs.segments;
+          if constexpr (STATS) {
+            ++rs.items;
+            ++rs.segments;
+          }
         }
       }
     }
@@ -150,19 +153,21 @@ __device__ __forceinline__ void run_segments(const TraceCtx& tc, Src& src, unsig
       stage = ST_ROUND;
       continue;
     }
-    rs.rounds += s.rounds;
-    rs.tests += s.tests;
-    rs.hits += s.nhits;
-    rs.visits += s.visits;
+    if constexpr (STATS) {
+      rs.rounds += s.rounds;
+      rs.tests += s.tests;
+      rs.hits += s.nhits;
+      rs.visits += s.visits;
+    }
     if (src.finish(s, O, W)) {
       seg_begin(s, O, W);
       stage = ST_ROUND;
-      ++rs.segments;
+      if constexpr (STATS) ++rs.segments;
     } else {
       stage = ST_IDLE;
     }
   }
-  if (counters) rs.flush(counters);
+  if constexpr (STATS) rs.flush(counters);
 }
 
 }  // namespace eag

@@ -82,6 +82,7 @@ TraceCtx make_ctx(const eag_bvh* b, const Attr* attrs, const eag_trace_params* p
   tc.nodes = b->nodes4;
   tc.recs = b->recs;
   tc.attrs = attrs;
+  tc.inv = b->inv;
   tc.root = b->root;
   tc.idx_bits = ts.idx_bits;
   tc.max_bucket = ts.max_bucket;
