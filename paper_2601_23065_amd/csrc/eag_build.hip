@@ -546,7 +546,60 @@ __global__ void k_collapse_init(int32_t* counts, int2* q0) {
   }
 }
 
-__global__ void k_collapse_level(const Node* bin, Node4* out, Collapse cq, int level) {
+// The node as the traversal reads it, from its children's boxes. The planes
+// lie on or outside the boxes; what the traversal rounds off is a few ulp of
+// the coordinates, inside the pad of the leaf boxes. An axis that is not
+// finite (a surfel at infinity or not a number) bounds nothing.
+__device__ __forceinline__ void write_nodeq(NodeQ* out, const float (&lo)[4][3], const float (&hi)[4][3],
+                                            const int (&ref)[4]) {
+  NodeQ nq;
+  float o[3];
+  nq.exps = 0u;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    float l = __builtin_inff(), h = -__builtin_inff();
+    for (int k = 0; k < 4; ++k) {
+      if (ref[k] == NODE4_EMPTY) continue;
+      l = fminf(l, lo[k][a]);
+      h = fmaxf(h, hi[k][a]);
+    }
+    uint32_t ql = 0u, qh = 0u;
+    const double ext = (double)h - (double)l;
+    if (fabsf(l) < 1e18f && fabsf(h) < 1e18f && ext >= 0.0) {
+      // the smallest step with ext <= 255 steps (at least 2^-126: a normal float)
+      int e = -126;
+      if (ext > 0.0) {
+        e = ilogb(ext) - 8;
+        while (ldexp(255.0, e) < ext) ++e;
+        if (e < -126) e = -126;
+      }
+      const double inv = ldexp(1.0, -e);
+      for (int k = 0; k < 4; ++k) {
+        // an empty slot, and a box that is not a number, span the node
+        double a0 = floor(((double)lo[k][a] - (double)l) * inv), a1 = ceil(((double)hi[k][a] - (double)l) * inv);
+        if (ref[k] == NODE4_EMPTY || !(a0 >= 0.0 && a0 <= 255.0)) a0 = 0.0;
+        if (ref[k] == NODE4_EMPTY || !(a1 >= 0.0 && a1 <= 255.0)) a1 = 255.0;
+        ql |= (uint32_t)a0 << (8 * k);
+        qh |= (uint32_t)a1 << (8 * k);
+      }
+      o[a] = l;
+      nq.exps |= (uint32_t)(e + 127) << (8 * a);
+    } else {
+      o[a] = 0.0f;
+      nq.exps |= 255u << (8 * a);
+    }
+    nq.q[a] = ql;
+    nq.q[3 + a] = qh;
+  }
+  nq.ox = o[0];
+  nq.oy = o[1];
+  nq.oz = o[2];
+  for (int k = 0; k < 4; ++k) nq.ref[k] = ref[k];
+  nq.pad[0] = nq.pad[1] = 0;
+  *out = nq;
+}
+
+__global__ void k_collapse_level(const Node* bin, Node4* out, NodeQ* outq, Collapse cq, int level) {
   const int count = cq.counts[level];
   const int2* qin = cq.q[level & 1];
   int2* qout = cq.q[(level + 1) & 1];
@@ -602,41 +655,45 @@ __global__ void k_collapse_level(const Node* bin, Node4* out, Collapse cq, int l
     }
     m.ref = make_int4(dst[0], dst[1], dst[2], dst[3]);
     m.src = make_int4(src[0], src[1], src[2], src[3]);
+    write_nodeq(outq + job.y, lo, hi, dst);
   }
 }
 
 // Refit of 4-wide boxes from the binary tree (internal children) and the
 // surfel boxes (leaves).
-__global__ void k_node4_boxes(const Node* bin, Node4* out, const BvhHeader* h, const float* box,
+__global__ void k_node4_boxes(const Node* bin, Node4* out, NodeQ* outq, const BvhHeader* h, const float* box,
                               const int32_t* perm, int64_t n) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= h->n_nodes4) return;
   Node4& nd = out[m];
   const int s[4] = {nd.src.x, nd.src.y, nd.src.z, nd.src.w};
+  const int ref[4] = {nd.ref.x, nd.ref.y, nd.ref.z, nd.ref.w};
   float* bf = reinterpret_cast<float*>(nd.b);
+  float lo[4][3] = {}, hi[4][3] = {};
+#pragma unroll
   for (int k = 0; k < 4; ++k) {
     if (s[k] == NODE4_EMPTY) continue;
-    float lo[3], hi[3];
     if (s[k] >= 0) {
       float l2[3], h2[3];
-      child_box(bin[s[k]], 0, lo, hi);
+      child_box(bin[s[k]], 0, lo[k], hi[k]);
       child_box(bin[s[k]], 1, l2, h2);
       for (int a = 0; a < 3; ++a) {
-        lo[a] = fminf(lo[a], l2[a]);
-        hi[a] = fmaxf(hi[a], h2[a]);
+        lo[k][a] = fminf(lo[k][a], l2[a]);
+        hi[k][a] = fmaxf(hi[k][a], h2[a]);
       }
     } else {
       const int64_t i = perm[~s[k]];
       for (int a = 0; a < 3; ++a) {
-        lo[a] = box[a * n + i];
-        hi[a] = box[(3 + a) * n + i];
+        lo[k][a] = box[a * n + i];
+        hi[k][a] = box[(3 + a) * n + i];
       }
     }
     for (int a = 0; a < 3; ++a) {
-      bf[k * 6 + a] = lo[a];
-      bf[k * 6 + 3 + a] = hi[a];
+      bf[k * 6 + a] = lo[k][a];
+      bf[k * 6 + 3 + a] = hi[k][a];
     }
   }
+  write_nodeq(outq + m, lo, hi, ref);
 }
 
 __global__ void k_collapse_finish(const int32_t* counts, BvhHeader* h) {
@@ -721,6 +778,7 @@ BvhLayout bvh_layout(void* base, int64_t n) {
   l.hdr = c.take<BvhHeader>(1);
   l.nodes = c.take<Node>(n > 1 ? n - 1 : 1);
   l.nodes4 = c.take<Node4>(n > 1 ? n - 1 : 1);
+  l.nodesq = c.take<NodeQ>(n > 1 ? n - 1 : 1);
   l.recs = c.take<Record>(n);
   l.perm = c.take<int32_t>(n);
   l.inv = c.take<int32_t>(n);
@@ -735,6 +793,7 @@ void bvh_attach(eag_bvh* b, const BvhLayout& l) {
   b->hdr = l.hdr;
   b->nodes = l.nodes;
   b->nodes4 = l.nodes4;
+  b->nodesq = l.nodesq;
   b->recs = l.recs;
   b->perm = l.perm;
   b->inv = l.inv;
@@ -760,7 +819,7 @@ static void geometry_pass(const eag_surfels* s, eag_bvh* b, const BuildWs& w, hi
 
 void build_bvh(const eag_surfels* s, eag_bvh* b, void* ws, size_t ws_bytes, hipStream_t st) {
   const int64_t n = s->n;
-  if (!b->hdr || !b->nodes || !b->nodes4 || !b->recs || !b->perm || !b->inv || !b->leaf_parent || !b->node_parent || !b->levels)
+  if (!b->hdr || !b->nodes || !b->nodes4 || !b->nodesq || !b->recs || !b->perm || !b->inv || !b->leaf_parent || !b->node_parent || !b->levels)
     fail(EAG_ERR_INTERNAL, "bvh handle without its device arrays");
   BuildWs w = build_ws(ws, n);
   if (ws_bytes < w.bytes) fail(EAG_ERR_WORKSPACE_TOO_SMALL, "build workspace too small");
@@ -795,7 +854,8 @@ void build_bvh(const eag_surfels* s, eag_bvh* b, void* ws, size_t ws_bytes, hipS
     const unsigned g = std::min<unsigned>(blocks(n), 1024u);
     const int levels = collapse_levels(b->idx_bits);
     for (int level = 0; level < levels; ++level)
-      hipLaunchKernelGGL(k_collapse_level, dim3(g), dim3(256), 0, st, b->nodes, b->nodes4, cq, level);
+      hipLaunchKernelGGL(k_collapse_level, dim3(g), dim3(256), 0, st, b->nodes, b->nodes4, b->nodesq, cq,
+                         level);
     hipLaunchKernelGGL(k_collapse_finish, dim3(1), dim3(64), 0, st, w.counts, b->hdr);
     check_hip(hipGetLastError(), "collapse launch");
   }
@@ -804,7 +864,7 @@ void build_bvh(const eag_surfels* s, eag_bvh* b, void* ws, size_t ws_bytes, hipS
 
 void refit_bvh(const eag_surfels* s, eag_bvh* b, void* ws, size_t ws_bytes, hipStream_t st) {
   const int64_t n = s->n;
-  if (!b->hdr || !b->nodes || !b->nodes4 || !b->recs || !b->perm || !b->levels)
+  if (!b->hdr || !b->nodes || !b->nodes4 || !b->nodesq || !b->recs || !b->perm || !b->levels)
     fail(EAG_ERR_INTERNAL, "bvh handle without its device arrays");
   BuildWs w = build_ws(ws, n);
   if (ws_bytes < w.bytes) fail(EAG_ERR_WORKSPACE_TOO_SMALL, "refit workspace too small");
@@ -824,8 +884,8 @@ void refit_bvh(const eag_surfels* s, eag_bvh* b, void* ws, size_t ws_bytes, hipS
                          b->nodes, (const int32_t*)b->levels, t);
     // (the 4-wide node count is on the device: the grid covers the n - 1 it
     // can reach)
-    hipLaunchKernelGGL(k_node4_boxes, dim3(blocks(n - 1)), dim3(256), 0, st, b->nodes, b->nodes4, h, w.box,
-                       b->perm, n);
+    hipLaunchKernelGGL(k_node4_boxes, dim3(blocks(n - 1)), dim3(256), 0, st, b->nodes, b->nodes4, b->nodesq, h,
+                       w.box, b->perm, n);
   }
   check_hip(hipGetLastError(), "refit launch");
   check_hip(hipEventRecord(b->built, st), "refit event");

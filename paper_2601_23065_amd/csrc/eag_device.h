@@ -44,6 +44,24 @@ struct __align__(16) Node4 {
   int4 src;
 };
 
+// What a traversal reads of a 4-wide node, 64 B: the children's boxes as
+// 8-bit steps from the node's lower corner, and their references. Along axis
+// a, child k spans [o + qlo step, o + qhi step] with step a power of two, which
+// holds its box (rounded outward). q.a holds axis a's lower steps, q.(3 + a)
+// its upper ones, child k in byte k. exps has the steps' biased exponents in
+// bytes 0 to 2; 255 (step +inf, all q 0) makes every plane of the axis a NaN,
+// which bounds nothing: an axis on which the box is not finite.
+// A visit is limited by the L1, which takes one lane's 16-byte access a cycle
+// when 64 lanes read 64 places: 4 of them here, where the exact boxes take 7.
+struct __align__(16) NodeQ {
+  float ox, oy, oz;
+  uint32_t exps;
+  uint32_t q[6];
+  int32_t ref[4];
+  int32_t pad[2];
+};
+static_assert(sizeof(NodeQ) == 64, "one node per half cache line");
+
 // Geometry record of one surfel in sorted order, 48 B (three float4 loads):
 //   p.x p.y p.z sigma | q.w q.x q.y q.z | s_u s_v index -
 // with q the caller's (unnormalised) quaternion and index the original surfel
@@ -169,7 +187,7 @@ __device__ __forceinline__ uint64_t key_max(uint64_t a, uint64_t b) {
 }
 
 struct TraceCtx {
-  const Node4* nodes;
+  const NodeQ* nodes;
   const Record* recs;
   const Attr* attrs;
   const int32_t* inv;      // sorted position of each surfel
@@ -312,7 +330,11 @@ struct SegOut {
 
 enum { Q_ALL = 0, Q_RADIANCE = 1 };
 
+// byte k as a float (one conversion instruction)
+__device__ __forceinline__ float q_byte(uint32_t w, int k) { return (float)((w >> (8 * k)) & 255u); }
+
 // Slab test of a box against [tlo, thi]; returns the entry distance or +inf.
+// (for exact boxes: the light pdf's tree; node_visit has its own over NodeQ)
 // OiW = O * iW per component: each plane distance (l - O) / W is one fused
 // multiply-add, l * iW - OiW. Its rounding error, in space, is a few ulp of
 // |O| and |l|, far inside the pad that every leaf box carries around its
@@ -578,41 +600,47 @@ __device__ __forceinline__ bool round_begin(const TraceCtx& tc, S& s, Round& r, 
 template <class S>
 __device__ __forceinline__ void node_visit(const TraceCtx& tc, S& s, Round& r, TravStack& st, int* pend) {
   if constexpr (S::kStats) ++s.visits;
-  const Node4* nd = elem(tc.nodes, (uint32_t)r.ref);
-  const int4 cr = nd->ref;
-  const float4* bb = nd->b;
-  const float4 b0 = bb[0], b1 = bb[1], b2 = bb[2], b3 = bb[3], b4 = bb[4], b5 = bb[5];
-  float e[4];
-  e[0] = slab(b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, s.OiW, s.iW, r.tlo0, r.t_cut);
-  e[1] = slab(b1.z, b1.w, b2.x, b2.y, b2.z, b2.w, s.OiW, s.iW, r.tlo0, r.t_cut);
-  e[2] = slab(b3.x, b3.y, b3.z, b3.w, b4.x, b4.y, s.OiW, s.iW, r.tlo0, r.t_cut);
-  e[3] = slab(b4.z, b4.w, b5.x, b5.y, b5.z, b5.w, s.OiW, s.iW, r.tlo0, r.t_cut);
-  const int c[4] = {cr.x, cr.y, cr.z, cr.w};
-  float ie[4];
-  int ic[4];
+  const float4* np = reinterpret_cast<const float4*>(elem(tc.nodes, (uint32_t)r.ref));
+  const float4 h = np[0];
+  const uint4 u0 = *reinterpret_cast<const uint4*>(np + 1), u1 = *reinterpret_cast<const uint4*>(np + 2);
+  const uint2 u2 = *reinterpret_cast<const uint2*>(np + 3);
+  const uint32_t ex = __float_as_uint(h.w);
+  // plane distances are q a + b per axis
+  const float ax = __uint_as_float((ex & 255u) << 23) * s.iW.x, bx = fmaf(h.x, s.iW.x, -s.OiW.x);
+  const float ay = __uint_as_float((ex & 0xff00u) << 15) * s.iW.y, by = fmaf(h.y, s.iW.y, -s.OiW.y);
+  const float az = __uint_as_float((ex & 0xff0000u) << 7) * s.iW.z, bz = fmaf(h.z, s.iW.z, -s.OiW.z);
+  const bool gx = s.iW.x < 0.0f, gy = s.iW.y < 0.0f, gz = s.iW.z < 0.0f;
+  // the four children's near and far planes
+  const uint32_t nx = gx ? u0.w : u0.x, fx = gx ? u0.x : u0.w;
+  const uint32_t ny = gy ? u1.x : u0.y, fy = gy ? u0.y : u1.x;
+  const uint32_t nz = gz ? u1.y : u0.z, fz = gz ? u0.z : u1.y;
+  const int c[4] = {(int)u1.z, (int)u1.w, (int)u2.x, (int)u2.y};
+  uint64_t ek[4];
   int ni = 0;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    // a missed box reports +inf (the slab test already holds the entry to the
-    // widened cut), which must not pass while the cut is infinite
-    const bool m = c[k] != NODE4_EMPTY && e[k] < __builtin_inff();
+    const float tn = fmaxf(fmaxf(fmaf(q_byte(nx, k), ax, bx), fmaf(q_byte(ny, k), ay, by)),
+                           fmaxf(fmaf(q_byte(nz, k), az, bz), r.tlo0));
+    // widen the exit so that rounding (and the float32 copy of the ray) never
+    // rejects a box the ray touches
+    const float tf = fminf(fminf(fmaf(q_byte(fx, k), ax, bx), fmaf(q_byte(fy, k), ay, by)),
+                           fminf(fmaf(q_byte(fz, k), az, bz), r.t_cut)) * 1.000002f + 1e-6f;
+    const bool m = c[k] != NODE4_EMPTY && tn <= tf;
     // leaves are queued without a branch: the slot past the queue is always
     // written (nodes are visited only while np <= PEND - 4, so it exists)
     pend[r.np * TRACE_BLOCK] = ~c[k];
     r.np += (m && c[k] < 0) ? 1 : 0;
-    ie[k] = (m && c[k] >= 0) ? e[k] : __builtin_inff();
-    ic[k] = c[k];
-    ni += (m && c[k] >= 0) ? 1 : 0;
+    // (entry, child), ordered as a double by the entry: the float's bits in
+    // the high word make a finite double, +inf included
+    const bool mi = m && c[k] >= 0;
+    ek[k] = ((uint64_t)__float_as_uint(mi ? tn : __builtin_inff()) << 32) | (uint32_t)c[k];
+    ni += mi ? 1 : 0;
   }
   if (ni > 0) {
-    // sort the four (entry, child) pairs by entry, misses (+inf) last
-#define EAG_CSWAP(i, j)                                  \
-    if (ie[j] < ie[i]) {                                 \
-      const float tf = ie[i]; ie[i] = ie[j]; ie[j] = tf; \
-      const int tc_ = ic[i]; ic[i] = ic[j]; ic[j] = tc_; \
-    }
-    EAG_CSWAP(0, 1) EAG_CSWAP(2, 3) EAG_CSWAP(0, 2) EAG_CSWAP(1, 3) EAG_CSWAP(1, 2)
-#undef EAG_CSWAP
+    // sort by entry, misses (+inf) last
+    cswap_key(ek[0], ek[1]); cswap_key(ek[2], ek[3]); cswap_key(ek[0], ek[2]); cswap_key(ek[1], ek[3]);
+    cswap_key(ek[1], ek[2]);
+    const int ic[4] = {(int)(uint32_t)ek[0], (int)(uint32_t)ek[1], (int)(uint32_t)ek[2], (int)(uint32_t)ek[3]};
     // push the others farthest first: bottom to top ic[ni-1] .. ic[1]
     if (st.sp + 3 <= STACK_LDS) {
       // branch-free: three slots written, the stack grows by ni - 1

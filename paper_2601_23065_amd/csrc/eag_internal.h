@@ -14,6 +14,7 @@ namespace eag {
 
 struct Node;
 struct Node4;
+struct NodeQ;
 struct Record;
 struct Attr;
 struct CamDev;
@@ -70,6 +71,7 @@ struct eag_bvh {
   eag::BvhHeader* hdr;
   eag::Node* nodes;
   eag::Node4* nodes4;
+  eag::NodeQ* nodesq;     // nodes4 as the traversal reads it
   int32_t n_nodes4;       // synced
   int32_t depth4;         // synced
   eag::Record* recs;
@@ -123,6 +125,7 @@ struct BvhLayout {
   BvhHeader* hdr;
   Node* nodes;
   Node4* nodes4;
+  NodeQ* nodesq;
   Record* recs;
   int32_t* perm;
   int32_t* inv;

@@ -79,7 +79,7 @@ __global__ void __launch_bounds__(256) k_trace_rays(TraceCtx tc, int64_t n_rays,
 
 TraceCtx make_ctx(const eag_bvh* b, const Attr* attrs, const eag_trace_params* p, const TraceSetup& ts) {
   TraceCtx tc;
-  tc.nodes = b->nodes4;
+  tc.nodes = b->nodesq;
   tc.recs = b->recs;
   tc.attrs = attrs;
   tc.inv = b->inv;
