@@ -159,6 +159,14 @@ __device__ __forceinline__ D3 cosine_dir(D3 n, double u0, double u1) {
             r * c * b1.z + r * s * b2.z + z * n.z);
 }
 
+// Element i of an array of at most 4 GiB (2^23 surfels: 1 GiB of nodes at
+// most). A 32-bit byte offset beside a uniform base is an addressing mode of
+// its own; a 64-bit one costs each lane its address arithmetic and registers.
+template <class T>
+__device__ __forceinline__ const T* elem(const T* base, uint32_t i) {
+  return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (uint32_t)(i * (uint32_t)sizeof(T)));
+}
+
 // ---------------------------------------------------------------------------
 // Order key: (bucket, original index) packed into 64 bits, bucket =
 // floor(t / dq) (dq a power of two) or the float bits of t when dq == 0.
@@ -202,32 +210,42 @@ struct TraceCtx {
   // Mapped host word receiving device status codes (a key beyond the last
   // bucket); null: not reported.
   unsigned int* status;
-  // Optional per-lane hit list (null: off). Entry j of this lane is
-  // hl[j * HL_STRIDE]. A lane's entries are contiguous: appends happen at
+  // Per-lane hit lists (segments without one: null), HL_CAP entries each; this lane's
+  // begin at entry hl_at. A lane's entries are contiguous: appends happen at
   // different times in different lanes, and a lane filling its own cache
   // lines writes each line back once.
   uint64_t* hl;
+  uint32_t hl_at;
+  uint32_t hl_bytes;       // of all lanes' lists
 };
 
 constexpr int HL_CAP = 256;        // entries per lane (a multiple of 8: the list is scanned 8 at a time)
-constexpr int HL_STRIDE = 1;
-static_assert(HL_CAP % 8 == 0 && HL_STRIDE == 1, "hit-list scan reads 8 contiguous entries");
+static_assert(HL_CAP % 8 == 0, "hit-list scan reads 8 contiguous entries");
 
-__device__ __noinline__ void report_key_range(unsigned int* status) {
+__device__ __forceinline__ void report_key_range(unsigned int* status) {
   if (status) __hip_atomic_fetch_or(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Write v to entry j of this lane's hit list if `on`. One instruction that
+// every lane issues (a lane that is not on passes an offset past the buffer's
+// end, which the buffer store drops by definition): behind a branch, the
+// compiler could not count the stores in flight, and would wait for all of
+// them before it uses a record loaded earlier.
+__device__ __forceinline__ void hl_store(const TraceCtx& tc, int j, uint64_t v, bool on) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 w = {(uint32_t)v, (uint32_t)(v >> 32)};
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(tc.hl, 0, (int)tc.hl_bytes, 0x00020000);
+  __builtin_amdgcn_raw_buffer_store_b64(w, rs, (int)(on ? (tc.hl_at + (uint32_t)j) * 8u : 0xffffffffu), 0, 0);
 }
 __device__ __forceinline__ uint64_t pack_key(const TraceCtx& tc, uint32_t bucket, uint32_t idx) {
   return ((uint64_t)bucket << tc.idx_bits) | (uint64_t)idx | KEY_BIAS;
 }
 __device__ __forceinline__ uint64_t make_key(const TraceCtx& tc, double t, uint32_t idx) {
-  uint32_t bucket;
-  if (tc.inv_dq > 0.0) {
-    const double b = floor(t * tc.inv_dq);
-    bucket = b >= (double)tc.max_bucket ? tc.max_bucket : (uint32_t)b;
-  } else {
-    bucket = __float_as_uint((float)t);
-  }
-  return pack_key(tc, bucket, idx);
+  // (both kinds of bucket: a branch would split the leaf test)
+  const double b = floor(t * tc.inv_dq);
+  const uint32_t bq = b >= (double)tc.max_bucket ? tc.max_bucket : (uint32_t)b;
+  const uint32_t bt = __float_as_uint((float)t);
+  return pack_key(tc, tc.inv_dq > 0.0 ? bq : bt, idx);
 }
 __device__ __forceinline__ uint64_t make_key_b(const TraceCtx& tc, uint32_t bucket, uint32_t idx) {
   return pack_key(tc, bucket >= tc.max_bucket ? tc.max_bucket : bucket, idx);
@@ -247,14 +265,14 @@ __device__ __forceinline__ uint64_t next_bucket_key(const TraceCtx& tc, uint64_t
 // smallest t that can carry the given key's bucket (for culling)
 __device__ __forceinline__ float key_tlo(const TraceCtx& tc, uint64_t k) {
   const uint32_t b = key_bucket(tc, k);
-  if (tc.inv_dq > 0.0) return (float)((double)b * tc.dq);
-  return __uint_as_float(b);
+  const float tq = (float)((double)b * tc.dq);
+  return tc.inv_dq > 0.0 ? tq : __uint_as_float(b);
 }
 // largest t whose bucket does not exceed the key's bucket
 __device__ __forceinline__ float key_thi(const TraceCtx& tc, uint64_t k) {
   const uint32_t b = key_bucket(tc, k);
-  if (tc.inv_dq > 0.0) return (float)((double)(b + 1u) * tc.dq);
-  return __uint_as_float(b);
+  const float tq = (float)((double)(b + 1u) * tc.dq);
+  return tc.inv_dq > 0.0 ? tq : __uint_as_float(b);
 }
 
 // ---------------------------------------------------------------------------
@@ -267,14 +285,6 @@ __device__ __forceinline__ float key_thi(const TraceCtx& tc, uint64_t k) {
 // evaluation could not settle, so a float screen in front of it only added
 // instructions.
 // ---------------------------------------------------------------------------
-// Element i of an array of at most 4 GiB (2^23 surfels: 1 GiB of nodes at
-// most). A 32-bit byte offset beside a uniform base is an addressing mode of
-// its own; a 64-bit one costs each lane its address arithmetic and registers.
-template <class T>
-__device__ __forceinline__ const T* elem(const T* base, uint32_t i) {
-  return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (uint32_t)(i * (uint32_t)sizeof(T)));
-}
-
 __device__ __forceinline__ Record load_record(const Record* recs, uint32_t pos) {
   const float4* p = reinterpret_cast<const float4*>(elem(recs, pos));
   Record r;
@@ -391,13 +401,11 @@ struct TravStack {
 // that falls off the end (the old last entry, or the candidate itself when it
 // is not below it).
 __device__ __forceinline__ uint64_t kbuf_insert(uint64_t (&kk)[KBUF], uint64_t key) {
+  const uint64_t spill = key_max(key, kk[KBUF - 1]);
 #pragma unroll
-  for (int j = 0; j < KBUF; ++j) {
-    const uint64_t lo = key_min(kk[j], key);
-    key = key_max(kk[j], key);
-    kk[j] = lo;
-  }
-  return key;
+  for (int j = KBUF - 1; j > 0; --j) kk[j] = key_max(kk[j - 1], key_min(kk[j], key));
+  kk[0] = key_min(kk[0], key);
+  return spill;
 }
 
 // Compare-exchange: afterwards a <= b.
@@ -478,14 +486,15 @@ struct Seg {
 };
 
 // A segment with its statistics, kept only where the caller reads them: they
-// cost a register each, and registers are what the runner's waves have least of.
-template <bool DACC, bool STATS>
+// cost a register each, and registers are what the runner's waves have least
+// of. LIST: it has a hit list (tc.hl is not null).
+template <bool DACC, bool STATS, bool LIST>
 struct SegStats : Seg<DACC> {
-  static constexpr bool kStats = false;
+  static constexpr bool kStats = false, kList = LIST;
 };
-template <bool DACC>
-struct SegStats<DACC, true> : Seg<DACC> {
-  static constexpr bool kStats = true;
+template <bool DACC, bool LIST>
+struct SegStats<DACC, true, LIST> : Seg<DACC> {
+  static constexpr bool kStats = true, kList = LIST;
   int32_t nhits, rounds, tests, visits;
 };
 
@@ -539,12 +548,12 @@ __device__ __forceinline__ bool round_begin(const TraceCtx& tc, S& s, Round& r, 
   r.over = false;
   r.partial = false;
   bool traverse = true;
-  if (s.lhi > s.last + 1) {
+  if (S::kList && s.lhi > s.last + 1) {
     // keys in (last, lhi) from the list (entries at or below last were
     // blended by earlier rounds and are skipped, not removed)
     // (loaded 8 at a time: entries up to HL_CAP are this lane's, those past
     // nl are ignored)
-    const uint64_t* const hl = tc.hl;
+    const uint64_t* const hl = elem(tc.hl, tc.hl_at);
     int w = 0;
     for (int j = 0; j < s.nl; j += 8) {
       uint64_t e[8];
@@ -688,65 +697,78 @@ __device__ __forceinline__ uint64_t leaf_key(const TraceCtx& tc, const Record& r
   const double su2 = (double)rec.s_idx.x * rec.s_idx.x, sv2 = (double)rec.s_idx.y * rec.s_idx.y;
   const double up = dot(yv, cu), vp = dot(yv, cv);
   // (multiplied through by s_u^2 s_v^2, all positive: no division)
-  const bool hit = fabs(den) > 1e-12 * q2n && rec.p_sigma.w > 0.0f && t > tc.t_min &&
-                   up * up * sv2 + vp * vp * su2 <= tc.k2 * q2n * q2n * su2 * sv2;
+  // (&, not &&: nothing is skipped, so nothing is branched around)
+  const bool hit = (fabs(den) > 1e-12 * q2n) & (rec.p_sigma.w > 0.0f) & (t > tc.t_min) &
+                   (up * up * sv2 + vp * vp * su2 <= tc.k2 * q2n * q2n * su2 * sv2);
   const uint64_t key = make_key(tc, t, rec_index(rec));
-  const bool qual = hit && key > floor_key;
+  const bool qual = hit & (key > floor_key);
   // A hit in the last bucket may stand for a farther one that the key
   // saturated into it, whose order among the others is then unknown: the
   // launch reports it (a rare branch; never taken within the range).
   if (qual && tc.inv_dq > 0.0 && key_bucket(tc, key) >= tc.max_bucket) report_key_range(tc.status);
-  return qual && key < cutlim ? key : KEY_NONE;
+  return qual & (key < cutlim) ? key : KEY_NONE;
 }
 
-// Take a qualifying key into the round. The list needs only keys beyond the
-// round's final KBUF-th key: a key goes there when the k-buffer rejects it
-// or later evicts it.
+// Take a key into the round (KEY_NONE: nothing happens). The list needs only
+// keys beyond the round's final KBUF-th key: a key goes there when the
+// k-buffer rejects it or later evicts it. Everything here runs without a
+// branch: a wave nearly always holds a lane for either side.
 template <class S>
 __device__ __forceinline__ void take_key(const TraceCtx& tc, S& s, Round& r, uint64_t key) {
-  // The insert runs without a branch: a key not below the last entry passes
-  // through the chain unchanged and comes back as the spill.
+  // a key not below the last entry leaves the buffer unchanged and comes back
+  // as the spill
   const bool ins = key < r.kk[KBUF - 1];
   const uint64_t spill = kbuf_insert(r.kk, key);   // KEY_NONE while the buffer is not full
-  r.cnt += ins ? 1 : 0;
-  if (ins && r.cnt >= KBUF) {
-    r.cnt = KBUF;
-    r.t_cut = key_thi(tc, r.kk[KBUF - 1]) * 1.000002f + 1e-6f;
-    r.cut_key = next_bucket_key(tc, r.kk[KBUF - 1]);
-  }
-  if (tc.hl && spill < r.cut_key) {
-    if (s.nl < HL_CAP) tc.hl[(s.nl++) * HL_STRIDE] = spill;
-    else r.over = true;
+  r.cnt = ins && r.cnt < KBUF ? r.cnt + 1 : r.cnt;
+  const bool full = r.kk[KBUF - 1] != KEY_NONE;
+  const float tc_new = key_thi(tc, r.kk[KBUF - 1]) * 1.000002f + 1e-6f;
+  const uint64_t ck_new = next_bucket_key(tc, r.kk[KBUF - 1]);
+  r.t_cut = full ? tc_new : r.t_cut;
+  r.cut_key = full ? ck_new : r.cut_key;
+  if constexpr (S::kList) {
+    const bool app = spill < r.cut_key;   // (KEY_NONE is not)
+    const bool room = s.nl < HL_CAP;
+    hl_store(tc, s.nl, spill, app && room);
+    s.nl += app && room ? 1 : 0;
+    r.over = r.over || (app && !room);
   }
 }
 
-__device__ __forceinline__ uint64_t round_cutlim(const TraceCtx& tc, const Round& r) {
-  return tc.hl ? r.cut_key : r.kk[KBUF - 1];
+template <class S>
+__device__ __forceinline__ uint64_t round_cutlim(const Round& r) {
+  return S::kList ? r.cut_key : r.kk[KBUF - 1];
 }
 
 // Test one postponed leaf of this lane's own ray and take its key.
 template <class S>
 __device__ __forceinline__ void leaf_eval(const TraceCtx& tc, S& s, Round& r, const Record& rec) {
   if constexpr (S::kStats) ++s.tests;
-  const uint64_t key = leaf_key(tc, rec, s.O, s.W, r.floor_key, round_cutlim(tc, r));
-  if (key != KEY_NONE) take_key(tc, s, r, key);
+  const uint64_t key = leaf_key(tc, rec, s.O, s.W, r.floor_key, round_cutlim<S>(r));
+  take_key(tc, s, r, key);
 }
 
 // Test postponed leaves, most recent first. The next leaf's record is loaded
 // before the current one is tested, so that its latency overlaps the test's
-// arithmetic. A lane whose traversal continues stops once fewer than
+// arithmetic. The load is not behind a branch (a lane without a next leaf
+// loads the current one again): the compiler then knows how many loads are in
+// flight and waits for the current record alone; behind a branch it waited
+// for both, and every test paid the whole latency. A lane whose traversal continues stops once fewer than
 // LEAF_MIN_LANES lanes of the wave still hold leaves, and keeps the rest for
 // its next leaf phase; a lane whose traversal has ended tests all of them.
 constexpr int LEAF_MIN_LANES = 16;
 template <class S>
 __device__ __forceinline__ void leaf_phase(const TraceCtx& tc, S& s, Round& r, int* pend) {
   if (r.np <= 0) return;
-  Record rec = load_record(tc.recs, (uint32_t)pend[(--r.np) * TRACE_BLOCK]);
+  uint32_t pos = (uint32_t)pend[(--r.np) * TRACE_BLOCK];
+  Record rec = load_record(tc.recs, pos);
   while (true) {
     const bool more = r.np > 0 && !(r.trav && __popcll(__ballot(r.np > 0)) < LEAF_MIN_LANES);
-    Record nrec;
-    if (more) nrec = load_record(tc.recs, (uint32_t)pend[(--r.np) * TRACE_BLOCK]);
+    r.np -= more ? 1 : 0;
+    const uint32_t queued = (uint32_t)pend[r.np * TRACE_BLOCK];
+    pos = more ? queued : pos;
+    const Record nrec = load_record(tc.recs, pos);
     leaf_eval(tc, s, r, rec);
+    __builtin_amdgcn_sched_barrier(0);   // the next record is not waited for before this one is done
     if (!more) break;
     rec = nrec;
   }
@@ -755,7 +777,7 @@ __device__ __forceinline__ void leaf_phase(const TraceCtx& tc, S& s, Round& r, i
 // After a traversal round: what the hit list now covers.
 template <class S>
 __device__ __forceinline__ void round_end_traversal(const TraceCtx& tc, S& s, const Round& r) {
-  if (tc.hl) s.lhi = r.over ? 0ull : (r.cnt == KBUF ? r.cut_key : KEY_NONE);
+  if constexpr (S::kList) s.lhi = r.over ? 0ull : (r.cnt == KBUF ? r.cut_key : KEY_NONE);
 }
 
 // Traverse one round to completion for this lane.
@@ -790,24 +812,18 @@ __device__ __forceinline__ void blend_round(const TraceCtx& tc, S& s, Round& r, 
   uint32_t at_pos[KBUF];
 #pragma unroll
   for (int m = 0; m < KBUF; ++m) at_pos[m] = (uint32_t)*elem(tc.inv, m < r.cnt ? key_idx(tc, r.kk[m]) : 0u);
-  // the next hit's record and attributes are loaded while the current one
-  // is blended
-  Record rec;
-  Attr at;
-  if (r.cnt > 0) {
-    rec = load_record(tc.recs, at_pos[0]);
-    at = *elem(tc.attrs, at_pos[0]);
-  }
+  __builtin_amdgcn_sched_barrier(0);   // all of them, before anything waits for the first
+  // the next hit's record and attributes are loaded while the current one is
+  // blended (always: entries past the round's hits are surfel 0's; a load
+  // behind a branch would not overlap, as in leaf_phase)
+  Record rec = load_record(tc.recs, at_pos[0]);
+  Attr at = *elem(tc.attrs, at_pos[0]);
   for (int j = 0; j < r.cnt && !s.done; ++j) {
     const uint32_t pos = at_pos[0];
 #pragma unroll
     for (int m = 0; m < KBUF - 1; ++m) at_pos[m] = at_pos[m + 1];
-    Record nrec;
-    Attr nat;
-    if (j + 1 < r.cnt) {
-      nrec = load_record(tc.recs, at_pos[0]);
-      nat = *elem(tc.attrs, at_pos[0]);
-    }
+    const Record nrec = load_record(tc.recs, at_pos[0]);
+    const Attr nat = *elem(tc.attrs, at_pos[0]);
     // t, u, v and the unit normal from the columns of the unnormalised
     // quaternion's rotation, |q|^2 (t_u, t_v, n): no square root, and one
     // reciprocal c = 1 / (|q|^2 s_u s_v) for u^2 + v^2 and the normal's scale
@@ -847,6 +863,7 @@ __device__ __forceinline__ void blend_round(const TraceCtx& tc, S& s, Round& r, 
     if constexpr (S::kStats) ++s.nhits;
     s.T *= (1.0 - a);
     if (s.T < tc.T_min) s.done = true;
+    __builtin_amdgcn_sched_barrier(0);   // the next record is not waited for before this one is done
     rec = nrec;
     at = nat;
   }
@@ -867,7 +884,7 @@ __device__ SegOut trace_segment_cb(const TraceCtx& tc, D3 O, D3 W, HitFn& on_hit
   st.ovf = s_ovf;
   st.sp = 0;
   int* pend = s_pend + threadIdx.x;   // this lane's queue of postponed leaves
-  SegStats<DACC, true> s;
+  SegStats<DACC, true, false> s;
   seg_begin(s, O, W);
   while (!s.done) {
     Round r;

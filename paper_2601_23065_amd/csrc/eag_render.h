@@ -105,7 +105,7 @@ struct PtLaunch {
 // holds HL_CAP keys for each), and a launch that zeroes n counters.
 int64_t runner_lanes();
 void launch_zero_u64(unsigned long long* p, int n, hipStream_t st);
-// hitlist: pt_lanes() * HL_CAP keys, or null to trace without the list.
+// hitlist: runner_lanes() * HL_CAP keys.
 void launch_path_trace(const TraceCtx& tc, const PtLaunch& L, unsigned long long* work_counter,
                        unsigned long long* counters, uint64_t* hitlist, hipStream_t st);
 

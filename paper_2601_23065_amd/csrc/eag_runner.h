@@ -85,10 +85,12 @@ __device__ __forceinline__ void run_segments(const TraceCtx& tc, Src& src, unsig
   const int lane = (int)(threadIdx.x & 63);
   const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   TraceCtx tcl = tc;
-  tcl.hl = hitlist ? hitlist + ((int64_t)blockIdx.x * TRACE_BLOCK + threadIdx.x) * HL_CAP : nullptr;
+  tcl.hl = hitlist;
+  tcl.hl_at = (blockIdx.x * TRACE_BLOCK + threadIdx.x) * HL_CAP;
+  tcl.hl_bytes = gridDim.x * TRACE_BLOCK * HL_CAP * 8u;   // (256 MiB on 256 CUs)
 
   int stage = ST_IDLE;
-  SegStats<DACC, STATS> s;
+  SegStats<DACC, STATS, true> s;
   seg_begin(s, d3(0.0, 0.0, 0.0), d3(0.0, 0.0, 1.0));
   Round r;
   r.cnt = 0;
