@@ -168,8 +168,6 @@ __device__ __forceinline__ void emit_record(const GradRecs& gr, const GradPtrs& 
 // work item per (pixel, sample); only R1 = sum w r is used. Items of pixels
 // that did not take the reflect branch write zero adjoints without tracing.
 struct SecondaryAdjSource {
-  const Record* recs;
-  const Attr* attrs;
   const CamBatch* cams;
   int64_t hw;
   int32_t S;
@@ -227,11 +225,11 @@ struct SecondaryAdjSource {
     return true;
   }
 
-  __device__ __forceinline__ void operator()(uint32_t pos, double t, double alpha, double w, double Tb, D3 O, D3 W) {
-    const Record r = load_record(recs, pos);
+  __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, D3 O,
+                                             D3 W) {
     const uint32_t idx = rec_index(r);
     const Geo ge = surfel_geo(r);
-    const float4 rr = attrs[pos].r;
+    const float4 rr = at.r;
     const double c = gR1.x * rr.x + gR1.y * rr.y + gR1.z * rr.z;
     prefix += w * c;
     const double g_alpha = Tb * c - (G - prefix) / (1.0 - alpha);
@@ -285,8 +283,6 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
                                                                   GradRecs gr, double* adj, unsigned long long* work,
                                                                   uint64_t* hitlist) {
   SecondaryAdjSource src;
-  src.recs = tc.recs;
-  src.attrs = tc.attrs;
   src.cams = &cams;
   src.hw = hw;
   src.S = sp.spp;
@@ -320,8 +316,6 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
 // through Nt = N/|N| and Dt = D/A; dP = dL * mean R1 (or dR = dL for emitter
 // pixels). Missed pixels have nothing to reverse.
 struct CameraAdjSource {
-  const Record* recs;
-  const Attr* attrs;
   const CamBatch* cams;
   int64_t hw;
   SbParams sp;
@@ -378,11 +372,10 @@ struct CameraAdjSource {
     return true;
   }
 
-  __device__ __forceinline__ void operator()(uint32_t pos, double t, double alpha, double w, double Tb, D3 O, D3 W) {
-    const Record r = load_record(recs, pos);
+  __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, D3 O,
+                                             D3 W) {
     const uint32_t idx = rec_index(r);
     const Geo ge = surfel_geo(r);
-    const Attr at = attrs[pos];
     const D3 nn = ge.n;
     const double sgn = dot(W, nn) > 0.0 ? -1.0 : 1.0;   // n' = sgn n faces the origin
     const D3 rho = d3(at.rho_e.x, at.rho_e.y, at.rho_e.z), rad = d3(at.r.x, at.r.y, at.r.z);
@@ -413,8 +406,6 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
                                                                GradPtrs gp, GradRecs gr, unsigned long long* work,
                                                                uint64_t* hitlist) {
   CameraAdjSource src;
-  src.recs = tc.recs;
-  src.attrs = tc.attrs;
   src.cams = &cams;
   src.hw = hw;
   src.sp = sp;
@@ -445,8 +436,6 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
 // dE and then through the blended hits. Records carry the emissive gradient
 // w dE in row 10 (the albedo rows are otherwise unused here).
 struct Stage0AdjSource {
-  const Record* recs;
-  const Attr* attrs;
   const CamBatch* cams;
   int64_t hw;
   SbParams sp;
@@ -479,11 +468,10 @@ struct Stage0AdjSource {
     return true;
   }
 
-  __device__ __forceinline__ void operator()(uint32_t pos, double t, double alpha, double w, double Tb, D3 O, D3 W) {
-    const Record r = load_record(recs, pos);
+  __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, D3 O,
+                                             D3 W) {
     const uint32_t idx = rec_index(r);
     const Geo ge = surfel_geo(r);
-    const Attr at = attrs[pos];
     const double sgn = dot(W, ge.n) > 0.0 ? -1.0 : 1.0;   // n' = sgn n faces the origin
     const double c = sgn * dot(gN, ge.n) + gD * t + gR.x * at.r.x + gR.y * at.r.y + gR.z * at.r.z +
                      gE * at.rho_e.w;
@@ -510,8 +498,6 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
 k_stage0_bwd(TraceCtx tc, const CamBatch cams, int64_t hw, int32_t n_cams, SbParams sp, const float* state,
              const float* dimg, GradPtrs gp, GradRecs gr, unsigned long long* work, uint64_t* hitlist) {
   Stage0AdjSource src;
-  src.recs = tc.recs;
-  src.attrs = tc.attrs;
   src.cams = &cams;
   src.hw = hw;
   src.sp = sp;

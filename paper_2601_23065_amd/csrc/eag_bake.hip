@@ -56,7 +56,7 @@ struct ZeroBounceSource {
   float* rgb;
   int64_t item;
 
-  __device__ __forceinline__ void operator()(uint32_t, double, double, double, double, D3, D3) const {}
+  __device__ __forceinline__ void operator()(const Record&, const Attr&, double, double, double, double, D3, D3) const {}
 
   __device__ __forceinline__ bool start(int64_t wid, TraceCtx&, D3& O, D3& W) {
     item = wid;
@@ -74,7 +74,7 @@ struct ZeroBounceSource {
   }
 };
 
-__global__ void __launch_bounds__(TRACE_BLOCK) k_zero_bounce(TraceCtx tc, const CamBatch cams, int64_t hw,
+__global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(2))) k_zero_bounce(TraceCtx tc, const CamBatch cams, int64_t hw,
                                                             int32_t n_cams, SbParams sp, float* rgb,
                                                             unsigned long long* work, uint64_t* hitlist) {
   ZeroBounceSource src;
@@ -87,7 +87,6 @@ __global__ void __launch_bounds__(TRACE_BLOCK) k_zero_bounce(TraceCtx tc, const 
 }
 
 struct RadianceAdjSource {
-  const Record* recs;
   const CamBatch* cams;
   int64_t hw;
   SbParams sp;
@@ -105,8 +104,8 @@ struct RadianceAdjSource {
     return true;
   }
 
-  __device__ __forceinline__ void operator()(uint32_t pos, double, double, double w, double, D3, D3) {
-    const uint32_t idx = rec_index(load_record(recs, pos));
+  __device__ __forceinline__ void operator()(const Record& r, const Attr&, double, double, double w, double, D3, D3) {
+    const uint32_t idx = rec_index(r);
     atomicAdd(gr + idx, w * (double)dl.x);
     atomicAdd(gr + n + idx, w * (double)dl.y);
     atomicAdd(gr + 2 * n + idx, w * (double)dl.z);
@@ -115,12 +114,11 @@ struct RadianceAdjSource {
   __device__ __forceinline__ bool finish(const Seg<false>&, D3&, D3&) { return false; }
 };
 
-__global__ void __launch_bounds__(TRACE_BLOCK) k_zero_bounce_adj_r(TraceCtx tc, const CamBatch cams, int64_t hw,
+__global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(2))) k_zero_bounce_adj_r(TraceCtx tc, const CamBatch cams, int64_t hw,
                                                                   int32_t n_cams, SbParams sp, const float* dL,
                                                                   double* gr, int64_t n, unsigned long long* work,
                                                                   uint64_t* hitlist) {
   RadianceAdjSource src;
-  src.recs = tc.recs;
   src.cams = &cams;
   src.hw = hw;
   src.sp = sp;

@@ -363,7 +363,7 @@ __device__ __forceinline__ float slab(float lx, float ly, float lz, float hx, fl
 
 // No per-hit callback (forward passes).
 struct NoHit {
-  __device__ __forceinline__ void operator()(uint32_t, double, double, double, double, D3, D3) const {}
+  __device__ __forceinline__ void operator()(const Record&, const Attr&, double, double, double, double, D3, D3) const {}
 };
 
 // Traversal stack: the top STACK_LDS entries of every lane live in LDS,
@@ -801,7 +801,8 @@ __device__ __forceinline__ void traverse_round(const TraceCtx& tc, S& s, Round& 
 // positions of all the round's hits are fetched at once (their latency is
 // paid once a round), and shifted down one entry per hit, which keeps the
 // indexing static.
-// on_hit(pos, t, alpha, w, T_before, O, W) is called for every blended hit; if
+// on_hit(record, attributes, t, alpha, w, T_before, O, W) is called for every
+// blended hit (its loads would stand between the next hit's and this one); if
 // hit_out is non-null, up to max_hits blended surfel indices are written.
 template <int QMODE, class S, class HitFn>
 __device__ __forceinline__ void blend_round(const TraceCtx& tc, S& s, Round& r, HitFn& on_hit,
@@ -819,7 +820,6 @@ __device__ __forceinline__ void blend_round(const TraceCtx& tc, S& s, Round& r, 
   Record rec = load_record(tc.recs, at_pos[0]);
   Attr at = *elem(tc.attrs, at_pos[0]);
   for (int j = 0; j < r.cnt && !s.done; ++j) {
-    const uint32_t pos = at_pos[0];
 #pragma unroll
     for (int m = 0; m < KBUF - 1; ++m) at_pos[m] = at_pos[m + 1];
     const Record nrec = load_record(tc.recs, at_pos[0]);
@@ -859,7 +859,7 @@ __device__ __forceinline__ void blend_round(const TraceCtx& tc, S& s, Round& r, 
     if constexpr (S::kStats) {
       if (hit_out && s.nhits < max_hits) hit_out[s.nhits] = (int32_t)rec_index(rec);
     }
-    on_hit(pos, t, a, w, s.T, s.O, s.W);
+    on_hit(rec, at, t, a, w, s.T, s.O, s.W);
     if constexpr (S::kStats) ++s.nhits;
     s.T *= (1.0 - a);
     if (s.T < tc.T_min) s.done = true;

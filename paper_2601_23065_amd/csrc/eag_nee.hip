@@ -263,7 +263,7 @@ struct MisPathSource {
     return true;
   }
 
-  __device__ __forceinline__ void operator()(uint32_t, double, double, double, double, D3, D3) const {}
+  __device__ __forceinline__ void operator()(const Record&, const Attr&, double, double, double, double, D3, D3) const {}
 
   // Queue a contribution; the lanes that call this together claim their
   // slots with one atomic.

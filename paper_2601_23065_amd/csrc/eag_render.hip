@@ -29,7 +29,7 @@ struct CameraSource {
   float* rgb;
   int64_t item;
 
-  __device__ __forceinline__ void operator()(uint32_t, double, double, double, double, D3, D3) const {}
+  __device__ __forceinline__ void operator()(const Record&, const Attr&, double, double, double, double, D3, D3) const {}
 
   __device__ __forceinline__ bool start(int64_t wid, TraceCtx&, D3& O, D3& W) {
     item = wid;
@@ -72,7 +72,7 @@ struct CameraSource {
   }
 };
 
-__global__ void __launch_bounds__(TRACE_BLOCK) k_sb_camera(TraceCtx tc, const CamBatch cams, int64_t hw,
+__global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(2))) k_sb_camera(TraceCtx tc, const CamBatch cams, int64_t hw,
                                                            int32_t n_cams, SbParams sp, float* state, float* rgb,
                                                            unsigned long long* work, uint64_t* hitlist) {
   CameraSource src;
@@ -119,7 +119,7 @@ struct SecondarySource {
     return true;
   }
 
-  __device__ __forceinline__ void operator()(uint32_t, double, double, double, double, D3, D3) const {}
+  __device__ __forceinline__ void operator()(const Record&, const Attr&, double, double, double, double, D3, D3) const {}
 
   __device__ __forceinline__ bool finish(const Seg<true>& sg, D3&, D3&) {
     r1[item * 3 + 0] = sg.R0;
@@ -129,7 +129,7 @@ struct SecondarySource {
   }
 };
 
-__global__ void __launch_bounds__(TRACE_BLOCK) k_sb_secondary(
+__global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(2))) k_sb_secondary(
     TraceCtx tc, const CamBatch cams, int64_t hw, int32_t n_cams, SbParams sp, const float* state, double* r1,
     unsigned long long* work, uint64_t* hitlist) {
   SecondarySource src;

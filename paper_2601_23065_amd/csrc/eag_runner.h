@@ -24,8 +24,8 @@
 //       needs no tracing (the source then writes its own result);
 //   bool finish(const Seg<DACC>& s, D3& O, D3& W)
 //       the lane's segment has ended; true with the next segment's ray;
-//   void operator()(uint32_t pos, double t, double alpha, double w,
-//                   double T_before, D3 O, D3 W)
+//   void operator()(const Record&, const Attr&, double t, double alpha,
+//                   double w, double T_before, D3 O, D3 W)
 //       called for every blended hit, in blending order (may be empty).
 #pragma once
 
