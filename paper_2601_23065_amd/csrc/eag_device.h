@@ -443,6 +443,14 @@ __device__ __forceinline__ void kbuf_merge8(uint64_t (&kk)[KBUF], const uint64_t
   }
 }
 
+// Lanes of each wave that take work: 64, or fewer when the launch has fewer
+// items than the grid has lanes. A wave runs as long as the longest of its
+// lanes' paths through every phase, so few items are spread over all waves.
+__host__ __device__ inline int lanes_per_wave(int64_t n_work, int64_t n_waves) {
+  const int64_t q = (n_work + n_waves - 1) / n_waves;
+  return q < 1 ? 1 : (q > 64 ? 64 : (int)q);
+}
+
 // ---------------------------------------------------------------------------
 // One ray segment: multi-round k-buffer traversal and front-to-back blending.
 // Round r collects the KBUF smallest keys strictly greater than the last key
@@ -749,20 +757,21 @@ __device__ __forceinline__ void leaf_eval(const TraceCtx& tc, S& s, Round& r, co
 
 // Test postponed leaves, most recent first. The next leaf's record is loaded
 // before the current one is tested, so that its latency overlaps the test's
-// arithmetic. The load is not behind a branch (a lane without a next leaf
+// arithmetic. A lane whose traversal continues stops once fewer than leaf_min
+// lanes of the wave still hold leaves, and keeps the rest for its next leaf
+// phase; a lane whose traversal has ended tests all of them.
+// The load is not behind a branch (a lane without a next leaf
 // loads the current one again): the compiler then knows how many loads are in
 // flight and waits for the current record alone; behind a branch it waited
-// for both, and every test paid the whole latency. A lane whose traversal continues stops once fewer than
-// LEAF_MIN_LANES lanes of the wave still hold leaves, and keeps the rest for
-// its next leaf phase; a lane whose traversal has ended tests all of them.
-constexpr int LEAF_MIN_LANES = 16;
+// for both, and every test paid the whole latency.
+constexpr int LEAF_MIN_LANES = 16;   // leaf_min of a wave with 64 lanes at work
 template <class S>
-__device__ __forceinline__ void leaf_phase(const TraceCtx& tc, S& s, Round& r, int* pend) {
+__device__ __forceinline__ void leaf_phase(const TraceCtx& tc, S& s, Round& r, int* pend, int leaf_min) {
   if (r.np <= 0) return;
   uint32_t pos = (uint32_t)pend[(--r.np) * TRACE_BLOCK];
   Record rec = load_record(tc.recs, pos);
   while (true) {
-    const bool more = r.np > 0 && !(r.trav && __popcll(__ballot(r.np > 0)) < LEAF_MIN_LANES);
+    const bool more = r.np > 0 && !(r.trav && __popcll(__ballot(r.np > 0)) < leaf_min);
     r.np -= more ? 1 : 0;
     const uint32_t queued = (uint32_t)pend[r.np * TRACE_BLOCK];
     pos = more ? queued : pos;
@@ -783,13 +792,13 @@ __device__ __forceinline__ void round_end_traversal(const TraceCtx& tc, S& s, co
 // Traverse one round to completion for this lane.
 template <class S>
 __device__ __forceinline__ void traverse_round(const TraceCtx& tc, S& s, Round& r, TravStack& st,
-                                               int* pend) {
+                                               int* pend, int leaf_min) {
   while (true) {
     while (r.trav && r.np <= PEND - 4) {
       node_visit(tc, s, r, st, pend);
       if (__all(r.np > 0 || !r.trav)) break;
     }
-    leaf_phase(tc, s, r, pend);
+    leaf_phase(tc, s, r, pend, leaf_min);
     if (!r.trav) break;
   }
   round_end_traversal(tc, s, r);
@@ -872,10 +881,12 @@ __device__ __forceinline__ void blend_round(const TraceCtx& tc, S& s, Round& r, 
 }
 
 // A whole segment for this lane. Must be called from a TRACE_BLOCK-thread
-// block (the traversal stack and the postponed leaves live in LDS).
+// block (the traversal stack and the postponed leaves live in LDS), with the
+// same `lanes` lanes of every wave at work.
 template <int QMODE, bool DACC, class HitFn>
-__device__ SegOut trace_segment_cb(const TraceCtx& tc, D3 O, D3 W, HitFn& on_hit, int32_t* hit_out = nullptr,
+__device__ SegOut trace_segment_cb(const TraceCtx& tc, D3 O, D3 W, int lanes, HitFn& on_hit, int32_t* hit_out = nullptr,
                                    int max_hits = 0) {
+  const int leaf_min = (LEAF_MIN_LANES * lanes + 63) / 64;
   __shared__ int s_stack[STACK_LDS * TRACE_BLOCK];
   __shared__ int s_pend[PEND * TRACE_BLOCK];
   int s_ovf[STACK_OVF];
@@ -888,7 +899,7 @@ __device__ SegOut trace_segment_cb(const TraceCtx& tc, D3 O, D3 W, HitFn& on_hit
   seg_begin(s, O, W);
   while (!s.done) {
     Round r;
-    if (round_begin(tc, s, r, st, pend)) traverse_round(tc, s, r, st, pend);
+    if (round_begin(tc, s, r, st, pend)) traverse_round(tc, s, r, st, pend, leaf_min);
     blend_round<QMODE>(tc, s, r, on_hit, hit_out, max_hits);
   }
   SegOut o;
@@ -906,10 +917,10 @@ __device__ SegOut trace_segment_cb(const TraceCtx& tc, D3 O, D3 W, HitFn& on_hit
 }
 
 template <int QMODE, bool DACC = false>
-__device__ __forceinline__ SegOut trace_segment(const TraceCtx& tc, D3 O, D3 W, int32_t* hit_out = nullptr,
-                                                int max_hits = 0) {
+__device__ __forceinline__ SegOut trace_segment(const TraceCtx& tc, D3 O, D3 W, int lanes,
+                                                int32_t* hit_out = nullptr, int max_hits = 0) {
   NoHit nh;
-  return trace_segment_cb<QMODE, DACC>(tc, O, W, nh, hit_out, max_hits);
+  return trace_segment_cb<QMODE, DACC>(tc, O, W, lanes, nh, hit_out, max_hits);
 }
 
 }  // namespace eag

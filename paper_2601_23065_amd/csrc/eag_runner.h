@@ -33,7 +33,7 @@
 
 namespace eag {
 
-constexpr int RUN_BLEND_BATCH = 20;   // lanes waiting to blend that end a traversal stretch
+constexpr int RUN_BLEND_BATCH = 20;   // lanes of a full wave waiting to blend that end a traversal stretch
 // Runner kernels launch this many TRACE_BLOCK-thread blocks per CU: their
 // LDS (stack and postponed leaves, 56 KB per block) admits two per CU, and
 // the per-lane hit list is sized for exactly this grid.
@@ -89,6 +89,11 @@ __device__ __forceinline__ void run_segments(const TraceCtx& tc, Src& src, unsig
   tcl.hl_at = (blockIdx.x * TRACE_BLOCK + threadIdx.x) * HL_CAP;
   tcl.hl_bytes = gridDim.x * TRACE_BLOCK * HL_CAP * 8u;   // (256 MiB on 256 CUs)
 
+  // thresholds in lanes, scaled to the lanes that take work
+  const int lanes = lanes_per_wave(n_work, (int64_t)gridDim.x * (TRACE_BLOCK / 64));
+  const int blend_batch = (RUN_BLEND_BATCH * lanes + 63) / 64;
+  const int leaf_min = (LEAF_MIN_LANES * lanes + 63) / 64;
+
   int stage = ST_IDLE;
   SegStats<DACC, STATS, true> s;
   seg_begin(s, d3(0.0, 0.0, 0.0), d3(0.0, 0.0, 1.0));
@@ -101,7 +106,7 @@ __device__ __forceinline__ void run_segments(const TraceCtx& tc, Src& src, unsig
 
   while (true) {
     // ---- refill idle lanes from the global work counter
-    const bool need = stage == ST_IDLE;
+    const bool need = stage == ST_IDLE && lane < lanes;
     const uint64_t idle = __ballot(need);
     bool exhausted = false;
     if (idle) {
@@ -139,13 +144,13 @@ __device__ __forceinline__ void run_segments(const TraceCtx& tc, Src& src, unsig
           node_visit(tcl, s, r, st, pend);
           if (__all(r.np > 0 || !r.trav)) break;
         }
-        leaf_phase(tcl, s, r, pend);
+        leaf_phase(tcl, s, r, pend, leaf_min);
         if (!r.trav) {
           round_end_traversal(tcl, s, r);
           stage = ST_BLEND;
         }
       }
-      if (__ballot(stage == ST_TRAV) == 0 || __popcll(__ballot(stage == ST_BLEND)) >= RUN_BLEND_BATCH) break;
+      if (__ballot(stage == ST_TRAV) == 0 || __popcll(__ballot(stage == ST_BLEND)) >= blend_batch) break;
     }
 
     // ---- blend, and finish ended segments

@@ -1,8 +1,10 @@
-// Tracing of caller-supplied rays (Sec. 3.1, Eq. 1-3): one thread per ray,
+// Tracing of caller-supplied rays (Sec. 3.1, Eq. 1-3): one lane per ray (of
+// every wave, as many lanes as it takes to use the whole chip),
 // multi-round k-buffer traversal and front-to-back blending, output of the
 // normalised traced quantities and, optionally, the blended hit list.
 #include "eag_device.h"
 #include "eag_internal.h"
+#include "eag_render.h"
 
 #include <mutex>
 
@@ -45,13 +47,14 @@ namespace {
 
 __global__ void __launch_bounds__(256) k_trace_rays(TraceCtx tc, int64_t n_rays, const double* o, const double* d,
                                                     float* out, int32_t* hit_idx, int32_t* hit_count,
-                                                    int32_t max_hits, int32_t* stats) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= n_rays) return;
+                                                    int32_t max_hits, int32_t* stats, int lanes) {
+  const int lane = (int)(threadIdx.x & 63);
+  const int64_t i = (blockIdx.x * (int64_t)(TRACE_BLOCK / 64) + (threadIdx.x >> 6)) * lanes + lane;
+  if (lane >= lanes || i >= n_rays) return;
   const D3 O = d3(o[i], o[n_rays + i], o[2 * n_rays + i]);
   const D3 W = d3(d[i], d[n_rays + i], d[2 * n_rays + i]);
   int32_t* hl = hit_idx ? hit_idx + i * (int64_t)max_hits : nullptr;
-  const SegOut s = trace_segment<Q_ALL, true>(tc, O, W, hl, max_hits);
+  const SegOut s = trace_segment<Q_ALL, true>(tc, O, W, lanes, hl, max_hits);
   const double A = 1.0 - s.T;
   float v[12];
   if (s.nhits > 0 && A > 0.0) {
@@ -101,9 +104,10 @@ void launch_trace_rays(const eag_bvh* b, const Attr* attrs, const eag_trace_para
                        int64_t n_rays, const double* o, const double* d, float* out, int32_t* hit_idx,
                        int32_t* hit_count, int32_t max_hits, int32_t* stats, hipStream_t st) {
   const TraceCtx tc = make_ctx(b, attrs, p, ts);
-  const unsigned g = (unsigned)((n_rays + 255) / 256);
-  hipLaunchKernelGGL(k_trace_rays, dim3(g), dim3(256), 0, st, tc, n_rays, o, d, out, hit_idx, hit_count,
-                     max_hits, stats);
+  const int lanes = lanes_per_wave(n_rays, runner_lanes() / 64);
+  const int64_t per_block = (int64_t)lanes * (TRACE_BLOCK / 64);
+  hipLaunchKernelGGL(k_trace_rays, dim3((unsigned)((n_rays + per_block - 1) / per_block)), dim3(TRACE_BLOCK), 0, st, tc,
+                     n_rays, o, d, out, hit_idx, hit_count, max_hits, stats, lanes);
   check_hip(hipGetLastError(), "trace_rays launch");
 }
 
