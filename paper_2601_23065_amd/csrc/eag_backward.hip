@@ -128,7 +128,9 @@ __device__ __forceinline__ void emit_record(const GradRecs& gr, const GradPtrs& 
   const unsigned k = (unsigned)__popcll(act);
   unsigned base = 0, chunk = REC_NO_CHUNK;
   if (lane == leader) {
-    unsigned cur = wcur[0], ch = wcur[1];
+    // (volatile: the lanes of a wave take turns as leader)
+    volatile unsigned* const wc = wcur;
+    unsigned cur = wc[0], ch = wc[1];
     if (ch == REC_NO_CHUNK || (ch != REC_SPENT && cur + k > (unsigned)REC_CHUNK)) {
       if (ch < (unsigned)gr.n_chunks) gr.chunk_used[ch] = cur;
       const unsigned long long c = atomicAdd(gr.chunk_next, 1ull);
@@ -137,8 +139,8 @@ __device__ __forceinline__ void emit_record(const GradRecs& gr, const GradPtrs& 
     }
     base = cur;
     chunk = ch;
-    wcur[0] = cur + k;
-    wcur[1] = ch;
+    wc[0] = cur + k;
+    wc[1] = ch;
   }
   base = __shfl(base, leader);
   chunk = __shfl(chunk, leader);
@@ -535,29 +537,50 @@ __global__ void k_stage0_finalize(const double* acc, int64_t n, eag_surfel_grads
   if (dst) dst[j] += (float)acc[i];
 }
 
-__global__ void k_zero_u32(uint32_t* p, int64_t n) {
+// The counts of a pass: per surfel, per chunk, and the chunks claimed.
+__global__ void k_zero_records(GradRecs gr, int64_t n) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0u;
+  if (i < n) {
+    gr.cnt[i] = 0u;
+    gr.cursor[i] = 0u;
+  }
+  if (i < gr.n_chunks) gr.chunk_used[i] = 0u;
+  if (i == 0) *gr.chunk_next = 0ull;
 }
 
 // Every used slot of the claimed chunks goes to the next free position of its
 // surfel's range [off[i], off[i] + cnt[i]) of order (cursor: zeroed per-surfel
-// counts). Blocks stride over the claimed chunks only.
+// counts). Blocks stride over the claimed chunks only. Bound by the latency of
+// index, offset and returning atomic: a thread has its four slots of a chunk
+// in flight together.
 __global__ void __launch_bounds__(256) k_rec_place(GradRecs gr) {
+  constexpr int PER = (int)(REC_CHUNK / 256);
   const unsigned long long claimed = *gr.chunk_next;
   const int64_t nc = claimed < (unsigned long long)gr.n_chunks ? (int64_t)claimed : gr.n_chunks;
   for (int64_t ch = blockIdx.x; ch < nc; ch += gridDim.x) {
     const uint32_t used = gr.chunk_used[ch];
-    for (uint32_t j = threadIdx.x; j < used; j += blockDim.x) {
-      const int64_t s = ch * REC_CHUNK + j;
-      const uint32_t i = gr.idx[s];
-      gr.order[gr.off[i] + atomicAdd(gr.cursor + i, 1u)] = (uint32_t)s;
+    const int64_t s0 = ch * REC_CHUNK + threadIdx.x;
+    uint32_t at[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) at[k] = threadIdx.x + 256u * k < used ? gr.idx[s0 + 256 * k] : 0u;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const uint32_t i = at[k];
+      if (threadIdx.x + 256u * k < used) at[k] = gr.off[i] + atomicAdd(gr.cursor + i, 1u);
     }
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (threadIdx.x + 256u * k < used) gr.order[at[k]] = (uint32_t)(s0 + 256 * k);
   }
 }
 
 // One wave per surfel: its records, summed lane-strided and then across the
-// wave in a fixed order, are added to the accumulator rows.
+// wave in a fixed order, are added to the accumulator rows. Across the wave,
+// each of four steps halves the rows a lane holds (it hands the other half to
+// its partner) and two more finish the row that is left: 17 exchanges, where
+// every row through all six steps takes 96. (A record as one access of 16
+// lanes, with no exchange but the last two, was slower: 0.81 ms against 0.27
+// at 5 M records of 100,000 surfels, for its serial loads.)
 __global__ void __launch_bounds__(256) k_rec_reduce(GradRecs gr, double* gacc, int64_t n) {
   const int64_t i = blockIdx.x * 4 + (int64_t)(threadIdx.x >> 6);
   const int lane = (int)(threadIdx.x & 63);
@@ -578,15 +601,20 @@ __global__ void __launch_bounds__(256) k_rec_reduce(GradRecs gr, double* gacc, i
       acc[4 * k + 3] += v.w;
     }
   }
+  static_assert(GRAD_ROWS == 16, "four halvings leave one row per lane");
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
+  for (int h = 8, m = 32; h >= 1; h >>= 1, m >>= 1) {
+    const bool up = (lane & m) != 0;   // keeps the upper h rows
 #pragma unroll
-    for (int k = 0; k < GRAD_ROWS; ++k) acc[k] += __shfl_xor(acc[k], m);
+    for (int k = 0; k < h; ++k) {
+      const double got = __shfl_xor(up ? acc[k] : acc[k + h], m);
+      acc[k] = (up ? acc[k + h] : acc[k]) + got;
+    }
   }
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < GRAD_ROWS; ++k) gacc[k * n + i] += acc[k];
-  }
+  acc[0] += __shfl_xor(acc[0], 2);
+  acc[0] += __shfl_xor(acc[0], 1);
+  // lane bits 5 to 2 are the row's bits 3 to 0
+  if ((lane & 3) == 0) gacc[(lane >> 2) * n + i] += acc[0];
 }
 
 __global__ void k_zero_f64(double* p, int64_t n) {
@@ -621,11 +649,8 @@ size_t grad_rec_scan_bytes(int64_t n) { return scan_u32_bytes(n); }
 
 void zero_record_counts(const GradRecs& gr, int64_t n, hipStream_t st) {
   if (gr.n_chunks <= 0) return;
-  hipLaunchKernelGGL(k_zero_u32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, gr.cnt, n);
-  hipLaunchKernelGGL(k_zero_u32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, gr.cursor, n);
-  hipLaunchKernelGGL(k_zero_u32, dim3((unsigned)((gr.n_chunks + 255) / 256)), dim3(256), 0, st, gr.chunk_used,
-                     gr.n_chunks);
-  launch_zero_u64(gr.chunk_next, 1, st);
+  const int64_t m = n > gr.n_chunks ? n : gr.n_chunks;
+  hipLaunchKernelGGL(k_zero_records, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, gr, n);
 }
 
 // Group the records of the pass just run by surfel and add their sums.

@@ -76,15 +76,26 @@ __global__ void k_stage0_images(const float* state, int64_t n_pix, float* images
   o[7] = hit ? st.E : 0.0f;
 }
 
-__global__ void k_stage0_count(const float* images, int64_t n_pix, int64_t W, int64_t H, unsigned long long* counts) {
-  const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const bool in = g < n_pix;
-  const bool hit = in && is_hit(images + g * STAGE0_FLOATS);
-  const bool valid = in && dn_valid(images, g, W, H);
-  const uint64_t bh = __ballot(hit), bv = __ballot(valid);
+// Grid-stride, so that a launch ends with two atomics per block: one pair per
+// wave of pixels put 16,000 atomics on two addresses (200 us at 524,288 pixels).
+__global__ void __launch_bounds__(256) k_stage0_count(const float* images, int64_t n_pix, int64_t W, int64_t H,
+                                                     unsigned long long* counts) {
+  __shared__ unsigned long long part[4][2];
+  unsigned long long nh = 0, nv = 0;
+  for (int64_t g0 = blockIdx.x * (int64_t)blockDim.x; g0 < n_pix; g0 += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t g = g0 + threadIdx.x;
+    const bool in = g < n_pix;
+    nh += (unsigned long long)__popcll(__ballot(in && is_hit(images + g * STAGE0_FLOATS)));
+    nv += (unsigned long long)__popcll(__ballot(in && dn_valid(images, g, W, H)));
+  }
   if ((threadIdx.x & 63) == 0) {
-    if (bh) atomicAdd(&counts[0], (unsigned long long)__popcll(bh));
-    if (bv) atomicAdd(&counts[1], (unsigned long long)__popcll(bv));
+    part[threadIdx.x >> 6][0] = nh;
+    part[threadIdx.x >> 6][1] = nv;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    const unsigned long long t = part[0][threadIdx.x] + part[1][threadIdx.x] + part[2][threadIdx.x] + part[3][threadIdx.x];
+    if (t) atomicAdd(&counts[threadIdx.x], t);
   }
 }
 
@@ -179,16 +190,12 @@ __global__ void k_stage0_gather(const float* contrib, int64_t n_pix, int64_t W, 
   dimg[g * STAGE0_FLOATS + 3] = (float)s;
 }
 
-__global__ void k_set_u64(unsigned long long* p, unsigned long long v0, unsigned long long v1, unsigned long long v2) {
+__global__ void k_stage0_begin(unsigned long long* counts, unsigned long long n_pix, double* loss) {
   if (threadIdx.x == 0) {
-    p[0] = v0;
-    p[1] = v1;
-    p[2] = v2;
+    counts[0] = counts[1] = 0ull;
+    counts[2] = n_pix;
+    loss[0] = 0.0;
   }
-}
-
-__global__ void k_zero_f64_s0(double* p) {
-  if (threadIdx.x == 0) p[0] = 0.0;
 }
 
 unsigned nblocks(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -202,10 +209,10 @@ void launch_stage0_images(const float* state, int64_t n_pix, float* images, hipS
 
 void launch_stage0_count(const float* images, int64_t n_pix, int64_t W, int64_t H, unsigned long long* counts,
                          double* loss, hipStream_t st) {
-  hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(64), 0, st, counts, 0ull, 0ull, (unsigned long long)n_pix);
-  hipLaunchKernelGGL(k_zero_f64_s0, dim3(1), dim3(64), 0, st, loss);
+  hipLaunchKernelGGL(k_stage0_begin, dim3(1), dim3(64), 0, st, counts, (unsigned long long)n_pix, loss);
   if (n_pix > 0)
-    hipLaunchKernelGGL(k_stage0_count, dim3(nblocks(n_pix)), dim3(256), 0, st, images, n_pix, W, H, counts);
+    hipLaunchKernelGGL(k_stage0_count, dim3(nblocks(n_pix) < 512u ? nblocks(n_pix) : 512u), dim3(256), 0, st, images,
+                       n_pix, W, H, counts);
   check_hip(hipGetLastError(), "stage-0 count launch");
 }
 
