@@ -15,6 +15,7 @@
 #include "eag_internal.h"
 #include "eag_render.h"
 
+#include <algorithm>
 #include <cmath>
 
 
@@ -110,9 +111,9 @@ __device__ __forceinline__ double child_area(const Node4& nd, int k) {
 
 __global__ void __launch_bounds__(256) k_sah_sum(const Node4* nodes, const BvhHeader* h, int32_t root, double* acc) {
   __shared__ double part[4];
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   double a = 0.0;
-  if (i < h->n_nodes4) {
+  const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  for (int64_t i = i0; i < h->n_nodes4; i += (int64_t)gridDim.x * blockDim.x) {
     const Node4& nd = nodes[i];
     const int c[4] = {nd.ref.x, nd.ref.y, nd.ref.z, nd.ref.w};
     for (int k = 0; k < 4; ++k)
@@ -123,9 +124,9 @@ __global__ void __launch_bounds__(256) k_sah_sum(const Node4* nodes, const BvhHe
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = a;
   __syncthreads();
   if (threadIdx.x == 0) atomicAdd(&acc[0], part[0] + part[1] + part[2] + part[3]);
-  if (i == root) {
+  if (i0 == root) {
     // the root's box: the union of its children's
-    const Node4& nd = nodes[i];
+    const Node4& nd = nodes[root];
     const int c[4] = {nd.ref.x, nd.ref.y, nd.ref.z, nd.ref.w};
     const float4* b = nd.b;
     const float lo[4][3] = {{b[0].x, b[0].y, b[0].z}, {b[1].z, b[1].w, b[2].x}, {b[3].x, b[3].y, b[3].z},
@@ -213,9 +214,9 @@ void launch_sah_cost(const Node4* nodes, const BvhHeader* h, int64_t max_nodes, 
   if (root < 0 || max_nodes <= 0) {
     hipLaunchKernelGGL(k_sah_single, dim3(1), dim3(64), 0, st, cost);
   } else {
-    // the node count is in the device header: the grid covers the most there can be
+    // (grid-stride: one atomic per block, on one address)
     hipLaunchKernelGGL(k_sah_zero, dim3(1), dim3(64), 0, st, acc);
-    hipLaunchKernelGGL(k_sah_sum, dim3(nb(max_nodes)), dim3(256), 0, st, nodes, h, root, acc);
+    hipLaunchKernelGGL(k_sah_sum, dim3(std::min(nb(max_nodes), 512u)), dim3(256), 0, st, nodes, h, root, acc);
     hipLaunchKernelGGL(k_sah_final, dim3(1), dim3(64), 0, st, acc, cost);
   }
   check_hip(hipGetLastError(), "tree cost launch");

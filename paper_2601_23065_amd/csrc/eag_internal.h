@@ -77,8 +77,6 @@ struct eag_bvh {
   eag::Record* recs;
   int32_t* perm;          // surfel at each sorted position
   int32_t* inv;           // sorted position of each surfel
-  int32_t* leaf_parent;
-  int32_t* node_parent;
   int32_t* levels;        // internal nodes made before each clustering iteration
   hipEvent_t built = nullptr;   // recorded after the last build or refit
 };
@@ -129,8 +127,6 @@ struct BvhLayout {
   Record* recs;
   int32_t* perm;
   int32_t* inv;
-  int32_t* leaf_parent;
-  int32_t* node_parent;
   int32_t* levels;
   size_t bytes;
 };
