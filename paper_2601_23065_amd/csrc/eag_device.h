@@ -612,12 +612,19 @@ __device__ __forceinline__ bool round_begin(const TraceCtx& tc, S& s, Round& r, 
   return traverse;
 }
 
-// Visit internal node r.ref: leaves the ray reaches are postponed, internal
-// children are visited nearest first (the others pushed farthest first).
-template <class S>
-__device__ __forceinline__ void node_visit(const TraceCtx& tc, S& s, Round& r, TravStack& st, int* pend) {
-  if constexpr (S::kStats) ++s.visits;
-  const float4* np = reinterpret_cast<const float4*>(elem(tc.nodes, (uint32_t)r.ref));
+// A node's children for a ray: ek holds (entry, child) of the internal ones
+// the ray reaches, ordered as doubles by the entry (the float's bits in the
+// high word make a finite double, +inf included; +inf for the others), ni of
+// them; leaf says which children are leaves the ray reaches.
+struct NodeKids {
+  int c[4];
+  bool leaf[4];
+  uint64_t ek[4];
+  int ni;
+};
+template <bool DACC>
+__device__ __forceinline__ NodeKids node_test(const TraceCtx& tc, const Seg<DACC>& s, int ref, float tlo0, float t_cut) {
+  const float4* np = reinterpret_cast<const float4*>(elem(tc.nodes, (uint32_t)ref));
   const float4 h = np[0];
   const uint4 u0 = *reinterpret_cast<const uint4*>(np + 1), u1 = *reinterpret_cast<const uint4*>(np + 2);
   const uint2 u2 = *reinterpret_cast<const uint2*>(np + 3);
@@ -631,33 +638,52 @@ __device__ __forceinline__ void node_visit(const TraceCtx& tc, S& s, Round& r, T
   const uint32_t nx = gx ? u0.w : u0.x, fx = gx ? u0.x : u0.w;
   const uint32_t ny = gy ? u1.x : u0.y, fy = gy ? u0.y : u1.x;
   const uint32_t nz = gz ? u1.y : u0.z, fz = gz ? u0.z : u1.y;
-  const int c[4] = {(int)u1.z, (int)u1.w, (int)u2.x, (int)u2.y};
-  uint64_t ek[4];
-  int ni = 0;
+  NodeKids kd;
+  kd.c[0] = (int)u1.z;
+  kd.c[1] = (int)u1.w;
+  kd.c[2] = (int)u2.x;
+  kd.c[3] = (int)u2.y;
+  kd.ni = 0;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const float tn = fmaxf(fmaxf(fmaf(q_byte(nx, k), ax, bx), fmaf(q_byte(ny, k), ay, by)),
-                           fmaxf(fmaf(q_byte(nz, k), az, bz), r.tlo0));
+                           fmaxf(fmaf(q_byte(nz, k), az, bz), tlo0));
     // widen the exit so that rounding (and the float32 copy of the ray) never
     // rejects a box the ray touches
     const float tf = fminf(fminf(fmaf(q_byte(fx, k), ax, bx), fmaf(q_byte(fy, k), ay, by)),
-                           fminf(fmaf(q_byte(fz, k), az, bz), r.t_cut)) * 1.000002f + 1e-6f;
-    const bool m = c[k] != NODE4_EMPTY && tn <= tf;
+                           fminf(fmaf(q_byte(fz, k), az, bz), t_cut)) * 1.000002f + 1e-6f;
+    const bool m = kd.c[k] != NODE4_EMPTY && tn <= tf;
+    const bool mi = m && kd.c[k] >= 0;
+    kd.leaf[k] = m && kd.c[k] < 0;
+    kd.ek[k] = ((uint64_t)__float_as_uint(mi ? tn : __builtin_inff()) << 32) | (uint32_t)kd.c[k];
+    kd.ni += mi ? 1 : 0;
+  }
+  return kd;
+}
+__device__ __forceinline__ void sort_kids(NodeKids& kd, int (&ic)[4]) {
+  cswap_key(kd.ek[0], kd.ek[1]); cswap_key(kd.ek[2], kd.ek[3]); cswap_key(kd.ek[0], kd.ek[2]);
+  cswap_key(kd.ek[1], kd.ek[3]); cswap_key(kd.ek[1], kd.ek[2]);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) ic[k] = (int)(uint32_t)kd.ek[k];
+}
+
+// Visit internal node r.ref: leaves the ray reaches are postponed, internal
+// children are visited nearest first (the others pushed farthest first).
+template <class S>
+__device__ __forceinline__ void node_visit(const TraceCtx& tc, S& s, Round& r, TravStack& st, int* pend) {
+  if constexpr (S::kStats) ++s.visits;
+  NodeKids kd = node_test(tc, s, r.ref, r.tlo0, r.t_cut);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
     // leaves are queued without a branch: the slot past the queue is always
     // written (nodes are visited only while np <= PEND - 4, so it exists)
-    pend[r.np * TRACE_BLOCK] = ~c[k];
-    r.np += (m && c[k] < 0) ? 1 : 0;
-    // (entry, child), ordered as a double by the entry: the float's bits in
-    // the high word make a finite double, +inf included
-    const bool mi = m && c[k] >= 0;
-    ek[k] = ((uint64_t)__float_as_uint(mi ? tn : __builtin_inff()) << 32) | (uint32_t)c[k];
-    ni += mi ? 1 : 0;
+    pend[r.np * TRACE_BLOCK] = ~kd.c[k];
+    r.np += kd.leaf[k] ? 1 : 0;
   }
+  const int ni = kd.ni;
   if (ni > 0) {
-    // sort by entry, misses (+inf) last
-    cswap_key(ek[0], ek[1]); cswap_key(ek[2], ek[3]); cswap_key(ek[0], ek[2]); cswap_key(ek[1], ek[3]);
-    cswap_key(ek[1], ek[2]);
-    const int ic[4] = {(int)(uint32_t)ek[0], (int)(uint32_t)ek[1], (int)(uint32_t)ek[2], (int)(uint32_t)ek[3]};
+    int ic[4];
+    sort_kids(kd, ic);
     // push the others farthest first: bottom to top ic[ni-1] .. ic[1]
     if (st.sp + 3 <= STACK_LDS) {
       // branch-free: three slots written, the stack grows by ni - 1
@@ -804,6 +830,149 @@ __device__ __forceinline__ void traverse_round(const TraceCtx& tc, S& s, Round& 
   round_end_traversal(tc, s, r);
 }
 
+// ---------------------------------------------------------------------------
+// One ray by a group of lanes. With few rays in a launch, what a ray costs is
+// the latency of its own chain of node visits and leaf tests, about a
+// microsecond each, while the chip is nearly idle. A group of G lanes (a power
+// of two, aligned in its wave) shares the ray's stack and its queue of leaves
+// and takes up to G of either at a time. Every lane keeps a k-buffer of what it
+// found; merges leave the KBUF smallest keys in the group's first lane. The
+// keys of a round do not depend on the order of the visits, so the hits are
+// those of a lane alone.
+// ---------------------------------------------------------------------------
+// Lanes per ray: the most that still gives every ray a group.
+__host__ __device__ inline int group_lanes(int lanes_per_wave) {
+  int g = 1;
+  while (2 * g * lanes_per_wave <= 64) g *= 2;
+  return g;
+}
+
+// The k-buffers of a group into its first lane's (KBUF smallest keys); the
+// others are emptied. All lanes of the wave call it.
+__device__ __forceinline__ void group_merge(uint64_t (&kk)[KBUF], int G) {
+  const int lig = (int)(threadIdx.x & 63) & (G - 1);
+  for (int m = 1; m < G; m <<= 1) {
+    // the lower lane of a pair keeps the lower half of both, bitonic; what
+    // lanes with a lower bit set hold is no longer looked at
+#pragma unroll
+    for (int i = 0; i < KBUF / 2; ++i) {
+      const uint64_t pa = (uint64_t)__shfl_xor((unsigned long long)kk[KBUF - 1 - i], m);
+      const uint64_t pb = (uint64_t)__shfl_xor((unsigned long long)kk[i], m);
+      kk[i] = key_min(kk[i], pa);
+      kk[KBUF - 1 - i] = key_min(kk[KBUF - 1 - i], pb);
+    }
+#pragma unroll
+    for (int st = KBUF / 2; st >= 1; st >>= 1) {
+#pragma unroll
+      for (int i = 0; i < KBUF; ++i)
+        if ((i & st) == 0) cswap_key(kk[i], kk[i + st]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < KBUF; ++i) kk[i] = lig == 0 ? kk[i] : KEY_NONE;
+}
+
+// A round's traversal by groups of G lanes; every lane of the wave calls it,
+// with `on` the same in a group, the ray and the round's floor in all lanes of
+// the group, and the block's whole stack and queue arrays. Afterwards the first
+// lane of each group holds the round. False for a group whose stack would not
+// have fitted its lanes' LDS (nothing else is valid then: the caller traverses
+// with one lane).
+template <class S>
+__device__ bool group_traverse(const TraceCtx& tc, S& s, Round& r, int* stack, int* queue, int G, bool on) {
+  static_assert(!S::kList, "group rounds keep no hit list");
+  const int lane = (int)(threadIdx.x & 63), lig = lane & (G - 1), gb = lane & ~(G - 1);
+  const uint64_t gmask = (G == 64 ? ~0ull : ((1ull << G) - 1ull)) << gb;
+  const uint64_t below = gmask & ((1ull << lane) - 1ull);
+  // entry e of the group's stack or queue: row e / G of its lanes' columns
+  // (volatile: lanes read what others wrote)
+  const int sh = __ffs(G) - 1, col = (int)(threadIdx.x & ~63u) + gb;
+  volatile int* const vs = stack;
+  volatile int* const vq = queue;
+  auto at = [&](int e) { return (e >> sh) * TRACE_BLOCK + col + (e & (G - 1)); };
+  const int cap = STACK_LDS * G;
+  int sp = 0, nq = 0, found = 0;
+  bool fits = true;
+  uint64_t lim = KEY_NONE;
+  if (on) {
+    if (tc.root >= 0) sp = 1;
+    else nq = 1;
+    if (lig == 0) (tc.root >= 0 ? vs : vq)[at(0)] = tc.root >= 0 ? tc.root : ~tc.root;
+  }
+  while (true) {
+    // nodes, while fewer than G leaves wait (so at most 5 G ever do)
+    const bool nodes = sp > 0 && nq < G;
+    if (__any(nodes)) {
+      int k = nodes ? min(sp, G) : 0;
+      const int room = (cap - sp) / 3;   // each node opened leaves at most three entries more
+      if (nodes && room < 1) {
+        fits = false;
+        k = sp = nq = 0;
+      }
+      k = min(k, max(room, 0));
+      const bool my = lig < k;
+      NodeKids kd;
+      kd.ni = 0;
+      int ic[4] = {0, 0, 0, 0};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        kd.leaf[c] = false;
+        kd.c[c] = 0;
+      }
+      if (my) {
+        if constexpr (S::kStats) ++s.visits;
+        kd = node_test(tc, s, vs[at(sp - 1 - lig)], r.tlo0, r.t_cut);
+        sort_kids(kd, ic);
+      }
+      sp -= k;
+      // each lane's farthest child first, so that the nearest end on top
+#pragma unroll
+      for (int c = 3; c >= 0; --c) {
+        const bool p = c < kd.ni;
+        const uint64_t m = __ballot(p) & gmask;
+        if (p) vs[at(sp + __popcll(m & below))] = ic[c];
+        sp += __popcll(m);
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const uint64_t m = __ballot(kd.leaf[c]) & gmask;
+        if (kd.leaf[c]) vq[at(nq + __popcll(m & below))] = ~kd.c[c];
+        nq += __popcll(m);
+      }
+    }
+    // leaves, once every lane has one or no node is left
+    const bool leaves = nq > 0 && (nq >= G || sp == 0);
+    if (__any(leaves)) {
+      const int k = leaves ? min(nq, G) : 0;
+      const bool my = lig < k;
+      uint64_t key = KEY_NONE;
+      if (my) {
+        if constexpr (S::kStats) ++s.tests;
+        const Record rec = load_record(tc.recs, (uint32_t)vq[at(nq - 1 - lig)]);
+        key = leaf_key(tc, rec, s.O, s.W, r.floor_key, key_min(lim, r.kk[KBUF - 1]));
+      }
+      kbuf_insert(r.kk, key);
+      nq -= k;
+      found += __popcll(__ballot(key != KEY_NONE) & gmask);
+    }
+    const bool end = !__any(sp > 0 || nq > 0);
+    // merged when a group has found enough for a new cut, and at the end
+    if (__any(found >= KBUF) || end) {
+      group_merge(r.kk, G);
+      lim = (uint64_t)__shfl((unsigned long long)r.kk[KBUF - 1], gb);
+      if (lim != KEY_NONE) r.t_cut = key_thi(tc, lim) * 1.000002f + 1e-6f;
+      found = 0;
+    }
+    if (end) break;
+  }
+  r.cnt = 0;
+#pragma unroll
+  for (int i = 0; i < KBUF; ++i) r.cnt += r.kk[i] != KEY_NONE ? 1 : 0;
+  r.trav = false;
+  r.np = 0;
+  return fits;
+}
+
 // Blend the round's hits in key order; t and alpha are recomputed from the
 // record with the same double-precision test. Sets s.done after the first hit
 // with T < T_min or when the round returned fewer than KBUF hits. The sorted
@@ -880,15 +1049,19 @@ __device__ __forceinline__ void blend_round(const TraceCtx& tc, S& s, Round& r, 
   if (!s.done) s.last = round_last;
 }
 
-// A whole segment for this lane. Must be called from a TRACE_BLOCK-thread
-// block (the traversal stack and the postponed leaves live in LDS), with the
-// same `lanes` lanes of every wave at work.
-template <int QMODE, bool DACC, class HitFn>
-__device__ SegOut trace_segment_cb(const TraceCtx& tc, D3 O, D3 W, int lanes, HitFn& on_hit, int32_t* hit_out = nullptr,
-                                   int max_hits = 0) {
-  const int leaf_min = (LEAF_MIN_LANES * lanes + 63) / 64;
+// A whole segment, without a hit list. Must be called from a
+// TRACE_BLOCK-thread block (the traversal stack and the postponed leaves live
+// in LDS), by every lane of the wave: with `on` for the lanes that have a ray.
+// G = 1: one lane per ray, `lanes` lanes of every wave at work. G > 1: the G
+// lanes of a group have the same ray, and the result is the first lane's.
+template <int QMODE, bool DACC>
+__device__ __forceinline__ SegOut trace_segment(const TraceCtx& tc, D3 O, D3 W, bool on, int lanes, int G,
+                                                int32_t* hit_out = nullptr, int max_hits = 0) {
   __shared__ int s_stack[STACK_LDS * TRACE_BLOCK];
   __shared__ int s_pend[PEND * TRACE_BLOCK];
+  const int leaf_min = (LEAF_MIN_LANES * lanes + 63) / 64;
+  const int lane = (int)(threadIdx.x & 63);
+  const bool first = (lane & (G - 1)) == 0;
   int s_ovf[STACK_OVF];
   TravStack st;
   st.lds = s_stack + threadIdx.x;
@@ -896,11 +1069,35 @@ __device__ SegOut trace_segment_cb(const TraceCtx& tc, D3 O, D3 W, int lanes, Hi
   st.sp = 0;
   int* pend = s_pend + threadIdx.x;   // this lane's queue of postponed leaves
   SegStats<DACC, true, false> s;
+  NoHit nh;
   seg_begin(s, O, W);
-  while (!s.done) {
-    Round r;
-    if (round_begin(tc, s, r, st, pend)) traverse_round(tc, s, r, st, pend, leaf_min);
-    blend_round<QMODE>(tc, s, r, on_hit, hit_out, max_hits);
+  s.done = !on;
+  Round r;
+  if (G == 1) {
+    while (!s.done) {
+      if (round_begin(tc, s, r, st, pend)) traverse_round(tc, s, r, st, pend, leaf_min);
+      blend_round<QMODE>(tc, s, r, nh, hit_out, max_hits);
+    }
+  } else {
+    while (__any(!s.done)) {
+      round_begin(tc, s, r, st, pend);
+      const bool fits = group_traverse(tc, s, r, s_stack, s_pend, G, !s.done);
+      if (first && !s.done) {
+        if (!fits) {
+          round_begin(tc, s, r, st, pend);
+          traverse_round(tc, s, r, st, pend, 1);
+        }
+        blend_round<QMODE>(tc, s, r, nh, hit_out, max_hits);
+      }
+      // the group follows its first lane
+      s.done = __shfl(s.done ? 1 : 0, lane & ~(G - 1)) != 0;
+      s.last = (uint64_t)__shfl((unsigned long long)s.last, lane & ~(G - 1));
+    }
+    // a group's visits and tests are its lanes'
+    for (int m = 1; m < G; m <<= 1) {
+      s.visits += __shfl_xor(s.visits, m);
+      s.tests += __shfl_xor(s.tests, m);
+    }
   }
   SegOut o;
   o.N = s.N;
@@ -914,13 +1111,6 @@ __device__ SegOut trace_segment_cb(const TraceCtx& tc, D3 O, D3 W, int lanes, Hi
   o.tests = s.tests;
   o.visits = s.visits;
   return o;
-}
-
-template <int QMODE, bool DACC = false>
-__device__ __forceinline__ SegOut trace_segment(const TraceCtx& tc, D3 O, D3 W, int lanes,
-                                                int32_t* hit_out = nullptr, int max_hits = 0) {
-  NoHit nh;
-  return trace_segment_cb<QMODE, DACC>(tc, O, W, lanes, nh, hit_out, max_hits);
 }
 
 }  // namespace eag

@@ -45,16 +45,19 @@ Attr* noalloc_scratch_current_device() {
 
 namespace {
 
+// `lanes` rays per wave, each by a group of G lanes.
 __global__ void __launch_bounds__(256) k_trace_rays(TraceCtx tc, int64_t n_rays, const double* o, const double* d,
                                                     float* out, int32_t* hit_idx, int32_t* hit_count,
-                                                    int32_t max_hits, int32_t* stats, int lanes) {
-  const int lane = (int)(threadIdx.x & 63);
-  const int64_t i = (blockIdx.x * (int64_t)(TRACE_BLOCK / 64) + (threadIdx.x >> 6)) * lanes + lane;
-  if (lane >= lanes || i >= n_rays) return;
-  const D3 O = d3(o[i], o[n_rays + i], o[2 * n_rays + i]);
-  const D3 W = d3(d[i], d[n_rays + i], d[2 * n_rays + i]);
-  int32_t* hl = hit_idx ? hit_idx + i * (int64_t)max_hits : nullptr;
-  const SegOut s = trace_segment<Q_ALL, true>(tc, O, W, lanes, hl, max_hits);
+                                                    int32_t max_hits, int32_t* stats, int lanes, int G) {
+  const int g = (int)(threadIdx.x & 63) / G;
+  const int64_t i = (blockIdx.x * (int64_t)(TRACE_BLOCK / 64) + (threadIdx.x >> 6)) * lanes + g;
+  const bool on = g < lanes && i < n_rays;
+  const int64_t at = on ? i : 0;   // (a lane without a ray takes part in its wave's steps)
+  const D3 O = d3(o[at], o[n_rays + at], o[2 * n_rays + at]);
+  const D3 W = d3(d[at], d[n_rays + at], d[2 * n_rays + at]);
+  int32_t* hl = hit_idx ? hit_idx + at * (int64_t)max_hits : nullptr;
+  const SegOut s = trace_segment<Q_ALL, true>(tc, O, W, on, lanes, G, hl, max_hits);
+  if (!on || ((int)threadIdx.x & (G - 1)) != 0) return;
   const double A = 1.0 - s.T;
   float v[12];
   if (s.nhits > 0 && A > 0.0) {
@@ -107,7 +110,7 @@ void launch_trace_rays(const eag_bvh* b, const Attr* attrs, const eag_trace_para
   const int lanes = lanes_per_wave(n_rays, runner_lanes() / 64);
   const int64_t per_block = (int64_t)lanes * (TRACE_BLOCK / 64);
   hipLaunchKernelGGL(k_trace_rays, dim3((unsigned)((n_rays + per_block - 1) / per_block)), dim3(TRACE_BLOCK), 0, st, tc,
-                     n_rays, o, d, out, hit_idx, hit_count, max_hits, stats, lanes);
+                     n_rays, o, d, out, hit_idx, hit_count, max_hits, stats, lanes, group_lanes(lanes));
   check_hip(hipGetLastError(), "trace_rays launch");
 }
 
