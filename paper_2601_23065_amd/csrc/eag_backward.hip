@@ -279,6 +279,7 @@ struct SecondaryAdjSource {
   }
 };
 
+template <bool GROUPS>
 __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(2))) k_sb_bwd_secondary(TraceCtx tc, const CamBatch cams, int64_t hw,
                                                                   int32_t n_cams, SbParams sp, const float* state,
                                                                   const double* r1, const float* dL, GradPtrs gp,
@@ -306,7 +307,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
   src.item = 0;
   src.gR1 = src.gO = src.gW = d3(0.0, 0.0, 0.0);
   src.G = src.prefix = 0.0;
-  run_segments<Q_RADIANCE, true, false>(tc, src, work, hw * n_cams * sp.spp, hitlist, nullptr);
+  run_work<GROUPS, Q_RADIANCE, true, false>(tc, src, work, hw * n_cams * sp.spp, hitlist, nullptr);
   // (the runner's loop ends for the whole wave at once)
   if ((threadIdx.x & 63) == 0 && s_wcur[2 * wv + 1] < (unsigned)gr.n_chunks)
     gr.chunk_used[s_wcur[2 * wv + 1]] = s_wcur[2 * wv];
@@ -402,6 +403,7 @@ struct CameraAdjSource {
   __device__ __forceinline__ bool finish(const Seg<true>&, D3&, D3&) { return false; }
 };
 
+template <bool GROUPS>
 __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(2))) k_sb_bwd_camera(TraceCtx tc, const CamBatch cams, int64_t hw,
                                                                int32_t n_cams, SbParams sp, const float* state,
                                                                const double* r1, const double* adj, const float* dL,
@@ -427,7 +429,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
   src.gN = src.gR = src.gP = d3(0.0, 0.0, 0.0);
   src.gD = src.gA = src.Tm = src.G = src.prefix = 0.0;
   src.has_R = src.has_P = false;
-  run_segments<Q_ALL, true, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
+  run_work<GROUPS, Q_ALL, true, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
   if ((threadIdx.x & 63) == 0 && s_wcur[2 * wv + 1] < (unsigned)gr.n_chunks)
     gr.chunk_used[s_wcur[2 * wv + 1]] = s_wcur[2 * wv];
 }
@@ -496,6 +498,7 @@ struct Stage0AdjSource {
   __device__ __forceinline__ bool finish(const Seg<true>&, D3&, D3&) { return false; }
 };
 
+template <bool GROUPS>
 __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
 k_stage0_bwd(TraceCtx tc, const CamBatch cams, int64_t hw, int32_t n_cams, SbParams sp, const float* state,
              const float* dimg, GradPtrs gp, GradRecs gr, unsigned long long* work, uint64_t* hitlist) {
@@ -516,7 +519,7 @@ k_stage0_bwd(TraceCtx tc, const CamBatch cams, int64_t hw, int32_t n_cams, SbPar
   src.wcur = s_wcur + 2 * wv;
   src.gN = src.gR = d3(0.0, 0.0, 0.0);
   src.gD = src.gA = src.gE = src.Tm = src.G = src.prefix = 0.0;
-  run_segments<Q_ALL, true, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
+  run_work<GROUPS, Q_ALL, true, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
   if ((threadIdx.x & 63) == 0 && s_wcur[2 * wv + 1] < (unsigned)gr.n_chunks)
     gr.chunk_used[s_wcur[2 * wv + 1]] = s_wcur[2 * wv];
 }
@@ -672,13 +675,13 @@ void launch_single_bounce_backward(const TraceCtx& tc, const eag_surfels& s, con
   const unsigned grid = (unsigned)(runner_lanes() / TRACE_BLOCK);
   launch_zero_u64(work, 1, st);
   zero_record_counts(gr, n, st);
-  hipLaunchKernelGGL(k_sb_bwd_secondary, dim3(grid), dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, state, r1,
-                     dL, gp, gr, reinterpret_cast<double*>(scratch), work, hitlist);
+  hipLaunchKernelGGL(by_groups(hw * n_cams * sp.spp, runner_lanes()) ? k_sb_bwd_secondary<true> : k_sb_bwd_secondary<false>,
+                     dim3(grid), dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, state, r1, dL, gp, gr, reinterpret_cast<double*>(scratch), work, hitlist);
   reduce_records(gr, gacc, n, st);
   launch_zero_u64(work, 1, st);
   zero_record_counts(gr, n, st);
-  hipLaunchKernelGGL(k_sb_bwd_camera, dim3(grid), dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, state, r1,
-                     reinterpret_cast<const double*>(scratch), dL, gp, gr, work, hitlist);
+  hipLaunchKernelGGL(by_groups(hw * n_cams, runner_lanes()) ? k_sb_bwd_camera<true> : k_sb_bwd_camera<false>, dim3(grid),
+                     dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, state, r1, reinterpret_cast<const double*>(scratch), dL, gp, gr, work, hitlist);
   reduce_records(gr, gacc, n, st);
   check_hip(hipGetLastError(), "single-bounce backward launch");
 }
@@ -692,8 +695,8 @@ void launch_stage0_backward(const TraceCtx& tc, const eag_surfels& s, const CamB
   gr.chunk_next = work + 1;
   launch_zero_u64(work, 1, st);
   zero_record_counts(gr, n, st);
-  hipLaunchKernelGGL(k_stage0_bwd, dim3((unsigned)(runner_lanes() / TRACE_BLOCK)), dim3(TRACE_BLOCK), 0, st, tc, cams,
-                     hw, n_cams, sp, state, dimg, gp, gr, work, hitlist);
+  hipLaunchKernelGGL(by_groups(hw * n_cams, runner_lanes()) ? k_stage0_bwd<true> : k_stage0_bwd<false>,
+                     dim3((unsigned)(runner_lanes() / TRACE_BLOCK)), dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, state, dimg, gp, gr, work, hitlist);
   reduce_records(gr, gacc, n, st);
   check_hip(hipGetLastError(), "stage-0 backward launch");
 }

@@ -74,6 +74,7 @@ struct ZeroBounceSource {
   }
 };
 
+template <bool GROUPS>
 __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(2))) k_zero_bounce(TraceCtx tc, const CamBatch cams, int64_t hw,
                                                             int32_t n_cams, SbParams sp, float* rgb,
                                                             unsigned long long* work, uint64_t* hitlist) {
@@ -83,7 +84,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
   src.sp = sp;
   src.rgb = rgb;
   src.item = 0;
-  run_segments<Q_RADIANCE, false, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
+  run_work<GROUPS, Q_RADIANCE, false, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
 }
 
 struct RadianceAdjSource {
@@ -114,6 +115,7 @@ struct RadianceAdjSource {
   __device__ __forceinline__ bool finish(const Seg<false>&, D3&, D3&) { return false; }
 };
 
+template <bool GROUPS>
 __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(2))) k_zero_bounce_adj_r(TraceCtx tc, const CamBatch cams, int64_t hw,
                                                                   int32_t n_cams, SbParams sp, const float* dL,
                                                                   double* gr, int64_t n, unsigned long long* work,
@@ -126,7 +128,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
   src.gr = gr;
   src.n = n;
   src.dl = v3(0.f, 0.f, 0.f);
-  run_segments<Q_RADIANCE, false, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
+  run_work<GROUPS, Q_RADIANCE, false, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
 }
 
 __global__ void __launch_bounds__(256) k_bake_loss(const float* rgb, const float* target, int64_t m, double inv_count,
@@ -180,8 +182,8 @@ unsigned blocks_for(int64_t count) { return (unsigned)((count + 255) / 256); }
 void launch_zero_bounce(const TraceCtx& tc, const CamBatch& cams, int64_t hw, int32_t n_cams, const SbParams& sp,
                         float* rgb, unsigned long long* work, uint64_t* hitlist, hipStream_t st) {
   launch_zero_u64(work, 1, st);
-  hipLaunchKernelGGL(k_zero_bounce, dim3((unsigned)(runner_lanes() / TRACE_BLOCK)), dim3(TRACE_BLOCK), 0, st, tc,
-                     cams, hw, n_cams, sp, rgb, work, hitlist);
+  hipLaunchKernelGGL(by_groups(hw * n_cams, runner_lanes()) ? k_zero_bounce<true> : k_zero_bounce<false>,
+                     dim3((unsigned)(runner_lanes() / TRACE_BLOCK)), dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, rgb, work, hitlist);
   check_hip(hipGetLastError(), "zero-bounce launch");
 }
 
@@ -189,8 +191,8 @@ void launch_zero_bounce_adj_r(const TraceCtx& tc, const CamBatch& cams, int64_t 
                               const SbParams& sp, const float* dL, double* gacc, int64_t n, unsigned long long* work,
                               uint64_t* hitlist, hipStream_t st) {
   launch_zero_u64(work, 1, st);
-  hipLaunchKernelGGL(k_zero_bounce_adj_r, dim3((unsigned)(runner_lanes() / TRACE_BLOCK)), dim3(TRACE_BLOCK), 0, st,
-                     tc, cams, hw, n_cams, sp, dL, gacc, n, work, hitlist);
+  hipLaunchKernelGGL(by_groups(hw * n_cams, runner_lanes()) ? k_zero_bounce_adj_r<true> : k_zero_bounce_adj_r<false>,
+                     dim3((unsigned)(runner_lanes() / TRACE_BLOCK)), dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, dL, gacc, n, work, hitlist);
   check_hip(hipGetLastError(), "zero-bounce adjoint launch");
 }
 

@@ -368,7 +368,7 @@ struct MisPathSource {
 
 // Two waves per SIMD, as the plain path tracer: without the bound the
 // allocator takes enough registers for one.
-template <bool STATS>
+template <bool STATS, bool GROUPS>
 __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
 k_path_trace_mis(TraceCtx tc, PtLaunch L, EmitterDev E, PdfQueue Q, unsigned long long* work_counter,
                  unsigned long long* counters, uint64_t* hitlist) {
@@ -383,7 +383,7 @@ k_path_trace_mis(TraceCtx tc, PtLaunch L, EmitterDev E, PdfQueue Q, unsigned lon
   src.Wb = d3(0.0, 0.0, 0.0);
   src.pb = src.pbl = src.Sx = 0.0;
   src.light = src.cont = false;
-  run_segments<Q_ALL, false, STATS>(tc, src, work_counter, L.n_work, hitlist, counters);
+  run_work<GROUPS, Q_ALL, false, STATS>(tc, src, work_counter, L.n_work, hitlist, counters);
 }
 
 // One queued contribution per thread (grid-stride): its light pdf, its MIS
@@ -748,9 +748,10 @@ void launch_path_trace_mis(const TraceCtx& tc, const PtLaunch& L, const EmitterD
   Q.cap = queue_entries;
   launch_zero_u64(work_counter, 1, st);
   launch_zero_u64(Q.count, 1, st);
-  hipLaunchKernelGGL(counters ? k_path_trace_mis<true> : k_path_trace_mis<false>, dim3(blocks), dim3(TRACE_BLOCK), 0, st,
-                     tc, L, E, Q, work_counter, counters,
-                     hitlist);
+  const bool groups = by_groups(L.n_work, runner_lanes());
+  auto* const kernel = counters ? (groups ? k_path_trace_mis<true, true> : k_path_trace_mis<true, false>)
+                                : (groups ? k_path_trace_mis<false, true> : k_path_trace_mis<false, false>);
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(TRACE_BLOCK), 0, st, tc, L, E, Q, work_counter, counters, hitlist);
   check_hip(hipGetLastError(), "path_trace_mis launch");
   if (E.n > 0) {
     hipLaunchKernelGGL(k_settle_pdfs, dim3(blocks), dim3(TRACE_BLOCK), 0, st, E, Q, L.s[0].accum, counters);

@@ -32,7 +32,9 @@ __device__ __forceinline__ void add_fixed(int64_t* acc, float v) {
   }
 }
 
-// One lane's path.
+// One lane's path. MULTI: the launch has several slots; with one, its values
+// are the kernel's arguments and need no load per lane.
+template <bool MULTI>
 struct PathSource {
   const PtLaunch* L;
   int slot;
@@ -42,7 +44,9 @@ struct PathSource {
 
   __device__ __forceinline__ bool start(int64_t wid, TraceCtx& tcl, D3& O, D3& W) {
     int k = 0;
-    while (k < L->n_slots - 1 && wid >= L->s[k].global_end) ++k;
+    if constexpr (MULTI) {
+      while (k < L->n_slots - 1 && wid >= L->s[k].global_end) ++k;
+    }
     const PtSlot& S = L->s[k];
     const int64_t item = S.work_begin + (wid - (k ? L->s[k - 1].global_end : 0));
     const int64_t s_rel = item / S.tile_pixels;
@@ -66,7 +70,7 @@ struct PathSource {
   __device__ __forceinline__ void operator()(const Record&, const Attr&, double, double, double, double, D3, D3) const {}
 
   __device__ __forceinline__ bool finish(const Seg<false>& s, D3& O, D3& W) {
-    const PtSlot& S = L->s[slot];
+    const PtSlot& S = L->s[MULTI ? slot : 0];
     const double A = 1.0 - s.T;
     if (!(A > 0.0)) return false;   // (A > 0: some hit was blended)
     const bool emit = s.E > S.tau_E;
@@ -95,17 +99,17 @@ struct PathSource {
   }
 };
 
-template <bool STATS>
+template <bool STATS, bool GROUPS, bool MULTI>
 __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(2))) k_path_trace(TraceCtx tc, PtLaunch L,
                                                             unsigned long long* work_counter,
                                                             unsigned long long* counters, uint64_t* hitlist) {
-  PathSource src;
+  PathSource<MULTI> src;
   src.L = &L;
   src.slot = 0;
   src.pix = src.sample = 0;
   src.depth = 0;
   src.beta = v3(1.f, 1.f, 1.f);
-  run_segments<Q_ALL, false, STATS>(tc, src, work_counter, L.n_work, hitlist, counters);
+  run_work<GROUPS, Q_ALL, false, STATS>(tc, src, work_counter, L.n_work, hitlist, counters);
 }
 
 __global__ void k_zero_u64(unsigned long long* p, int n) {
@@ -134,9 +138,12 @@ void launch_path_trace(const TraceCtx& tc, const PtLaunch& L, unsigned long long
                        unsigned long long* counters, uint64_t* hitlist, hipStream_t st) {
   const unsigned blocks = (unsigned)(runner_lanes() / TRACE_BLOCK);
   hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, st, work_counter, 1);
-  // the statistics cost registers: a kernel of its own without them
-  hipLaunchKernelGGL(counters ? k_path_trace<true> : k_path_trace<false>, dim3(blocks), dim3(TRACE_BLOCK), 0, st, tc, L,
-                     work_counter, counters, hitlist);
+  // the statistics cost registers: kernels of their own without them
+  const bool multi = L.n_slots > 1, groups = !multi && by_groups(L.n_work, runner_lanes());
+  auto* kernel = counters ? k_path_trace<true, false, true> : k_path_trace<false, false, true>;
+  if (groups) kernel = counters ? k_path_trace<true, true, false> : k_path_trace<false, true, false>;
+  else if (!multi) kernel = counters ? k_path_trace<true, false, false> : k_path_trace<false, false, false>;
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(TRACE_BLOCK), 0, st, tc, L, work_counter, counters, hitlist);
   check_hip(hipGetLastError(), "path_trace launch");
 }
 

@@ -72,6 +72,7 @@ struct CameraSource {
   }
 };
 
+template <bool GROUPS>
 __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(2))) k_sb_camera(TraceCtx tc, const CamBatch cams, int64_t hw,
                                                            int32_t n_cams, SbParams sp, float* state, float* rgb,
                                                            unsigned long long* work, uint64_t* hitlist) {
@@ -82,7 +83,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
   src.state = state;
   src.rgb = rgb;
   src.item = 0;
-  run_segments<Q_ALL, true, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
+  run_work<GROUPS, Q_ALL, true, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
 }
 
 // One (pixel, sample) secondary segment per work item; a pixel whose camera
@@ -129,6 +130,7 @@ struct SecondarySource {
   }
 };
 
+template <bool GROUPS>
 __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(2))) k_sb_secondary(
     TraceCtx tc, const CamBatch cams, int64_t hw, int32_t n_cams, SbParams sp, const float* state, double* r1,
     unsigned long long* work, uint64_t* hitlist) {
@@ -140,7 +142,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
   src.state = state;
   src.r1 = r1;
   src.item = 0;
-  run_segments<Q_RADIANCE, true, false>(tc, src, work, hw * n_cams * sp.spp, hitlist, nullptr);
+  run_work<GROUPS, Q_RADIANCE, true, false>(tc, src, work, hw * n_cams * sp.spp, hitlist, nullptr);
 }
 
 __global__ void k_sb_resolve(int64_t n_pix, SbParams sp, const float* state, const double* r1, float* rgb) {
@@ -166,8 +168,8 @@ __global__ void k_sb_resolve(int64_t n_pix, SbParams sp, const float* state, con
 void launch_camera_pass(const TraceCtx& tc, const CamBatch& cams, int64_t hw, int32_t n_cams, const SbParams& sp,
                         float* state, float* rgb, unsigned long long* work, uint64_t* hitlist, hipStream_t st) {
   launch_zero_u64(work, 1, st);
-  hipLaunchKernelGGL(k_sb_camera, dim3((unsigned)(runner_lanes() / TRACE_BLOCK)), dim3(TRACE_BLOCK), 0, st, tc, cams,
-                     hw, n_cams, sp, state, rgb, work, hitlist);
+  hipLaunchKernelGGL(by_groups(hw * n_cams, runner_lanes()) ? k_sb_camera<true> : k_sb_camera<false>,
+                     dim3((unsigned)(runner_lanes() / TRACE_BLOCK)), dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, state, rgb, work, hitlist);
   check_hip(hipGetLastError(), "camera pass launch");
 }
 
@@ -175,13 +177,10 @@ void launch_single_bounce(const TraceCtx& tc, const CamBatch& cams, int64_t hw, 
                           const SbParams& sp, float* state, double* r1, float* rgb, unsigned long long* work,
                           uint64_t* hitlist, hipStream_t st) {
   const int64_t np = hw * n_cams;
-  const unsigned grid = (unsigned)(runner_lanes() / TRACE_BLOCK);
+  launch_camera_pass(tc, cams, hw, n_cams, sp, state, rgb, work, hitlist, st);
   launch_zero_u64(work, 1, st);
-  hipLaunchKernelGGL(k_sb_camera, dim3(grid), dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, state, rgb, work,
-                     hitlist);
-  launch_zero_u64(work, 1, st);
-  hipLaunchKernelGGL(k_sb_secondary, dim3((unsigned)(runner_lanes() / TRACE_BLOCK)), dim3(TRACE_BLOCK), 0, st, tc,
-                     cams, hw, n_cams, sp, (const float*)state, r1, work, hitlist);
+  hipLaunchKernelGGL(by_groups(np * sp.spp, runner_lanes()) ? k_sb_secondary<true> : k_sb_secondary<false>,
+                     dim3((unsigned)(runner_lanes() / TRACE_BLOCK)), dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, (const float*)state, r1, work, hitlist);
   hipLaunchKernelGGL(k_sb_resolve, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, np, sp,
                      (const float*)state, (const double*)r1, rgb);
   check_hip(hipGetLastError(), "single-bounce launch");

@@ -177,4 +177,109 @@ __device__ __forceinline__ void run_segments(const TraceCtx& tc, Src& src, unsig
   if constexpr (STATS) rs.flush(counters);
 }
 
+// The same work by groups of lanes (group_traverse), for launches with too few
+// items to give every lane one: a wave holds lanes_per_wave items, each with a
+// group of G lanes, and its groups go round by round together. The first lane
+// of a group is the one that carries the item: it alone runs the source.
+// Rounds keep no hit list.
+template <int QMODE, bool DACC, bool STATS, class Src>
+__device__ __forceinline__ void run_groups(const TraceCtx& tc, Src& src, unsigned long long* work_counter,
+                                           int64_t n_work, unsigned long long* counters) {
+  __shared__ int s_stack[STACK_LDS * TRACE_BLOCK];
+  __shared__ int s_pend[PEND * TRACE_BLOCK];
+  int s_ovf[STACK_OVF];
+  TravStack st;
+  st.lds = s_stack + threadIdx.x;
+  st.ovf = s_ovf;
+  st.sp = 0;
+  bind_lds_stack(src, st.lds, 0);
+  int* const pend = s_pend + threadIdx.x;
+  const int lane = (int)(threadIdx.x & 63);
+  const uint64_t lt_mask = (1ull << lane) - 1ull;
+  const int lanes = lanes_per_wave(n_work, (int64_t)gridDim.x * (TRACE_BLOCK / 64));
+  const int G = group_lanes(lanes), lead = lane & ~(G - 1);
+  const bool first = lane == lead, eligible = first && lane / G < lanes;
+  TraceCtx tcl = tc;
+  SegStats<DACC, STATS, false> s;
+  seg_begin(s, d3(0.0, 0.0, 0.0), d3(0.0, 0.0, 1.0));
+  Round r;
+  RunStats rs;
+  D3 O = d3(0.0, 0.0, 0.0), W = d3(0.0, 0.0, 1.0);
+  bool idle = true, fresh = false;   // of the first lane's item; fresh: (O, W) is its next segment's ray
+  while (true) {
+    const bool need = eligible && idle;
+    const uint64_t m = __ballot(need);
+    bool exhausted = false;
+    if (m) {
+      const int leader = __ffsll((unsigned long long)m) - 1;
+      unsigned long long base = 0;
+      if (lane == leader) base = atomicAdd(work_counter, (unsigned long long)__popcll(m));
+      base = __shfl(base, leader);
+      exhausted = base + (unsigned long long)__popcll(m) >= (unsigned long long)n_work;
+      if (need) {
+        const int64_t wid = (int64_t)base + __popcll(m & lt_mask);
+        if (wid < n_work && src.start(wid, tcl, O, W)) {
+          idle = false;
+          fresh = true;
+          if constexpr (STATS) {
+            ++rs.items;
+            ++rs.segments;
+          }
+        }
+      }
+    }
+    if (!__any(!idle)) {
+      if (exhausted) break;
+      continue;
+    }
+    // the group follows its first lane: the ray of a new segment, else where
+    // the last round ended
+    const bool on = __shfl(idle ? 0 : 1, lead) != 0, begin = __shfl(fresh ? 1 : 0, lead) != 0;
+    if (__any(begin)) {
+      const D3 o = d3(__shfl(O.x, lead), __shfl(O.y, lead), __shfl(O.z, lead));
+      const D3 w = d3(__shfl(W.x, lead), __shfl(W.y, lead), __shfl(W.z, lead));
+      if (begin) seg_begin(s, o, w);
+    }
+    fresh = false;
+    s.last = (uint64_t)__shfl((unsigned long long)s.last, lead);
+    round_begin(tcl, s, r, st, pend);
+    const bool fits = group_traverse(tcl, s, r, s_stack, s_pend, G, on);
+    if (first && on) {
+      if (!fits) {
+        round_begin(tcl, s, r, st, pend);
+        traverse_round(tcl, s, r, st, pend, 1);
+      }
+      blend_round<QMODE>(tcl, s, r, src, nullptr, 0);
+      if constexpr (STATS) {
+        rs.rounds += s.rounds;
+        rs.hits += s.nhits;
+      }
+      if (s.done) {
+        fresh = src.finish(s, O, W);
+        idle = !fresh;
+        if constexpr (STATS) rs.segments += fresh ? 1 : 0;
+      }
+    }
+    if constexpr (STATS) {
+      rs.tests += s.tests;
+      rs.visits += s.visits;
+      s.rounds = s.tests = s.nhits = s.visits = 0;
+    }
+  }
+  if constexpr (STATS) rs.flush(counters);
+}
+
+// Whether a launch of n_work items runs by groups (the host's choice of
+// kernel: the two ways share nothing but LDS, and the registers of both).
+inline bool by_groups(int64_t n_work, int64_t grid_lanes) {
+  return group_lanes(lanes_per_wave(n_work, grid_lanes / 64)) > 1;
+}
+
+template <bool GROUPS, int QMODE, bool DACC, bool STATS, class Src>
+__device__ __forceinline__ void run_work(const TraceCtx& tc, Src& src, unsigned long long* work_counter,
+                                         int64_t n_work, uint64_t* hitlist, unsigned long long* counters) {
+  if constexpr (GROUPS) run_groups<QMODE, DACC, STATS>(tc, src, work_counter, n_work, counters);
+  else run_segments<QMODE, DACC, STATS>(tc, src, work_counter, n_work, hitlist, counters);
+}
+
 }  // namespace eag
