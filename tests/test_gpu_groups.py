@@ -1,0 +1,118 @@
+"""Rays carried by groups of lanes (launches with few items) against the same
+rays carried by one lane each: the hits and sums of a ray do not depend on who
+traverses for it: hit lists are equal, and values, which are computed in
+double precision by the same expressions, agree to two units of float32 (the
+compiler may fuse differently in the two forms)."""
+import numpy as np
+import pytest
+import torch
+
+import scenegen as sg
+from tests._util import coplanar_stack, gpu_scene
+
+pytestmark = pytest.mark.gpu
+
+FULL = 140_000   # more rays than the grid has lanes: one lane each
+ULPS = 2 * 2.0 ** -23
+
+
+def _same(a, b):
+    return bool(((a - b).abs() <= ULPS * b.abs() + 1e-30).all())
+
+
+def _scene(which):
+    if which == "cloud":
+        return sg.cloud_scene(2000, seed=9)
+    if which == "stack":       # 300 layers in one depth bucket: many rounds
+        return coplanar_stack(300, seed=3)
+    return sg.cloud_scene(1, seed=3)
+
+
+@pytest.mark.parametrize("which", ["cloud", "stack", "single"])
+@pytest.mark.parametrize("m", [1, 2, 255, 2048, 2049, 8191, 16_385, 40_000])
+def test_trace_rays_small_batches_equal_a_full_one(which, m):
+    from paper_2601_23065_amd.api import BVH, Params, trace_rays
+    scene = _scene(which)
+    gs = gpu_scene(scene)
+    bvh = BVH(gs)
+    O, D = (torch.from_numpy(x).cuda() for x in sg.random_rays(scene, 4096, seed=2))
+    if which == "stack":       # through the stack, within its centres' spread
+        O[2], D[:2], D[2] = -2.3, 0.0, 1.0
+        O[:2] *= 0.2
+    reps = -(-FULL // 4096)
+    full = trace_rays(bvh, gs, Params(), O.repeat(1, reps), D.repeat(1, reps), max_hits=64)
+    k = -(-m // 4096)
+    small = trace_rays(bvh, gs, Params(), O.repeat(1, k)[:, :m].contiguous(), D.repeat(1, k)[:, :m].contiguous(),
+                       max_hits=64)
+    assert _same(small[0], full[0][:, :m])
+    assert torch.equal(small[1], full[1][:m]) and torch.equal(small[2], full[2][:m])
+
+
+def test_group_stack_that_does_not_fit():
+    """A chain-shaped tree of 600 coincident surfels under groups of two lanes
+    (48 stack entries): whichever way the group takes, the hits are those of
+    one lane per ray."""
+    from paper_2601_23065_amd.api import BVH, Params, trace_rays
+    n, f32 = 600, lambda a: np.ascontiguousarray(a, dtype=np.float32)
+    rot = np.zeros((4, n))
+    rot[0] = 1.0
+    scene = sg.Scene(f32(np.zeros((3, n))), f32(rot), f32(np.full((2, n), 0.2)), f32(np.full(n, 0.02)),
+                     f32(np.full((3, n), 0.5)), f32(np.full((3, n), 2.0)), f32(np.ones(n)),
+                     bounds=(np.full(3, -1.0), np.full(3, 1.0)))
+    gs = gpu_scene(scene)
+    bvh = BVH(gs)
+    O = torch.zeros(3, FULL, device="cuda")
+    O[0] = torch.linspace(-0.3, 0.3, FULL, device="cuda")
+    O[2] = -2.3
+    D = torch.zeros(3, FULL, device="cuda")
+    D[2] = 1.0
+    full = trace_rays(bvh, gs, Params(), O, D, max_hits=32)
+    for m in (40_000, 20_000):
+        part = trace_rays(bvh, gs, Params(), O[:, :m].contiguous(), D[:, :m].contiguous(), max_hits=32)
+        assert _same(part[0], full[0][:, :m]) and torch.equal(part[1], full[1][:m])
+
+
+@pytest.mark.parametrize("size,mis", [((64, 64), False), ((40, 24), False), ((136, 128), True)])
+def test_frames_by_samples_equal_one_launch(size, mis):
+    """All samples in one launch (one lane per path) and one sample a launch
+    (groups) fill the same accumulator, with and without emitter sampling."""
+    from paper_2601_23065_amd import api
+    scene = sg.cloud_scene(2000, seed=9)
+    gs = gpu_scene(scene)
+    bvh = api.BVH(gs)
+    cam = sg.Camera((0.0, 0.0, -3.0), (0.0, 0.0, 0.0), (0.0, 1.0, 0.0), 60.0, *size)
+    spp = -(-66_000 // (size[0] * size[1])) if not mis else 4
+    p = api.Params(spp=spp, max_depth=4, rr_start=2, seed=11)
+    em = api.Emitters(gs, p) if mis else None
+    run = (lambda *a, **k: api.path_trace_mis(bvh, gs, em, cam, p, *a, **k)) if mis else \
+          (lambda *a, **k: api.path_trace(bvh, gs, cam, p, *a, **k))
+    one = run(0, spp)
+    acc = None
+    for k in range(spp):
+        acc = run(k, 1, accum=acc)
+    # a path's value is float32 and its directions carry about 1e-13 from one
+    # form to the other: 1e-5 of a pixel's sum (2^-32 steps) is far above both
+    assert ((one - acc).abs().double() <= 1e-5 * one.abs().double() + spp * 2.0 ** 32 * 1e-9).all()
+
+
+@pytest.mark.parametrize("cams,size", [(1, (30, 20)), (2, (64, 64)), (8, (160, 120))])
+def test_single_bounce_small_and_large_batches(cams, size):
+    """The forward state and image of a camera do not depend on how many
+    cameras share the call (groups against one lane per item), and neither
+    does its gradient."""
+    from paper_2601_23065_amd import api
+    scene = sg.cloud_scene(2000, seed=9)
+    gs = gpu_scene(scene)
+    bvh = api.BVH(gs)
+    cam = sg.Camera((0.0, 0.0, -3.0), (0.0, 0.0, 0.0), (0.0, 1.0, 0.0), 60.0, *size)
+    p = api.Params(spp=4, seed=5)
+    one = api.render_single_bounce(bvh, gs, [cam], p)
+    many = api.render_single_bounce(bvh, gs, [cam] * cams, p)
+    assert _same(one[0], many[0])
+    z1, zn = api.render_zero_bounce(bvh, gs, [cam], p), api.render_zero_bounce(bvh, gs, [cam] * cams, p)
+    for c in range(cams):
+        assert _same(z1[0], zn[c])
+    d = torch.ones(1, size[1], size[0], 3, device="cuda")
+    g1 = api.zero_bounce_backward(bvh, gs, [cam], p, d)
+    gn = api.zero_bounce_backward(bvh, gs, [cam] * cams, p, d.repeat(cams, 1, 1, 1))
+    assert ((gn - cams * g1).abs() <= 1e-5 * cams * g1.abs() + 1e-12).all()
