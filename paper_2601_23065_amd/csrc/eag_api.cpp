@@ -245,7 +245,7 @@ void check_bvh(const eag_bvh* b, const eag_surfels* s) {
 }
 
 // Light-baking workspace: packed attributes, work counter, hit list, double
-// radiance-gradient accumulators [3][n], and the image, image gradient and
+// radiance-gradient accumulators, and the image, image gradient and
 // loss of eag_bake_step.
 struct BakeWs {
   Attr* attrs;
@@ -264,7 +264,7 @@ BakeWs bake_ws(void* base, int64_t n, int64_t n_values, int64_t hl_lanes) {
   w.attrs = c.take<Attr>(n);
   w.work = c.take<unsigned long long>(8);
   w.hitlist = c.take<uint64_t>((size_t)hl_lanes * HL_CAP);
-  w.gacc = c.take<double>((size_t)n * 3);
+  w.gacc = c.take<double>((size_t)n * RAD_STRIDE);
   w.rgb = c.take<float>(n_values);
   w.dL = c.take<float>(n_values);
   w.loss = c.take<double>(1);
@@ -823,11 +823,11 @@ eag_status eag_zero_bounce_backward(const eag_bvh* b, const eag_surfels* s, cons
     if (!ws || ws_bytes < w.bytes) fail(EAG_ERR_WORKSPACE_TOO_SMALL, "bake workspace too small");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const BakeCall k = bake_setup(b, s, cams, n_cams, p, w, st);
-    launch_zero_f64(w.gacc, b->n * 3, st);
+    launch_zero_f64(w.gacc, b->n * RAD_STRIDE, st);
     for_camera_batches(cams, n_cams, p, [&](int c0, int nc, const CamBatch& cb) {
-      launch_zero_bounce_adj_r(k.tc, cb, hw, nc, k.sp, dL_drgb + c0 * hw * 3, w.gacc, b->n, w.work, w.hitlist, st);
+      launch_zero_bounce_adj_r(k.tc, cb, hw, nc, k.sp, dL_drgb + c0 * hw * 3, w.gacc, w.work, w.hitlist, st);
     });
-    launch_add_grad(w.gacc, b->n * 3, grad_radiance, st);
+    launch_add_grad(w.gacc, b->n, grad_radiance, st);
   });
 }
 
@@ -870,11 +870,11 @@ eag_status eag_bake_step(const eag_bvh* b, const eag_surfels* s, const eag_camer
       launch_zero_bounce(k.tc, cb, hw, nc, k.sp, w.rgb + c0 * hw * 3, w.work, w.hitlist, st);
     });
     launch_bake_loss(w.rgb, targets, nv, w.dL, loss, st);
-    launch_zero_f64(w.gacc, b->n * 3, st);
+    launch_zero_f64(w.gacc, b->n * RAD_STRIDE, st);
     for_camera_batches(cams, n_cams, p, [&](int c0, int nc, const CamBatch& cb) {
-      launch_zero_bounce_adj_r(k.tc, cb, hw, nc, k.sp, w.dL + c0 * hw * 3, w.gacc, b->n, w.work, w.hitlist, st);
+      launch_zero_bounce_adj_r(k.tc, cb, hw, nc, k.sp, w.dL + c0 * hw * 3, w.gacc, w.work, w.hitlist, st);
     });
-    launch_adam(radiance, w.gacc, m, v, b->n * 3, *a, step, st);
+    launch_adam_radiance(radiance, w.gacc, m, v, b->n, *a, step, st);
   });
 }
 

@@ -173,13 +173,16 @@ void launch_sah_cost(const Node4* nodes, const BvhHeader* h, int64_t max_nodes, 
 void launch_zero_bounce(const TraceCtx& tc, const CamBatch& cams, int64_t hw, int32_t n_cams, const SbParams& sp,
                         float* rgb, unsigned long long* work, uint64_t* hitlist, hipStream_t st);
 void launch_zero_bounce_adj_r(const TraceCtx& tc, const CamBatch& cams, int64_t hw, int32_t n_cams,
-                              const SbParams& sp, const float* dL, double* gacc, int64_t n, unsigned long long* work,
+                              const SbParams& sp, const float* dL, double* gacc, unsigned long long* work,
                               uint64_t* hitlist, hipStream_t st);
+// Radiance-gradient accumulators: RAD_STRIDE doubles per surfel, three used.
+constexpr int RAD_STRIDE = 4;
 void launch_zero_f64(double* p, int64_t count, hipStream_t st);
-void launch_add_grad(const double* acc, int64_t count, float* g, hipStream_t st);
+void launch_add_grad(const double* acc, int64_t n, float* g, hipStream_t st);
 void launch_bake_loss(const float* rgb, const float* target, int64_t m, float* dL, double* loss, hipStream_t st);
-void launch_adam(float* r, const double* g, float* m, float* v, int64_t count, const eag_adam& a, int32_t step,
-                 hipStream_t st);
+// (acc: radiance-gradient accumulators; r, m, v: [3][n])
+void launch_adam_radiance(float* r, const double* acc, float* m, float* v, int64_t n, const eag_adam& a, int32_t step,
+                          hipStream_t st);
 void launch_adam(float* r, const float* g, float* m, float* v, int64_t count, const eag_adam& a, int32_t step,
                  hipStream_t st);
 
