@@ -220,7 +220,7 @@ RenderWs render_ws(void* base, int64_t n, int64_t n_pix, int64_t spp, bool own_s
     g.idx = c.take<uint32_t>(cap);
     g.order = c.take<uint32_t>(cap);
     g.cnt = c.take<uint32_t>(n);
-    g.cursor = c.take<uint32_t>(n);
+    g.rank = c.take<uint32_t>(cap);
     g.off = c.take<uint32_t>(n);
     g.scan_bytes = grad_rec_scan_bytes(n);
     g.scan_tmp = c.take<char>(g.scan_bytes);
@@ -338,7 +338,7 @@ Stage0Ws stage0_ws(void* base, int64_t n, int64_t n_pix, int64_t n_pix_batch, in
   g.idx = c.take<uint32_t>(cap);
   g.order = c.take<uint32_t>(cap);
   g.cnt = c.take<uint32_t>(n);
-  g.cursor = c.take<uint32_t>(n);
+  g.rank = c.take<uint32_t>(cap);
   g.off = c.take<uint32_t>(n);
   g.scan_bytes = grad_rec_scan_bytes(n);
   g.scan_tmp = c.take<char>(g.scan_bytes);

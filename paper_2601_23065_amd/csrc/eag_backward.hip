@@ -110,7 +110,9 @@ __device__ __forceinline__ void chain_values(const Geo& ge, D3 O, D3 W, double t
 // their sums taken in double, so a surfel's sum carries an error of about
 // 2^-24 of the sum of its terms' magnitudes at most) to the next slot of its
 // wave's current chunk of REC_CHUNK slots, and counts itself in a per-surfel
-// counter with an atomic whose result it does not wait for. A wave claims a
+// counter. What the atomic returns is the record's rank among its surfel's; the
+// lane stores it with its next record (or at the item's end), so it never waits
+// for it, and the placement needs no atomics of its own. A wave claims a
 // chunk from a global counter when the lanes of a call do not fit in its
 // current one (one atomic per many hits) and records how much of the chunk it
 // used; its cursor lives in LDS. After the pass, an exclusive scan of the
@@ -119,8 +121,18 @@ __device__ __forceinline__ void chain_values(const Geo& ge, D3 O, D3 W, double t
 // atomics, so any capacity is correct.
 constexpr unsigned REC_NO_CHUNK = 0xffffffffu;   // none claimed yet
 constexpr unsigned REC_SPENT = 0xfffffffeu;      // the chunks are exhausted: atomics from here on
-__device__ __forceinline__ void emit_record(const GradRecs& gr, const GradPtrs& gp, unsigned* wcur, uint32_t idx,
-                                            const double (&v)[GRAD_ROWS]) {
+// A lane's last record: its slot (or NO_SLOT) and, once the atomic has returned, its rank.
+constexpr uint32_t NO_SLOT = 0xffffffffu;
+struct LastRec {
+  uint32_t slot = NO_SLOT, rank = 0;
+};
+__device__ __forceinline__ void store_rank(const GradRecs& gr, LastRec& last) {
+  if (last.slot != NO_SLOT) gr.rank[last.slot] = last.rank;
+  last.slot = NO_SLOT;
+}
+__device__ __forceinline__ void emit_record(const GradRecs& gr, const GradPtrs& gp, unsigned* wcur, LastRec& last,
+                                            uint32_t idx, const double (&v)[GRAD_ROWS]) {
+  store_rank(gr, last);
   // wcur[0]: slots used in the wave's chunk, wcur[1]: the chunk (or none)
   const uint64_t act = __ballot(1);
   const int lane = (int)(threadIdx.x & 63);
@@ -152,7 +164,8 @@ __device__ __forceinline__ void emit_record(const GradRecs& gr, const GradPtrs& 
     for (int q = 0; q < GRAD_ROWS / 4; ++q)
       dst[q] = make_float4((float)v[4 * q], (float)v[4 * q + 1], (float)v[4 * q + 2], (float)v[4 * q + 3]);
     gr.idx[slot] = idx;
-    atomicAdd(gr.cnt + idx, 1u);   // no return value: the lane does not wait for it
+    last.slot = (uint32_t)slot;   // (at most 2^27 records)
+    last.rank = atomicAdd(gr.cnt + idx, 1u);
   } else {
     const int64_t n = gp.n;
     atomic_add3(gp.pos, n, idx, d3(v[0], v[1], v[2]));
@@ -180,6 +193,7 @@ struct SecondaryAdjSource {
   GradPtrs gp;
   GradRecs gr;
   unsigned* wcur;     // this wave's record cursor and chunk (LDS)
+  LastRec last;
   double* adj;
   bool ray_grad;
   // per item
@@ -244,10 +258,11 @@ struct SecondaryAdjSource {
     v[13] = w * gR1.x;
     v[14] = w * gR1.y;
     v[15] = w * gR1.z;
-    emit_record(gr, gp, wcur, idx, v);
+    emit_record(gr, gp, wcur, last, idx, v);
   }
 
   __device__ __forceinline__ bool finish(const Seg<true>&, D3&, D3&) {
+    store_rank(gr, last);
     double out[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (ray_grad) {
       const int64_t g = item / S;
@@ -329,6 +344,7 @@ struct CameraAdjSource {
   GradPtrs gp;
   GradRecs gr;
   unsigned* wcur;     // this wave's record cursor and chunk (LDS)
+  LastRec last;
   // per item
   D3 gN, gR, gP;
   double gD, gA, Tm, G, prefix;
@@ -397,10 +413,13 @@ struct CameraAdjSource {
     v[13] = has_R ? w * gR.x : 0.0;
     v[14] = has_R ? w * gR.y : 0.0;
     v[15] = has_R ? w * gR.z : 0.0;
-    emit_record(gr, gp, wcur, idx, v);
+    emit_record(gr, gp, wcur, last, idx, v);
   }
 
-  __device__ __forceinline__ bool finish(const Seg<true>&, D3&, D3&) { return false; }
+  __device__ __forceinline__ bool finish(const Seg<true>&, D3&, D3&) {
+    store_rank(gr, last);
+    return false;
+  }
 };
 
 template <bool GROUPS>
@@ -447,7 +466,8 @@ struct Stage0AdjSource {
   const float* dimg;
   GradPtrs gp;
   GradRecs gr;
-  unsigned* wcur;
+  unsigned* wcur;     // this wave's record cursor and chunk (LDS)
+  LastRec last;
   // per item
   D3 gN, gR;
   double gD, gA, gE, Tm, G, prefix;
@@ -492,10 +512,13 @@ struct Stage0AdjSource {
     v[13] = w * gR.x;
     v[14] = w * gR.y;
     v[15] = w * gR.z;
-    emit_record(gr, gp, wcur, idx, v);
+    emit_record(gr, gp, wcur, last, idx, v);
   }
 
-  __device__ __forceinline__ bool finish(const Seg<true>&, D3&, D3&) { return false; }
+  __device__ __forceinline__ bool finish(const Seg<true>&, D3&, D3&) {
+    store_rank(gr, last);
+    return false;
+  }
 };
 
 template <bool GROUPS>
@@ -543,37 +566,21 @@ __global__ void k_stage0_finalize(const double* acc, int64_t n, eag_surfel_grads
 // The counts of a pass: per surfel, per chunk, and the chunks claimed.
 __global__ void k_zero_records(GradRecs gr, int64_t n) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) {
-    gr.cnt[i] = 0u;
-    gr.cursor[i] = 0u;
-  }
+  if (i < n) gr.cnt[i] = 0u;
   if (i < gr.n_chunks) gr.chunk_used[i] = 0u;
   if (i == 0) *gr.chunk_next = 0ull;
 }
 
-// Every used slot of the claimed chunks goes to the next free position of its
-// surfel's range [off[i], off[i] + cnt[i]) of order (cursor: zeroed per-surfel
-// counts). Blocks stride over the claimed chunks only. Bound by the latency of
-// index, offset and returning atomic: a thread has its four slots of a chunk
-// in flight together.
+// Every used slot of the claimed chunks goes to its rank in its surfel's range
+// [off[i], off[i] + cnt[i]) of order. Blocks stride over the claimed chunks only.
 __global__ void __launch_bounds__(256) k_rec_place(GradRecs gr) {
-  constexpr int PER = (int)(REC_CHUNK / 256);
   const unsigned long long claimed = *gr.chunk_next;
   const int64_t nc = claimed < (unsigned long long)gr.n_chunks ? (int64_t)claimed : gr.n_chunks;
   for (int64_t ch = blockIdx.x; ch < nc; ch += gridDim.x) {
     const uint32_t used = gr.chunk_used[ch];
-    const int64_t s0 = ch * REC_CHUNK + threadIdx.x;
-    uint32_t at[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) at[k] = threadIdx.x + 256u * k < used ? gr.idx[s0 + 256 * k] : 0u;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const uint32_t i = at[k];
-      if (threadIdx.x + 256u * k < used) at[k] = gr.off[i] + atomicAdd(gr.cursor + i, 1u);
-    }
-#pragma unroll
-    for (int k = 0; k < PER; ++k)
-      if (threadIdx.x + 256u * k < used) gr.order[at[k]] = (uint32_t)(s0 + 256 * k);
+    const int64_t s0 = ch * REC_CHUNK;
+    for (uint32_t j = threadIdx.x; j < used; j += 256)
+      gr.order[gr.off[gr.idx[s0 + j]] + gr.rank[s0 + j]] = (uint32_t)(s0 + j);
   }
 }
 

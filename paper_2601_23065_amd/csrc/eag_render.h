@@ -117,8 +117,8 @@ constexpr int64_t REC_CHUNK = 1024;                   // slots a wave claims at 
 struct GradRecs {
   float* rec;                   // [n_chunks * REC_CHUNK][16] accumulator rows of each hit
   uint32_t* idx;                // surfel index of each record
+  uint32_t* rank;               // rank of each record among its surfel's
   uint32_t* cnt;                // [n] records per surfel
-  uint32_t* cursor;             // [n] placement cursor per surfel
   uint32_t* off;                // [n] exclusive scan of cnt
   uint32_t* order;              // slots grouped by surfel
   uint32_t* chunk_used;         // [n_chunks] slots used in each chunk of REC_CHUNK slots
