@@ -183,11 +183,24 @@ __device__ __forceinline__ void run_segments(const TraceCtx& tc, Src& src, unsig
   if constexpr (STATS) rs.flush(counters);
 }
 
-// The same work by groups of lanes (group_traverse), for launches with too few
-// items to give every lane one: a wave holds lanes_per_wave items, each with a
-// group of G lanes, and its groups go round by round together. The first lane
+// The same work by groups of lanes (group_traverse), for launches with few
+// items: a wave holds group_items items, each with a group of G lanes, and its
+// groups go round by round together. The first lane
 // of a group is the one that carries the item: it alone runs the source.
 // Rounds keep no hit list.
+//
+// Items a wave carries at a time. Fewer than it has to do in all (q = items /
+// waves), so that a wave whose items are short takes more of them, and each
+// group has more lanes. Measured with 1, 2, 4, 8 and 16 (us; 2048 waves):
+//   path tracing, 100,000-surfel room: 4 k paths 492 448 535 531 532, 10 k 774
+//   652 560 669 685, 19 k 1169 927 775 765 976, 50 k 2613 1883 1379 1203 1285,
+//   75 k 3830 2645 1812 1515 1518; Stage-0 step: 10 k pixels 754 692 710 804 808,
+//   19 k 1126 890 834 949 1241, 40 k 2101 1362 1081 1153 1424.
+__host__ __device__ inline int group_items(int64_t n_work, int64_t n_waves) {
+  const int64_t q = (n_work + n_waves - 1) / n_waves;
+  return q >= 40 ? 16 : (q >= 12 ? 8 : (q >= 4 ? 4 : (q >= 2 ? 2 : 1)));
+}
+
 template <int QMODE, bool DACC, bool STATS, class Src>
 __device__ __forceinline__ void run_groups(const TraceCtx& tc, Src& src, unsigned long long* work_counter,
                                            int64_t n_work, unsigned long long* counters) {
@@ -202,9 +215,9 @@ __device__ __forceinline__ void run_groups(const TraceCtx& tc, Src& src, unsigne
   int* const pend = s_pend + threadIdx.x;
   const int lane = (int)(threadIdx.x & 63);
   const uint64_t lt_mask = (1ull << lane) - 1ull;
-  const int lanes = lanes_per_wave(n_work, (int64_t)gridDim.x * (TRACE_BLOCK / 64));
-  const int G = group_lanes(lanes), lead = lane & ~(G - 1);
-  const bool first = lane == lead, eligible = first && lane / G < lanes;
+  const int G = 64 / group_items(n_work, (int64_t)gridDim.x * (TRACE_BLOCK / 64));
+  const int lead = lane & ~(G - 1);
+  const bool first = lane == lead;
   TraceCtx tcl = tc;
   SegStats<DACC, STATS, false> s;
   seg_begin(s, d3(0.0, 0.0, 0.0), d3(0.0, 0.0, 1.0));
@@ -213,7 +226,7 @@ __device__ __forceinline__ void run_groups(const TraceCtx& tc, Src& src, unsigne
   D3 O = d3(0.0, 0.0, 0.0), W = d3(0.0, 0.0, 1.0);
   bool idle = true, fresh = false;   // of the first lane's item; fresh: (O, W) is its next segment's ray
   while (true) {
-    const bool need = eligible && idle;
+    const bool need = first && idle;
     const uint64_t m = __ballot(need);
     bool exhausted = false;
     if (m) {
@@ -276,9 +289,16 @@ __device__ __forceinline__ void run_groups(const TraceCtx& tc, Src& src, unsigne
 }
 
 // Whether a launch of n_work items runs by groups (the host's choice of
-// kernel: the two ways share nothing but LDS, and the registers of both).
-inline bool by_groups(int64_t n_work, int64_t grid_lanes) {
-  return group_lanes(lanes_per_wave(n_work, grid_lanes / 64)) > 1;
+// kernel: the two ways share nothing but LDS). One lane per item has the higher
+// rate, and waits 2 ms for its longest path at the end; one lane per item
+// against groups (ms, a grid of 131,072 lanes): path tracing 75 k paths 2.37,
+// 1.52, 153 k 2.85, 2.44, 307 k 3.41, 4.14; emitter sampling 75 k 6.84, 6.01,
+// 153 k 8.96, 10.50; with one segment per item, the Stage-0 step, 131 k pixels
+// 2.23, 1.60, 262 k 2.50, 1.98, 524 k 2.88, 2.92; single-bounce step 65 k
+// secondary segments 2.26, 2.01, 262 k 4.03, 3.98.
+enum { ONE_SEGMENT, PATHS };
+inline bool by_groups(int kind, int64_t n_work, int64_t grid_lanes) {
+  return n_work <= (kind == ONE_SEGMENT ? 2 : 1) * grid_lanes;
 }
 
 template <bool GROUPS, int QMODE, bool DACC, bool STATS, class Src>

@@ -72,7 +72,7 @@ def test_group_stack_that_does_not_fit():
         assert _same(part[0], full[0][:, :m]) and torch.equal(part[1], full[1][:m])
 
 
-@pytest.mark.parametrize("size,mis", [((64, 64), False), ((40, 24), False), ((136, 128), True)])
+@pytest.mark.parametrize("size,mis", [((64, 64), False), ((120, 104), False), ((192, 192), True)])
 def test_frames_by_samples_equal_one_launch(size, mis):
     """All samples in one launch (one lane per path) and one sample a launch
     (groups) fill the same accumulator, with and without emitter sampling."""
@@ -81,7 +81,7 @@ def test_frames_by_samples_equal_one_launch(size, mis):
     gs = gpu_scene(scene)
     bvh = api.BVH(gs)
     cam = sg.Camera((0.0, 0.0, -3.0), (0.0, 0.0, 0.0), (0.0, 1.0, 0.0), 60.0, *size)
-    spp = -(-66_000 // (size[0] * size[1])) if not mis else 4
+    spp = -(-FULL // (size[0] * size[1])) if not mis else 4
     p = api.Params(spp=spp, max_depth=4, rr_start=2, seed=11)
     em = api.Emitters(gs, p) if mis else None
     run = (lambda *a, **k: api.path_trace_mis(bvh, gs, em, cam, p, *a, **k)) if mis else \
@@ -95,7 +95,7 @@ def test_frames_by_samples_equal_one_launch(size, mis):
     assert ((one - acc).abs().double() <= 1e-5 * one.abs().double() + spp * 2.0 ** 32 * 1e-9).all()
 
 
-@pytest.mark.parametrize("cams,size", [(1, (30, 20)), (2, (64, 64)), (8, (160, 120))])
+@pytest.mark.parametrize("cams,size", [(1, (30, 20)), (2, (64, 64)), (8, (200, 170))])
 def test_single_bounce_small_and_large_batches(cams, size):
     """The forward state and image of a camera do not depend on how many
     cameras share the call (groups against one lane per item), and neither
