@@ -182,11 +182,11 @@ __global__ void k_morton(eag_surfels s, const BvhHeader* h, uint64_t* codes, uin
 //
 // The iterations' cost is their launches: the clusters shrink by about a third
 // each time, so all but the first few iterations are small. Those first ones
-// (wide_iters: enough to come near PLOC_TAIL clusters) are four launches over
+// (wide_iters: enough to come near PLOC_TAIL clusters) are two launches over
 // the whole chip each; one block then runs all the others in one launch, from
 // LDS once a cluster per thread is left. Launching every possible iteration, as
-// empty as most were, took 340 launches: 0.66 ms of a 2000-surfel build and
-// 1.2 ms of a 1 M one.
+// empty as most were, in four launches each, took 0.66 ms of a 2000-surfel build
+// and 1.2 ms of a 1 M one.
 // ---------------------------------------------------------------------------
 constexpr int PLOC_R = 2;          // search radius (measured best of 1 to 16 for the path tracer)
 constexpr int PLOC_ITERS = 64;     // iterations before the halving fallback
@@ -200,21 +200,17 @@ constexpr int PLOC_LEVELS = PLOC_ITERS + 24;   // iterations launched for up to 
 
 struct PlocState {
   int32_t n;          // clusters now
-  int32_t n_prev;     // clusters before the last merge step
   int32_t cur;        // buffer holding the current clusters
-  int32_t active;     // the last scan found work to merge
   int32_t made;       // internal nodes made so far
-  int32_t made_base;  // nodes made before the last merge step
-  int32_t pad[2];
+  int32_t pad;
 };
 
 struct Ploc {
   int32_t* cl[2];     // cluster references (node >= 0, leaf ~position)
   float4* cb[2];      // cluster boxes: [2i] lo.xyz, [2i + 1] hi.xyz
   int32_t* nn;        // nearest neighbour of each cluster
-  int32_t* bsum;      // per block: clusters kept, nodes made
-  int32_t* boff;      // exclusive offsets of bsum
-  PlocState* st;
+  int2* bsum;         // per block: clusters kept, nodes made
+  PlocState* st;      // [2]: iteration t reads state t & 1 and writes the other
 };
 
 __device__ __forceinline__ float union_area(float4 al, float4 ah, float4 bl, float4 bh) {
@@ -259,43 +255,6 @@ __device__ __forceinline__ void ploc_merge(Node* nodes, int id, int c0, int c1, 
   hi = make_float4(fmaxf(h0.x, h1.x), fmaxf(h0.y, h1.y), fmaxf(h0.z, h1.z), 0.0f);
 }
 
-// Nearest neighbour of every cluster.
-__global__ void __launch_bounds__(PLOC_TILE) k_ploc_nn(Ploc P) {
-  __shared__ float4 slo[PLOC_TILE + 2 * PLOC_R], shi[PLOC_TILE + 2 * PLOC_R];
-  const int n = P.st->n;
-  if (n <= 1) return;
-  const int p = P.st->cur;
-  const float4* cb = P.cb[p];
-  for (int base = blockIdx.x * PLOC_TILE; base < n; base += gridDim.x * PLOC_TILE) {
-    const int i = base + (int)threadIdx.x;
-    for (int k = threadIdx.x; k < PLOC_TILE + 2 * PLOC_R; k += PLOC_TILE) {
-      const int g = base - PLOC_R + k;
-      if (g >= 0 && g < n) {
-        slo[k] = cb[2 * g];
-        shi[k] = cb[2 * g + 1];
-      }
-    }
-    __syncthreads();
-    if (i < n) {
-      const int li = (int)threadIdx.x + PLOC_R;
-      const float4 al = slo[li], ah = shi[li];
-      float best = INFINITY;
-      int bj = i;
-      for (int d = -PLOC_R; d <= PLOC_R; ++d) {
-        const int g = i + d;
-        if (d == 0 || g < 0 || g >= n) continue;
-        const float a = union_area(al, ah, slo[li + d], shi[li + d]);
-        if (a < best) {   // ascending g: ties keep the lower position
-          best = a;
-          bj = g;
-        }
-      }
-      P.nn[i] = bj;
-    }
-    __syncthreads();
-  }
-}
-
 // Per position: kept (a cluster survives there) and made (a node is made
 // there, at the lower position of a mutual pair).
 __device__ __forceinline__ void ploc_decide(const int32_t* nn, int i, int& j, bool& keep, bool& made) {
@@ -330,103 +289,125 @@ __device__ __forceinline__ void ploc_chunk(int n, int& lo, int& hi) {
   hi = min(n, lo + chunk);
 }
 
-__global__ void __launch_bounds__(PLOC_TILE) k_ploc_count(Ploc P) {
-  __shared__ int lds[4];
-  const int n = P.st->n;
-  if (n <= 1) return;
-  int lo, hi;
-  ploc_chunk(n, lo, hi);
-  int keep_sum = 0, made_sum = 0;
-  for (int base = lo; base < hi; base += PLOC_TILE) {
-    const int i = base + (int)threadIdx.x;
-    int v = 0;
-    if (i < hi) {
-      int j;
-      bool keep, made;
-      ploc_decide(P.nn, i, j, keep, made);
-      v = (keep ? 1 : 0) | (made ? 1 << 16 : 0);
-    }
-    int tot;
-    scan_pair(v, lds, &tot);
-    keep_sum += tot & 0xffff;
-    made_sum += tot >> 16;
+// Sum of two counts over a block of PLOC_TILE threads, in every thread.
+__device__ __forceinline__ int2 block_sum2(int2 v, int2* lds) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    v.x += __shfl_xor(v.x, o);
+    v.y += __shfl_xor(v.y, o);
   }
-  if (threadIdx.x == 0) {
-    P.bsum[2 * blockIdx.x] = keep_sum;
-    P.bsum[2 * blockIdx.x + 1] = made_sum;
-  }
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+  __syncthreads();
+  const int2 t = make_int2(lds[0].x + lds[1].x + lds[2].x + lds[3].x, lds[0].y + lds[1].y + lds[2].y + lds[3].y);
+  __syncthreads();
+  return t;
 }
 
-// One block: offsets of the blocks' kept clusters and made nodes, and the
-// state for the write step.
+// First half of iteration t: the partner of every cluster (nn[i]: its mutual
+// nearest neighbour, or itself), and what each block's part of the order will
+// keep and make. A tile's neighbours' neighbours are found here again rather
+// than read from another launch.
+__global__ void __launch_bounds__(PLOC_TILE) k_ploc_pairs(Ploc P, int t) {
+  constexpr int BOXES = PLOC_TILE + 4 * PLOC_R, NEAR = PLOC_TILE + 2 * PLOC_R;
+  __shared__ float4 slo[BOXES], shi[BOXES];
+  __shared__ int snn[NEAR];
+  __shared__ int2 lds[PLOC_TILE / 64];
+  const PlocState st = P.st[t & 1];
+  const int n = st.n;
+  if (n <= 1) return;
+  const float4* cb = P.cb[st.cur];
+  int lo, hi;
+  ploc_chunk(n, lo, hi);
+  int2 sum = make_int2(0, 0);
+  for (int base = lo; base < hi; base += PLOC_TILE) {
+    for (int k = threadIdx.x; k < BOXES; k += PLOC_TILE) {
+      const int g = base - 2 * PLOC_R + k;
+      if (g >= 0 && g < n) {
+        slo[k] = cb[2 * g];
+        shi[k] = cb[2 * g + 1];
+      }
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < NEAR; k += PLOC_TILE) {
+      const int i = base - PLOC_R + k, li = k + PLOC_R;
+      int bj = i;
+      if (i >= 0 && i < n) {
+        const float4 al = slo[li], ah = shi[li];
+        float best = INFINITY;
+        for (int d = -PLOC_R; d <= PLOC_R; ++d) {
+          const int g = i + d;
+          if (d == 0 || g < 0 || g >= n) continue;
+          const float a = union_area(al, ah, slo[li + d], shi[li + d]);
+          if (a < best) {   // ascending g: ties keep the lower position
+            best = a;
+            bj = g;
+          }
+        }
+      }
+      snn[k] = bj;
+    }
+    __syncthreads();
+    const int i = base + (int)threadIdx.x;
+    if (i < hi) {
+      const int j = snn[i - base + PLOC_R];
+      const int p = j != i && snn[j - base + PLOC_R] == i ? j : i;
+      P.nn[i] = p;
+      sum.x += p >= i ? 1 : 0;
+      sum.y += p > i ? 1 : 0;
+    }
+    __syncthreads();
+  }
+  const int2 tot = block_sum2(sum, lds);
+  if (threadIdx.x == 0) P.bsum[blockIdx.x] = tot;
+}
+
+// Second half: the merges, and the order compacted. Each block sums up what the
+// blocks before it keep and make; the first one also makes the next state.
 // levels[t]: the nodes made before iteration t (iteration t makes the ids
 // n - 2 - k for k in [levels[t], levels[t + 1])), kept with the tree for
 // refits.
-__global__ void __launch_bounds__(PLOC_GRID) k_ploc_scan(Ploc P, int blocks, int t_iter, int32_t* levels) {
-  __shared__ int lk[PLOC_GRID / 64], lm[PLOC_GRID / 64];
-  PlocState* st = P.st;
-  const int n = st->n;
-  if (threadIdx.x == 0) levels[t_iter] = st->made;
+__global__ void __launch_bounds__(PLOC_TILE) k_ploc_write(Ploc P, int t, int32_t* levels, int64_t n_leaves,
+                                                         Node* nodes) {
+  __shared__ int lds[4];
+  __shared__ int2 lds2[PLOC_TILE / 64];
+  const PlocState st = P.st[t & 1];
+  const int n = st.n;
   if (n <= 1) {
-    if (threadIdx.x == 0) st->active = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      P.st[(t + 1) & 1] = st;
+      levels[t] = st.made;
+    }
     return;
   }
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int k0 = t < blocks ? P.bsum[2 * t] : 0, m0 = t < blocks ? P.bsum[2 * t + 1] : 0;
-  int k = k0, m = m0;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int a = __shfl_up(k, o), b = __shfl_up(m, o);
-    if (lane >= o) {
-      k += a;
-      m += b;
+  const int end = blockIdx.x == 0 ? (int)gridDim.x : (int)blockIdx.x;
+  int2 v = make_int2(0, 0);
+  for (int k = threadIdx.x; k < end; k += PLOC_TILE) {
+    const int2 q = P.bsum[k];
+    v.x += q.x;
+    v.y += q.y;
+  }
+  int2 before = block_sum2(v, lds2);
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) {
+      PlocState next = {};
+      next.n = before.x;
+      next.cur = st.cur ^ 1;
+      next.made = st.made + before.y;
+      P.st[(t + 1) & 1] = next;
+      levels[t] = st.made;
     }
+    before = make_int2(0, 0);
   }
-  if (lane == 63) {
-    lk[w] = k;
-    lm[w] = m;
-  }
-  __syncthreads();
-  int kb = 0, mb = 0, kt = 0, mt = 0;
-  for (int q = 0; q < PLOC_GRID / 64; ++q) {
-    if (q < w) {
-      kb += lk[q];
-      mb += lm[q];
-    }
-    kt += lk[q];
-    mt += lm[q];
-  }
-  if (t < blocks) {
-    P.boff[2 * t] = kb + k - k0;
-    P.boff[2 * t + 1] = mb + m - m0;
-  }
-  if (t == 0) {
-    st->n_prev = n;
-    st->n = kt;
-    st->cur ^= 1;
-    st->active = 1;
-    st->made_base = st->made;
-    st->made += mt;
-  }
-}
-
-__global__ void __launch_bounds__(PLOC_TILE) k_ploc_write(Ploc P, int64_t n_leaves, Node* nodes) {
-  __shared__ int lds[4];
-  const PlocState* st = P.st;
-  if (!st->active) return;
-  const int n = st->n_prev;
-  const int out = st->cur, in = out ^ 1;
+  const int in = st.cur, out = in ^ 1;
   const int32_t* cl = P.cl[in];
   const float4* cb = P.cb[in];
   int lo, hi;
   ploc_chunk(n, lo, hi);
-  int keep_at = P.boff[2 * blockIdx.x];
-  int made_at = st->made_base + P.boff[2 * blockIdx.x + 1];
+  int keep_at = before.x, made_at = st.made + before.y;
   for (int base = lo; base < hi; base += PLOC_TILE) {
     const int i = base + (int)threadIdx.x;
-    int j = i;
-    bool keep = false, made = false;
-    if (i < hi) ploc_decide(P.nn, i, j, keep, made);
+    const int j = i < hi ? P.nn[i] : -1;
+    const bool keep = i < hi && j >= i, made = keep && j > i;
     int tot;
     const int off = scan_pair((keep ? 1 : 0) | (made ? 1 << 16 : 0), lds, &tot);
     if (keep) {
@@ -481,7 +462,8 @@ __global__ void __launch_bounds__(PLOC_TAIL) k_ploc_tail(Ploc P, int64_t n_leave
   __shared__ float4 slo[PLOC_TAIL], shi[PLOC_TAIL];
   __shared__ int sref[PLOC_TAIL], snn[PLOC_TAIL], lds[PLOC_TAIL / 64];
   const int tid = (int)threadIdx.x;
-  int n = P.st->n, made = P.st->made, cur = P.st->cur, t = t0;
+  const PlocState st = P.st[t0 & 1];
+  int n = st.n, made = st.made, cur = st.cur, t = t0;
   // Too many clusters for LDS: the same iteration over memory, in tiles.
   while (n > PLOC_TAIL) {
     const bool halving = t >= PLOC_ITERS || n > PLOC_TAIL_MAX;
@@ -662,12 +644,15 @@ __global__ void __launch_bounds__(256) k_records(int64_t n, const int32_t* perm,
   r[2] = c;
 }
 
-__global__ void k_attrs(eag_surfels s, const int32_t* perm, Attr* attrs) {
+// Attribute rows into sorted order, from the caller's order: the seven arrays
+// are read in sequence and each row is one piece of 32 bytes wherever it goes.
+// (Gathered in the sorted order, each component cost a cache line: 121 us for
+// 1 M surfels against 39.)
+__global__ void __launch_bounds__(256) k_attrs(eag_surfels s, const int32_t* inv, Attr* attrs) {
   const int64_t n = s.n;
-  const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  const int64_t i = perm[j];
-  float4* a = reinterpret_cast<float4*>(attrs + j);
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  float4* a = reinterpret_cast<float4*>(attrs + inv[i]);
   a[0] = make_float4(s.albedo[i], s.albedo[n + i], s.albedo[2 * n + i], s.emissive[i]);
   a[1] = make_float4(s.radiance[i], s.radiance[n + i], s.radiance[2 * n + i], 0.0f);
 }
@@ -958,8 +943,7 @@ struct BuildWs {
   uint32_t* ids_in;
   int32_t* nn;
   float4* cbox[2];         // cluster boxes; before them, the records in the caller's order
-  int32_t* bsum;
-  int32_t* boff;
+  int2* bsum;
   PlocState* ploc;
   void* sort_tmp;
   size_t sort_bytes;
@@ -979,9 +963,8 @@ BuildWs build_ws(void* base, int64_t n) {
   w.nn = c.take<int32_t>(n);
   w.cbox[0] = c.take<float4>(4 * n);
   w.cbox[1] = w.cbox[0] + 2 * n;
-  w.bsum = c.take<int32_t>(2 * PLOC_GRID);
-  w.boff = c.take<int32_t>(2 * PLOC_GRID);
-  w.ploc = c.take<PlocState>(1);
+  w.bsum = c.take<int2>(PLOC_GRID);
+  w.ploc = c.take<PlocState>(2);
   w.sort_bytes = sort_pairs_bytes(n);
   w.sort_tmp = c.take<char>(w.sort_bytes);
   w.bytes = c.bytes();
@@ -999,7 +982,6 @@ Ploc ploc_ws(const BuildWs& w) {
   }
   P.nn = w.nn;
   P.bsum = w.bsum;
-  P.boff = w.boff;
   P.st = w.ploc;
   return P;
 }
@@ -1075,10 +1057,8 @@ void build_bvh(const eag_surfels* s, eag_bvh* b, void* ws, size_t ws_bytes, hipS
     const unsigned g = std::min<unsigned>(blocks(n, PLOC_TILE), (unsigned)PLOC_GRID);
     const int wide = wide_iters(n);
     for (int t = 0; t < wide; ++t) {
-      hipLaunchKernelGGL(k_ploc_nn, dim3(g), dim3(PLOC_TILE), 0, st, P);
-      hipLaunchKernelGGL(k_ploc_count, dim3(g), dim3(PLOC_TILE), 0, st, P);
-      hipLaunchKernelGGL(k_ploc_scan, dim3(1), dim3(PLOC_GRID), 0, st, P, (int)g, t, b->levels);
-      hipLaunchKernelGGL(k_ploc_write, dim3(g), dim3(PLOC_TILE), 0, st, P, n, b->nodes);
+      hipLaunchKernelGGL(k_ploc_pairs, dim3(g), dim3(PLOC_TILE), 0, st, P, t);
+      hipLaunchKernelGGL(k_ploc_write, dim3(g), dim3(PLOC_TILE), 0, st, P, t, b->levels, n, b->nodes);
     }
     hipLaunchKernelGGL(k_ploc_tail, dim3(1), dim3(PLOC_TAIL), 0, st, P, n, b->nodes, wide, PLOC_ITERS + b->idx_bits,
                        b->levels, b->hdr);
@@ -1128,7 +1108,7 @@ void refit_bvh(const eag_surfels* s, eag_bvh* b, void* ws, size_t ws_bytes, hipS
 }
 
 void pack_attrs(const eag_surfels* s, const eag_bvh* b, Attr* attrs, hipStream_t st) {
-  hipLaunchKernelGGL(k_attrs, dim3(blocks(s->n)), dim3(256), 0, st, *s, b->perm, attrs);
+  hipLaunchKernelGGL(k_attrs, dim3(blocks(s->n)), dim3(256), 0, st, *s, b->inv, attrs);
 }
 
 }  // namespace eag
