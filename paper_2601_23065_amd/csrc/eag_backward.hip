@@ -241,6 +241,7 @@ struct SecondaryAdjSource {
     return true;
   }
 
+  static constexpr bool kHits = true;
   __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, D3 O,
                                              D3 W) {
     const uint32_t idx = rec_index(r);
@@ -391,6 +392,7 @@ struct CameraAdjSource {
     return true;
   }
 
+  static constexpr bool kHits = true;
   __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, D3 O,
                                              D3 W) {
     const uint32_t idx = rec_index(r);
@@ -492,6 +494,7 @@ struct Stage0AdjSource {
     return true;
   }
 
+  static constexpr bool kHits = true;
   __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, D3 O,
                                              D3 W) {
     const uint32_t idx = rec_index(r);

@@ -58,6 +58,7 @@ struct ZeroBounceSource {
   float* rgb;
   int64_t item;
 
+  static constexpr bool kHits = false;
   __device__ __forceinline__ void operator()(const Record&, const Attr&, double, double, double, double, D3, D3) const {}
 
   __device__ __forceinline__ bool start(int64_t wid, TraceCtx&, D3& O, D3& W) {
@@ -108,6 +109,7 @@ struct RadianceAdjSource {
     return true;
   }
 
+  static constexpr bool kHits = true;
   __device__ __forceinline__ void operator()(const Record& r, const Attr&, double, double, double w, double, D3, D3) {
     const uint32_t idx = rec_index(r);
     const double v[3] = {w * (double)dl.x, w * (double)dl.y, w * (double)dl.z};

@@ -363,6 +363,7 @@ __device__ __forceinline__ float slab(float lx, float ly, float lz, float hx, fl
 
 // No per-hit callback (forward passes).
 struct NoHit {
+  static constexpr bool kHits = false;
   __device__ __forceinline__ void operator()(const Record&, const Attr&, double, double, double, double, D3, D3) const {}
 };
 
@@ -976,6 +977,65 @@ __device__ bool group_traverse(const TraceCtx& tc, S& s, Round& r, int* stack, i
   return fits;
 }
 
+// A hit of the ray (O, W) on a surfel, as group_blend passes it round (blend_round
+// has the same expressions in line: through these functions its register
+// allocation cost the path tracer 3%): distance t, alpha,
+// the unnormalised normal cn = |q|^2 n with its scale 1 / |q|^2, negated when n
+// points along the ray (n' faces the origin).
+struct HitEval {
+  double t, a, iq2;
+  D3 cn;
+};
+__device__ __forceinline__ HitEval eval_hit(const Record& rec, D3 O, D3 W) {
+  // t, u, v and the unit normal from the columns of the unnormalised
+  // quaternion's rotation, |q|^2 (t_u, t_v, n): no square root, and one
+  // reciprocal c = 1 / (|q|^2 s_u s_v) for u^2 + v^2 and the normal's scale
+  const double qw = rec.q.x, qx = rec.q.y, qy = rec.q.z, qz = rec.q.w;
+  const double su = rec.s_idx.x, sv = rec.s_idx.y;
+  const double c = 1.0 / ((qw * qw + qx * qx + qy * qy + qz * qz) * (su * sv));
+  const double iq2 = c * (su * sv);
+  const D3 cu = d3(qw * qw + qx * qx - qy * qy - qz * qz, 2.0 * (qx * qy + qw * qz), 2.0 * (qx * qz - qw * qy));
+  const D3 cv = d3(2.0 * (qx * qy - qw * qz), qw * qw - qx * qx + qy * qy - qz * qz, 2.0 * (qy * qz + qw * qx));
+  const D3 cn = d3(2.0 * (qx * qz + qw * qy), 2.0 * (qy * qz - qw * qx), qw * qw - qx * qx - qy * qy + qz * qz);
+  const D3 dp = d3((double)rec.p_sigma.x - O.x, (double)rec.p_sigma.y - O.y, (double)rec.p_sigma.z - O.z);
+  const double dn = dot(W, cn);
+  const double t = dot(dp, cn) / dn;
+  const D3 yv = d3(t * W.x - dp.x, t * W.y - dp.y, t * W.z - dp.z);
+  const double uc = dot(yv, cu) * sv, vc = dot(yv, cv) * su;   // u, v times |q|^2 s_u s_v
+  const double a = (double)rec.p_sigma.w * exp(-0.5 * ((uc * uc + vc * vc) * (c * c)));
+  HitEval h;
+  h.t = t;
+  h.a = a;
+  h.iq2 = dn > 0.0 ? -iq2 : iq2;
+  h.cn = cn;
+  return h;
+}
+
+// Add a hit's terms to the segment: weight T alpha on everything, then T.
+template <int QMODE, class S>
+__device__ __forceinline__ void blend_hit(const TraceCtx& tc, S& s, const HitEval& h, const float4& rho_e,
+                                          const float4& rr) {
+  using Acc = typename S::Acc;
+  const double w = s.T * h.a;
+  const Acc wf = (Acc)w;
+  if (QMODE == Q_ALL) {
+    const double sw = w * h.iq2;
+    s.N.x += sw * h.cn.x;
+    s.N.y += sw * h.cn.y;
+    s.N.z += sw * h.cn.z;
+    s.D += w * h.t;
+    s.P0 += wf * rho_e.x;
+    s.P1 += wf * rho_e.y;
+    s.P2 += wf * rho_e.z;
+    s.E += wf * rho_e.w;
+  }
+  s.R0 += wf * rr.x;
+  s.R1 += wf * rr.y;
+  s.R2 += wf * rr.z;
+  s.T *= (1.0 - h.a);
+  if (s.T < tc.T_min) s.done = true;
+}
+
 // Blend the round's hits in key order; t and alpha are recomputed from the
 // record with the same double-precision test. Sets s.done after the first hit
 // with T < T_min or when the round returned fewer than KBUF hits. The sorted
@@ -1040,7 +1100,7 @@ __device__ __forceinline__ void blend_round(const TraceCtx& tc, S& s, Round& r, 
     if constexpr (S::kStats) {
       if (hit_out && s.nhits < max_hits) hit_out[s.nhits] = (int32_t)rec_index(rec);
     }
-    on_hit(rec, at, t, a, w, s.T, s.O, s.W);
+    if constexpr (HitFn::kHits) on_hit(rec, at, t, a, w, s.T, s.O, s.W);
     if constexpr (S::kStats) ++s.nhits;
     s.T *= (1.0 - a);
     if (s.T < tc.T_min) s.done = true;
@@ -1050,6 +1110,64 @@ __device__ __forceinline__ void blend_round(const TraceCtx& tc, S& s, Round& r, 
   }
   if (r.cnt < KBUF && !r.partial) s.done = true;
   if (!s.done) s.last = round_last;
+}
+
+// The blend of a round by a group of G lanes (all lanes of the wave call it; the
+// round is in the first lane of each group that is `on`): each lane evaluates
+// one of the round's hits, G at a time, and all lanes of the group then blend
+// them in order, so that every lane carries the segment. The same sums in the
+// same order as blend_round's. queue: the block's array of postponed leaves,
+// empty now.
+template <int QMODE, class S>
+__device__ __forceinline__ void group_blend(const TraceCtx& tc, S& s, const Round& r, int* queue, int G, bool on,
+                                            int32_t* hit_out, int max_hits) {
+  static_assert(!S::kList, "group rounds keep no hit list");
+  const int lane = (int)(threadIdx.x & 63), lig = lane & (G - 1), gb = lane & ~(G - 1);
+  const int sh = __ffs(G) - 1, col = (int)(threadIdx.x & ~63u) + gb;
+  volatile int* const vq = queue;
+  auto at = [&](int e) { return (e >> sh) * TRACE_BLOCK + col + (e & (G - 1)); };
+  if (lig == 0) {
+#pragma unroll
+    for (int i = 0; i < KBUF; ++i) vq[at(i)] = (int)key_idx(tc, r.kk[i]);
+  }
+  const int cnt = on ? __shfl(r.cnt, gb) : 0;
+  const uint64_t last = (uint64_t)__shfl((unsigned long long)r.kk[KBUF - 1], gb);
+  if (!on) s.done = true;
+  for (int c = 0; c < KBUF; c += G) {
+    if (!__any(c < cnt && !s.done)) break;
+    const int mine = c + lig;
+    const uint32_t idx = mine < cnt ? (uint32_t)vq[at(mine)] : 0u;
+    const uint32_t pos = (uint32_t)*elem(tc.inv, idx);
+    const Attr a0 = *elem(tc.attrs, pos);
+    const HitEval h0 = eval_hit(load_record(tc.recs, pos), s.O, s.W);
+    for (int j = 0; j < G && c + j < KBUF; ++j) {
+      if (!__any(c + j < cnt && !s.done)) break;
+      const int from = gb + j;
+      HitEval h;
+      float4 rho_e = make_float4(0.f, 0.f, 0.f, 0.f), rr = rho_e;
+      h.t = h.iq2 = 0.0;
+      h.cn = d3(0.0, 0.0, 0.0);
+      h.a = __shfl(h0.a, from);
+      rr = make_float4(__shfl(a0.r.x, from), __shfl(a0.r.y, from), __shfl(a0.r.z, from), 0.f);
+      if (QMODE == Q_ALL) {
+        h.t = __shfl(h0.t, from);
+        h.iq2 = __shfl(h0.iq2, from);
+        h.cn = d3(__shfl(h0.cn.x, from), __shfl(h0.cn.y, from), __shfl(h0.cn.z, from));
+        rho_e = make_float4(__shfl(a0.rho_e.x, from), __shfl(a0.rho_e.y, from), __shfl(a0.rho_e.z, from),
+                            __shfl(a0.rho_e.w, from));
+      }
+      const uint32_t hit = hit_out ? (uint32_t)__shfl((int)idx, from) : 0u;
+      if (c + j < cnt && !s.done) {
+        if constexpr (S::kStats) {
+          if (hit_out && lig == 0 && s.nhits < max_hits) hit_out[s.nhits] = (int32_t)hit;
+          ++s.nhits;
+        }
+        blend_hit<QMODE>(tc, s, h, rho_e, rr);
+      }
+    }
+  }
+  if (cnt < KBUF) s.done = true;
+  if (!s.done) s.last = last;
 }
 
 // A whole segment, without a hit list. Must be called from a
@@ -1085,16 +1203,11 @@ __device__ __forceinline__ SegOut trace_segment(const TraceCtx& tc, D3 O, D3 W, 
     while (__any(!s.done)) {
       round_begin(tc, s, r, st, pend);
       const bool fits = group_traverse(tc, s, r, s_stack, s_pend, G, !s.done);
-      if (first && !s.done) {
-        if (!fits) {
-          round_begin(tc, s, r, st, pend);
-          traverse_round(tc, s, r, st, pend, 1);
-        }
-        blend_round<QMODE>(tc, s, r, nh, hit_out, max_hits);
+      if (first && !s.done && !fits) {
+        round_begin(tc, s, r, st, pend);
+        traverse_round(tc, s, r, st, pend, 1);
       }
-      // the group follows its first lane
-      s.done = __shfl(s.done ? 1 : 0, lane & ~(G - 1)) != 0;
-      s.last = (uint64_t)__shfl((unsigned long long)s.last, lane & ~(G - 1));
+      group_blend<QMODE>(tc, s, r, s_pend, G, !s.done, hit_out, max_hits);
     }
     // a group's visits and tests are its lanes'
     for (int m = 1; m < G; m <<= 1) {

@@ -263,6 +263,7 @@ struct MisPathSource {
     return true;
   }
 
+  static constexpr bool kHits = false;
   __device__ __forceinline__ void operator()(const Record&, const Attr&, double, double, double, double, D3, D3) const {}
 
   // Queue a contribution; the lanes that call this together claim their

@@ -67,6 +67,7 @@ struct PathSource {
     return true;
   }
 
+  static constexpr bool kHits = false;
   __device__ __forceinline__ void operator()(const Record&, const Attr&, double, double, double, double, D3, D3) const {}
 
   __device__ __forceinline__ bool finish(const Seg<false>& s, D3& O, D3& W) {

@@ -29,6 +29,7 @@ struct CameraSource {
   float* rgb;
   int64_t item;
 
+  static constexpr bool kHits = false;
   __device__ __forceinline__ void operator()(const Record&, const Attr&, double, double, double, double, D3, D3) const {}
 
   __device__ __forceinline__ bool start(int64_t wid, TraceCtx&, D3& O, D3& W) {
@@ -120,6 +121,7 @@ struct SecondarySource {
     return true;
   }
 
+  static constexpr bool kHits = false;
   __device__ __forceinline__ void operator()(const Record&, const Attr&, double, double, double, double, D3, D3) const {}
 
   __device__ __forceinline__ bool finish(const Seg<true>& sg, D3&, D3&) {

@@ -24,9 +24,10 @@
 //       needs no tracing (the source then writes its own result);
 //   bool finish(const Seg<DACC>& s, D3& O, D3& W)
 //       the lane's segment has ended; true with the next segment's ray;
+//   static constexpr bool kHits: whether it has
 //   void operator()(const Record&, const Attr&, double t, double alpha,
 //                   double w, double T_before, D3 O, D3 W)
-//       called for every blended hit, in blending order (may be empty).
+//       called for every blended hit, in blending order.
 #pragma once
 
 #include "eag_device.h"
@@ -40,6 +41,11 @@ namespace eag {
 // tracing 139.7 to 140.1 ms (28 lanes or five leaves cost it 1%).
 constexpr int RUN_BLEND_BATCH = 24;
 constexpr int RUN_LEAVES = 2;
+// Lanes with an ended segment that the source finishes together: its work (a
+// bounce, a light sample) runs for few lanes otherwise. 1, 8, 16 and 24 lanes:
+// emitter sampling 24.5, 24.1, 24.0 and 24.3 ms, path tracing 140.4, 140.0, 142.3
+// and 146.7.
+constexpr int FINISH_BATCH = 8;
 // Runner kernels launch this many TRACE_BLOCK-thread blocks per CU: their
 // LDS (stack and postponed leaves, 56 KB per block) admits two per CU, and
 // the per-lane hit list is sized for exactly this grid.
@@ -78,7 +84,7 @@ __device__ __forceinline__ void bind_lds_stack(Src&, int*, long) {}
 template <int QMODE, bool DACC, bool STATS, class Src>
 __device__ __forceinline__ void run_segments(const TraceCtx& tc, Src& src, unsigned long long* work_counter,
                                              int64_t n_work, uint64_t* hitlist, unsigned long long* counters) {
-  enum { ST_IDLE = 0, ST_ROUND = 1, ST_TRAV = 2, ST_BLEND = 3 };
+  enum { ST_IDLE = 0, ST_ROUND = 1, ST_TRAV = 2, ST_BLEND = 3, ST_DONE = 4 };
   __shared__ int s_stack[STACK_LDS * TRACE_BLOCK];
   __shared__ int s_pend[PEND * TRACE_BLOCK];
   int s_ovf[STACK_OVF];
@@ -99,6 +105,7 @@ __device__ __forceinline__ void run_segments(const TraceCtx& tc, Src& src, unsig
   const int lanes = lanes_per_wave(n_work, (int64_t)gridDim.x * (TRACE_BLOCK / 64));
   const int blend_batch = (RUN_BLEND_BATCH * lanes + 63) / 64;
   const int leaf_min = (LEAF_MIN_LANES * lanes + 63) / 64;
+  const int finish_batch = (FINISH_BATCH * lanes + 63) / 64;
 
   int stage = ST_IDLE;
   SegStats<DACC, STATS, true> s;
@@ -159,25 +166,29 @@ __device__ __forceinline__ void run_segments(const TraceCtx& tc, Src& src, unsig
       if (__ballot(stage == ST_TRAV) == 0 || __popcll(__ballot(stage == ST_BLEND)) >= blend_batch) break;
     }
 
-    // ---- blend, and finish ended segments
-    if (stage != ST_BLEND) continue;
-    blend_round<QMODE>(tcl, s, r, src, nullptr, 0);
-    if (!s.done) {
-      stage = ST_ROUND;
-      continue;
+    // ---- blend
+    if (stage == ST_BLEND) {
+      blend_round<QMODE>(tcl, s, r, src, nullptr, 0);
+      stage = s.done ? ST_DONE : ST_ROUND;
     }
-    if constexpr (STATS) {
-      rs.rounds += s.rounds;
-      rs.tests += s.tests;
-      rs.hits += s.nhits;
-      rs.visits += s.visits;
-    }
-    if (src.finish(s, O, W)) {
-      seg_begin(s, O, W);
-      stage = ST_ROUND;
-      if constexpr (STATS) ++rs.segments;
-    } else {
-      stage = ST_IDLE;
+
+    // ---- finish ended segments, once enough lanes have one (or nothing else is left to do)
+    if (__popcll(__ballot(stage == ST_DONE)) >= finish_batch || __ballot(stage == ST_ROUND || stage == ST_TRAV) == 0) {
+      if (stage == ST_DONE) {
+        if constexpr (STATS) {
+          rs.rounds += s.rounds;
+          rs.tests += s.tests;
+          rs.hits += s.nhits;
+          rs.visits += s.visits;
+        }
+        if (src.finish(s, O, W)) {
+          seg_begin(s, O, W);
+          stage = ST_ROUND;
+          if constexpr (STATS) ++rs.segments;
+        } else {
+          stage = ST_IDLE;
+        }
+      }
     }
   }
   if constexpr (STATS) rs.flush(counters);
@@ -260,15 +271,20 @@ __device__ __forceinline__ void run_groups(const TraceCtx& tc, Src& src, unsigne
       if (begin) seg_begin(s, o, w);
     }
     fresh = false;
-    s.last = (uint64_t)__shfl((unsigned long long)s.last, lead);
     round_begin(tcl, s, r, st, pend);
     const bool fits = group_traverse(tcl, s, r, s_stack, s_pend, G, on);
+    if (first && on && !fits) {
+      round_begin(tcl, s, r, st, pend);
+      traverse_round(tcl, s, r, st, pend, 1);
+    }
+    if constexpr (Src::kHits) {
+      // the source takes every hit: one lane blends
+      if (first && on) blend_round<QMODE>(tcl, s, r, src, nullptr, 0);
+      s.last = (uint64_t)__shfl((unsigned long long)s.last, lead);
+    } else {
+      group_blend<QMODE>(tcl, s, r, s_pend, G, on, nullptr, 0);
+    }
     if (first && on) {
-      if (!fits) {
-        round_begin(tcl, s, r, st, pend);
-        traverse_round(tcl, s, r, st, pend, 1);
-      }
-      blend_round<QMODE>(tcl, s, r, src, nullptr, 0);
       if constexpr (STATS) {
         rs.rounds += s.rounds;
         rs.hits += s.nhits;

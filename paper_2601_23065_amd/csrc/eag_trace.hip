@@ -46,7 +46,7 @@ Attr* noalloc_scratch_current_device() {
 namespace {
 
 // `lanes` rays per wave, each by a group of G lanes.
-__global__ void __launch_bounds__(256) k_trace_rays(TraceCtx tc, int64_t n_rays, const double* o, const double* d,
+__global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_eu(2))) k_trace_rays(TraceCtx tc, int64_t n_rays, const double* o, const double* d,
                                                     float* out, int32_t* hit_idx, int32_t* hit_count,
                                                     int32_t max_hits, int32_t* stats, int lanes, int G) {
   const int g = (int)(threadIdx.x & 63) / G;
