@@ -244,12 +244,22 @@ struct SecondaryAdjSource {
   static constexpr bool kHits = true;
   __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, D3 O,
                                              D3 W) {
+    const double c = weight(r, at, t, W);
+    prefix += w * c;
+    adjoint(r, at, t, alpha, w, Tb, c, prefix, O, W);
+  }
+
+  // The hit's term of the blended quantity that is reversed.
+  __device__ __forceinline__ double weight(const Record& r, const Attr& at, double t, D3 W) const {
+    return gR1.x * at.r.x + gR1.y * at.r.y + gR1.z * at.r.z;
+  }
+
+  // Reverse a hit, given that term and the prefix of the sum that includes it.
+  __device__ __forceinline__ void adjoint(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, double c,
+                                          double upto, D3 O, D3 W) {
     const uint32_t idx = rec_index(r);
     const Geo ge = surfel_geo(r);
-    const float4 rr = at.r;
-    const double c = gR1.x * rr.x + gR1.y * rr.y + gR1.z * rr.z;
-    prefix += w * c;
-    const double g_alpha = Tb * c - (G - prefix) / (1.0 - alpha);
+    const double g_alpha = Tb * c - (G - upto) / (1.0 - alpha);
     double v[GRAD_ROWS];
     double cv[10];
     chain_values(ge, O, W, t, g_alpha, 0.0, d3(0.0, 0.0, 0.0), ray_grad, gO, gW, cv);
@@ -261,6 +271,20 @@ struct SecondaryAdjSource {
     v[15] = w * gR1.z;
     emit_record(gr, gp, wcur, last, idx, v);
   }
+
+  // The ray gradients of a group's lanes into its first lane's (all lanes call it; done: the group's segment has ended).
+  __device__ __forceinline__ void gather(int G, bool done) {
+    D3 o = gO, d = gW;
+    for (int m = 1; m < G; m <<= 1) {
+      o = o + d3(__shfl_xor(o.x, m), __shfl_xor(o.y, m), __shfl_xor(o.z, m));
+      d = d + d3(__shfl_xor(d.x, m), __shfl_xor(d.y, m), __shfl_xor(d.z, m));
+    }
+    gO = done ? o : gO;
+    gW = done ? d : gW;
+  }
+
+  // End of the item in the other lanes of a group.
+  __device__ __forceinline__ void leave() { store_rank(gr, last); }
 
   __device__ __forceinline__ bool finish(const Seg<true>&, D3&, D3&) {
     store_rank(gr, last);
@@ -395,14 +419,27 @@ struct CameraAdjSource {
   static constexpr bool kHits = true;
   __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, D3 O,
                                              D3 W) {
+    const double c = weight(r, at, t, W);
+    prefix += w * c;
+    adjoint(r, at, t, alpha, w, Tb, c, prefix, O, W);
+  }
+
+  // The hit's term of the blended quantity that is reversed.
+  __device__ __forceinline__ double weight(const Record& r, const Attr& at, double t, D3 W) const {
+    const D3 n = surfel_geo(r).n;
+    const double sgn = dot(W, n) > 0.0 ? -1.0 : 1.0;   // n' = sgn n faces the origin
+    const D3 rho = d3(at.rho_e.x, at.rho_e.y, at.rho_e.z), rad = d3(at.r.x, at.r.y, at.r.z);
+    return sgn * dot(gN, n) + gD * t + dot(gR, rad) + dot(gP, rho);
+  }
+
+  // Reverse a hit, given that term and the prefix of the sum that includes it.
+  __device__ __forceinline__ void adjoint(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, double c,
+                                          double upto, D3 O, D3 W) {
     const uint32_t idx = rec_index(r);
     const Geo ge = surfel_geo(r);
     const D3 nn = ge.n;
     const double sgn = dot(W, nn) > 0.0 ? -1.0 : 1.0;   // n' = sgn n faces the origin
-    const D3 rho = d3(at.rho_e.x, at.rho_e.y, at.rho_e.z), rad = d3(at.r.x, at.r.y, at.r.z);
-    const double c = sgn * dot(gN, nn) + gD * t + dot(gR, rad) + dot(gP, rho);
-    prefix += w * c;
-    const double g_alpha = Tb * c - (G - prefix - gA * Tm) / (1.0 - alpha);
+    const double g_alpha = Tb * c - (G - upto - gA * Tm) / (1.0 - alpha);
     D3 dummyO = d3(0.0, 0.0, 0.0), dummyW = d3(0.0, 0.0, 0.0);
     double v[GRAD_ROWS];
     double cv[10];
@@ -417,6 +454,11 @@ struct CameraAdjSource {
     v[15] = has_R ? w * gR.z : 0.0;
     emit_record(gr, gp, wcur, last, idx, v);
   }
+
+  __device__ __forceinline__ void gather(int, bool) {}
+
+  // End of the item in the other lanes of a group.
+  __device__ __forceinline__ void leave() { store_rank(gr, last); }
 
   __device__ __forceinline__ bool finish(const Seg<true>&, D3&, D3&) {
     store_rank(gr, last);
@@ -497,13 +539,25 @@ struct Stage0AdjSource {
   static constexpr bool kHits = true;
   __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, D3 O,
                                              D3 W) {
+    const double c = weight(r, at, t, W);
+    prefix += w * c;
+    adjoint(r, at, t, alpha, w, Tb, c, prefix, O, W);
+  }
+
+  // The hit's term of the blended quantity that is reversed.
+  __device__ __forceinline__ double weight(const Record& r, const Attr& at, double t, D3 W) const {
+    const D3 n = surfel_geo(r).n;
+    const double sgn = dot(W, n) > 0.0 ? -1.0 : 1.0;   // n' = sgn n faces the origin
+    return sgn * dot(gN, n) + gD * t + gR.x * at.r.x + gR.y * at.r.y + gR.z * at.r.z + gE * at.rho_e.w;
+  }
+
+  // Reverse a hit, given that term and the prefix of the sum that includes it.
+  __device__ __forceinline__ void adjoint(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, double c,
+                                          double upto, D3 O, D3 W) {
     const uint32_t idx = rec_index(r);
     const Geo ge = surfel_geo(r);
     const double sgn = dot(W, ge.n) > 0.0 ? -1.0 : 1.0;   // n' = sgn n faces the origin
-    const double c = sgn * dot(gN, ge.n) + gD * t + gR.x * at.r.x + gR.y * at.r.y + gR.z * at.r.z +
-                     gE * at.rho_e.w;
-    prefix += w * c;
-    const double g_alpha = Tb * c - (G - prefix - gA * Tm) / (1.0 - alpha);
+    const double g_alpha = Tb * c - (G - upto - gA * Tm) / (1.0 - alpha);
     D3 dummyO = d3(0.0, 0.0, 0.0), dummyW = d3(0.0, 0.0, 0.0);
     double v[GRAD_ROWS];
     double cv[10];
@@ -517,6 +571,11 @@ struct Stage0AdjSource {
     v[15] = w * gR.z;
     emit_record(gr, gp, wcur, last, idx, v);
   }
+
+  __device__ __forceinline__ void gather(int, bool) {}
+
+  // End of the item in the other lanes of a group.
+  __device__ __forceinline__ void leave() { store_rank(gr, last); }
 
   __device__ __forceinline__ bool finish(const Seg<true>&, D3&, D3&) {
     store_rank(gr, last);

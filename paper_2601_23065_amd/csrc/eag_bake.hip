@@ -110,7 +110,15 @@ struct RadianceAdjSource {
   }
 
   static constexpr bool kHits = true;
-  __device__ __forceinline__ void operator()(const Record& r, const Attr&, double, double, double w, double, D3, D3) {
+  double prefix = 0.0;   // (of nothing)
+  __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, D3 O,
+                                             D3 W) {
+    adjoint(r, at, t, alpha, w, Tb, 0.0, 0.0, O, W);
+  }
+  __device__ __forceinline__ double weight(const Record&, const Attr&, double, D3) const { return 0.0; }
+  __device__ __forceinline__ void gather(int, bool) {}
+  __device__ __forceinline__ void leave() {}
+  __device__ __forceinline__ void adjoint(const Record& r, const Attr&, double, double, double w, double, double, double, D3, D3) {
     const uint32_t idx = rec_index(r);
     const double v[3] = {w * (double)dl.x, w * (double)dl.y, w * (double)dl.z};
     add_rows(adds, gr, RAD_STRIDE, idx, v);

@@ -1116,11 +1116,12 @@ __device__ __forceinline__ void blend_round(const TraceCtx& tc, S& s, Round& r, 
 // round is in the first lane of each group that is `on`): each lane evaluates
 // one of the round's hits, G at a time, and all lanes of the group then blend
 // them in order, so that every lane carries the segment. The same sums in the
-// same order as blend_round's. queue: the block's array of postponed leaves,
-// empty now.
-template <int QMODE, class S>
-__device__ __forceinline__ void group_blend(const TraceCtx& tc, S& s, const Round& r, int* queue, int G, bool on,
-                                            int32_t* hit_out, int max_hits) {
+// same order as blend_round's. A source that takes the hits carries its item in
+// every lane; its running sum goes on in order, and then each lane hands it its
+// own hit. queue: the block's array of postponed leaves, empty now.
+template <int QMODE, class S, class HitFn>
+__device__ __forceinline__ void group_blend(const TraceCtx& tc, S& s, const Round& r, HitFn& src, int* queue, int G,
+                                            bool on, int32_t* hit_out, int max_hits) {
   static_assert(!S::kList, "group rounds keep no hit list");
   const int lane = (int)(threadIdx.x & 63), lig = lane & (G - 1), gb = lane & ~(G - 1);
   const int sh = __ffs(G) - 1, col = (int)(threadIdx.x & ~63u) + gb;
@@ -1139,7 +1140,11 @@ __device__ __forceinline__ void group_blend(const TraceCtx& tc, S& s, const Roun
     const uint32_t idx = mine < cnt ? (uint32_t)vq[at(mine)] : 0u;
     const uint32_t pos = (uint32_t)*elem(tc.inv, idx);
     const Attr a0 = *elem(tc.attrs, pos);
-    const HitEval h0 = eval_hit(load_record(tc.recs, pos), s.O, s.W);
+    const Record rec = load_record(tc.recs, pos);
+    const HitEval h0 = eval_hit(rec, s.O, s.W);
+    double c0 = 0.0, my_T = 0.0, my_prefix = 0.0;
+    bool taken = false;
+    if constexpr (HitFn::kHits) c0 = src.weight(rec, a0, h0.t, s.W);
     for (int j = 0; j < G && c + j < KBUF; ++j) {
       if (!__any(c + j < cnt && !s.done)) break;
       const int from = gb + j;
@@ -1157,13 +1162,26 @@ __device__ __forceinline__ void group_blend(const TraceCtx& tc, S& s, const Roun
                             __shfl(a0.rho_e.w, from));
       }
       const uint32_t hit = hit_out ? (uint32_t)__shfl((int)idx, from) : 0u;
+      double cj = 0.0;
+      if constexpr (HitFn::kHits) cj = __shfl(c0, from);
       if (c + j < cnt && !s.done) {
         if constexpr (S::kStats) {
           if (hit_out && lig == 0 && s.nhits < max_hits) hit_out[s.nhits] = (int32_t)hit;
           ++s.nhits;
         }
+        if constexpr (HitFn::kHits) {
+          src.prefix += (s.T * h.a) * cj;
+          if (lane == from) {
+            taken = true;
+            my_T = s.T;
+            my_prefix = src.prefix;
+          }
+        }
         blend_hit<QMODE>(tc, s, h, rho_e, rr);
       }
+    }
+    if constexpr (HitFn::kHits) {
+      if (taken) src.adjoint(rec, a0, h0.t, h0.a, my_T * h0.a, my_T, c0, my_prefix, s.O, s.W);
     }
   }
   if (cnt < KBUF) s.done = true;
@@ -1207,7 +1225,7 @@ __device__ __forceinline__ SegOut trace_segment(const TraceCtx& tc, D3 O, D3 W, 
         round_begin(tc, s, r, st, pend);
         traverse_round(tc, s, r, st, pend, 1);
       }
-      group_blend<QMODE>(tc, s, r, s_pend, G, !s.done, hit_out, max_hits);
+      group_blend<QMODE>(tc, s, r, nh, s_pend, G, !s.done, hit_out, max_hits);
     }
     // a group's visits and tests are its lanes'
     for (int m = 1; m < G; m <<= 1) {

@@ -246,8 +246,14 @@ __device__ __forceinline__ void run_groups(const TraceCtx& tc, Src& src, unsigne
       if (lane == leader) base = atomicAdd(work_counter, (unsigned long long)__popcll(m));
       base = __shfl(base, leader);
       exhausted = base + (unsigned long long)__popcll(m) >= (unsigned long long)n_work;
-      if (need) {
-        const int64_t wid = (int64_t)base + __popcll(m & lt_mask);
+      int64_t wid = (int64_t)base + __popcll(m & lt_mask);
+      bool take = need;
+      if constexpr (Src::kHits) {
+        // a source that takes the hits is carried by every lane of the group
+        wid = __shfl(wid, lead);
+        take = __shfl(need ? 1 : 0, lead) != 0;
+      }
+      if (take) {
         if (wid < n_work && src.start(wid, tcl, O, W)) {
           idle = false;
           fresh = true;
@@ -277,12 +283,9 @@ __device__ __forceinline__ void run_groups(const TraceCtx& tc, Src& src, unsigne
       round_begin(tcl, s, r, st, pend);
       traverse_round(tcl, s, r, st, pend, 1);
     }
+    group_blend<QMODE>(tcl, s, r, src, s_pend, G, on, nullptr, 0);
     if constexpr (Src::kHits) {
-      // the source takes every hit: one lane blends
-      if (first && on) blend_round<QMODE>(tcl, s, r, src, nullptr, 0);
-      s.last = (uint64_t)__shfl((unsigned long long)s.last, lead);
-    } else {
-      group_blend<QMODE>(tcl, s, r, s_pend, G, on, nullptr, 0);
+      if (__any(on && s.done)) src.gather(G, on && s.done);
     }
     if (first && on) {
       if constexpr (STATS) {
@@ -293,6 +296,13 @@ __device__ __forceinline__ void run_groups(const TraceCtx& tc, Src& src, unsigne
         fresh = src.finish(s, O, W);
         idle = !fresh;
         if constexpr (STATS) rs.segments += fresh ? 1 : 0;
+      }
+    }
+    // (an item of a source that takes the hits is one segment)
+    if constexpr (Src::kHits) {
+      if (!first && on && s.done) {
+        src.leave();
+        idle = true;
       }
     }
     if constexpr (STATS) {
