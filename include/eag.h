@@ -161,7 +161,7 @@ typedef struct {
                              /*   child >= 0: internal node, child < 0: leaf at sorted position ~child */
   const void* records;       /* device: n geometry records, 48 B each, in sorted (Morton) order */
   const int32_t* perm;       /* device [n]: sorted position -> surfel index */
-  const void* nodes4;        /* device: the 4-wide tree traversed by the tracer, 128 B per node: */
+  const void* nodes4;        /* device: the 4-wide tree, 128 B per node (the tracer reads a rounded-out copy): */
                              /*   float box[4][6] (lo.xyz hi.xyz); int32 ref[4] (>= 0 node, < 0 leaf ~pos, */
                              /*   0x7fffffff empty); int32 src[4] (binary-tree origin of each child) */
   int32_t n_nodes4;          /* nodes in nodes4; node 0 is the root */

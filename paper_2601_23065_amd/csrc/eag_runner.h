@@ -11,9 +11,10 @@
 //     atomic, and each idle lane takes base + its rank among them);
 //   * lanes whose round needs the BVH traverse together; the wave leaves the
 //     traversal loop once RUN_BLEND_BATCH lanes wait to blend (or no lane
-//     traverses), blends those lanes' rounds, finishes their segments, starts
-//     their next rounds or segments, and resumes: traversal state stays in
-//     registers and LDS.
+//     traverses), blends those lanes' rounds, finishes the segments that have
+//     ended (once FINISH_BATCH of them have, or nothing else is left to do),
+//     starts the next rounds or segments, and resumes: traversal state stays
+//     in registers and LDS.
 // A wave exits when the work counter is exhausted and all its lanes are
 // idle.
 //

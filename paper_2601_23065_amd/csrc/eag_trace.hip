@@ -1,5 +1,5 @@
-// Tracing of caller-supplied rays (Sec. 3.1, Eq. 1-3): one lane per ray (of
-// every wave, as many lanes as it takes to use the whole chip),
+// Tracing of caller-supplied rays (Sec. 3.1, Eq. 1-3): one lane per ray, or
+// a group of lanes per ray where there are too few rays for the whole chip,
 // multi-round k-buffer traversal and front-to-back blending, output of the
 // normalised traced quantities and, optionally, the blended hit list.
 #include "eag_device.h"
