@@ -135,8 +135,13 @@ void launch_zero_u64(unsigned long long* p, int n, hipStream_t st) {
   hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, st, p, n);
 }
 
-void launch_path_trace(const TraceCtx& tc, const PtLaunch& L, unsigned long long* work_counter,
+void launch_path_trace(const TraceCtx& ctx, const PtLaunch& L, unsigned long long* work_counter,
                        unsigned long long* counters, uint64_t* hitlist, hipStream_t st) {
+  // Every lane of a group reads attributes, and only its first one runs the
+  // source that sets them for its slot: a launch by groups has one slot, whose
+  // attributes they are (the server's context has none of its own).
+  TraceCtx tc = ctx;
+  tc.attrs = L.s[0].attrs;
   const unsigned blocks = (unsigned)(runner_lanes() / TRACE_BLOCK);
   hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, st, work_counter, 1);
   // the statistics cost registers: kernels of their own without them
