@@ -242,11 +242,11 @@ struct SecondaryAdjSource {
   }
 
   static constexpr bool kHits = true;
-  __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, D3 O,
+  __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double om, double w, double Tb, D3 O,
                                              D3 W) {
     const double c = weight(r, at, t, W);
     prefix += w * c;
-    adjoint(r, at, t, alpha, w, Tb, c, prefix, O, W);
+    adjoint(r, at, t, om, w, Tb, c, prefix, O, W);
   }
 
   // The hit's term of the blended quantity that is reversed.
@@ -255,11 +255,11 @@ struct SecondaryAdjSource {
   }
 
   // Reverse a hit, given that term and the prefix of the sum that includes it.
-  __device__ __forceinline__ void adjoint(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, double c,
+  __device__ __forceinline__ void adjoint(const Record& r, const Attr& at, double t, double om, double w, double Tb, double c,
                                           double upto, D3 O, D3 W) {
     const uint32_t idx = rec_index(r);
     const Geo ge = surfel_geo(r);
-    const double g_alpha = Tb * c - (G - upto) / (1.0 - alpha);
+    const double g_alpha = Tb * c - (G - upto) / om;
     double v[GRAD_ROWS];
     double cv[10];
     chain_values(ge, O, W, t, g_alpha, 0.0, d3(0.0, 0.0, 0.0), ray_grad, gO, gW, cv);
@@ -417,11 +417,11 @@ struct CameraAdjSource {
   }
 
   static constexpr bool kHits = true;
-  __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, D3 O,
+  __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double om, double w, double Tb, D3 O,
                                              D3 W) {
     const double c = weight(r, at, t, W);
     prefix += w * c;
-    adjoint(r, at, t, alpha, w, Tb, c, prefix, O, W);
+    adjoint(r, at, t, om, w, Tb, c, prefix, O, W);
   }
 
   // The hit's term of the blended quantity that is reversed.
@@ -433,13 +433,13 @@ struct CameraAdjSource {
   }
 
   // Reverse a hit, given that term and the prefix of the sum that includes it.
-  __device__ __forceinline__ void adjoint(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, double c,
+  __device__ __forceinline__ void adjoint(const Record& r, const Attr& at, double t, double om, double w, double Tb, double c,
                                           double upto, D3 O, D3 W) {
     const uint32_t idx = rec_index(r);
     const Geo ge = surfel_geo(r);
     const D3 nn = ge.n;
     const double sgn = dot(W, nn) > 0.0 ? -1.0 : 1.0;   // n' = sgn n faces the origin
-    const double g_alpha = Tb * c - (G - upto - gA * Tm) / (1.0 - alpha);
+    const double g_alpha = Tb * c - (G - upto - gA * Tm) / om;
     D3 dummyO = d3(0.0, 0.0, 0.0), dummyW = d3(0.0, 0.0, 0.0);
     double v[GRAD_ROWS];
     double cv[10];
@@ -537,11 +537,11 @@ struct Stage0AdjSource {
   }
 
   static constexpr bool kHits = true;
-  __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, D3 O,
+  __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double om, double w, double Tb, D3 O,
                                              D3 W) {
     const double c = weight(r, at, t, W);
     prefix += w * c;
-    adjoint(r, at, t, alpha, w, Tb, c, prefix, O, W);
+    adjoint(r, at, t, om, w, Tb, c, prefix, O, W);
   }
 
   // The hit's term of the blended quantity that is reversed.
@@ -552,12 +552,12 @@ struct Stage0AdjSource {
   }
 
   // Reverse a hit, given that term and the prefix of the sum that includes it.
-  __device__ __forceinline__ void adjoint(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, double c,
+  __device__ __forceinline__ void adjoint(const Record& r, const Attr& at, double t, double om, double w, double Tb, double c,
                                           double upto, D3 O, D3 W) {
     const uint32_t idx = rec_index(r);
     const Geo ge = surfel_geo(r);
     const double sgn = dot(W, ge.n) > 0.0 ? -1.0 : 1.0;   // n' = sgn n faces the origin
-    const double g_alpha = Tb * c - (G - upto - gA * Tm) / (1.0 - alpha);
+    const double g_alpha = Tb * c - (G - upto - gA * Tm) / om;
     D3 dummyO = d3(0.0, 0.0, 0.0), dummyW = d3(0.0, 0.0, 0.0);
     double v[GRAD_ROWS];
     double cv[10];

@@ -111,9 +111,9 @@ struct RadianceAdjSource {
 
   static constexpr bool kHits = true;
   double prefix = 0.0;   // (of nothing)
-  __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double alpha, double w, double Tb, D3 O,
+  __device__ __forceinline__ void operator()(const Record& r, const Attr& at, double t, double om, double w, double Tb, D3 O,
                                              D3 W) {
-    adjoint(r, at, t, alpha, w, Tb, 0.0, 0.0, O, W);
+    adjoint(r, at, t, om, w, Tb, 0.0, 0.0, O, W);
   }
   __device__ __forceinline__ double weight(const Record&, const Attr&, double, D3) const { return 0.0; }
   __device__ __forceinline__ void gather(int, bool) {}

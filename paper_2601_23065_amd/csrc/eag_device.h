@@ -979,13 +979,19 @@ __device__ bool group_traverse(const TraceCtx& tc, S& s, Round& r, int* stack, i
 
 // A hit of the ray (O, W) on a surfel, as group_blend passes it round (blend_round
 // has the same expressions in line: through these functions its register
-// allocation cost the path tracer 3%): distance t, alpha,
+// allocation cost the path tracer 3%): distance t, alpha, om = 1 - alpha,
 // the unnormalised normal cn = |q|^2 n with its scale 1 / |q|^2, negated when n
 // points along the ray (n' faces the origin).
+// Where a product could be fused into either of two sums, or into none, the
+// choice is written out, the same in every kernel: left to the compiler it went
+// with the code around it, and a gradient that is zero but for rounding (the
+// opacities of one flat wall) then had other digits in a kernel for groups than
+// in the kernel for lanes. adj: the adjoints round w y where the rest round x z.
 struct HitEval {
-  double t, a, iq2;
+  double t, a, om, iq2;
   D3 cn;
 };
+template <bool adj>
 __device__ __forceinline__ HitEval eval_hit(const Record& rec, D3 O, D3 W) {
   // t, u, v and the unit normal from the columns of the unnormalised
   // quaternion's rotation, |q|^2 (t_u, t_v, n): no square root, and one
@@ -994,18 +1000,20 @@ __device__ __forceinline__ HitEval eval_hit(const Record& rec, D3 O, D3 W) {
   const double su = rec.s_idx.x, sv = rec.s_idx.y;
   const double c = 1.0 / ((qw * qw + qx * qx + qy * qy + qz * qz) * (su * sv));
   const double iq2 = c * (su * sv);
-  const D3 cu = d3(qw * qw + qx * qx - qy * qy - qz * qz, 2.0 * (qx * qy + qw * qz), 2.0 * (qx * qz - qw * qy));
-  const D3 cv = d3(2.0 * (qx * qy - qw * qz), qw * qw - qx * qx + qy * qy - qz * qz, 2.0 * (qy * qz + qw * qx));
-  const D3 cn = d3(2.0 * (qx * qz + qw * qy), 2.0 * (qy * qz - qw * qx), qw * qw - qx * qx - qy * qy + qz * qz);
+  const double wx = qw * qx, wy = qw * qy, wz = qw * qz, xz = qx * qz;
+  const D3 cu = d3(qw * qw + qx * qx - qy * qy - qz * qz, 2.0 * fma(qx, qy, wz), 2.0 * (adj ? fma(qx, qz, -wy) : fma(-qw, qy, xz)));
+  const D3 cv = d3(2.0 * fma(qx, qy, -wz), qw * qw - qx * qx + qy * qy - qz * qz, 2.0 * fma(qy, qz, wx));
+  const D3 cn = d3(2.0 * (adj ? fma(qx, qz, wy) : fma(qw, qy, xz)), 2.0 * fma(qy, qz, -wx), qw * qw - qx * qx - qy * qy + qz * qz);
   const D3 dp = d3((double)rec.p_sigma.x - O.x, (double)rec.p_sigma.y - O.y, (double)rec.p_sigma.z - O.z);
-  const double dn = dot(W, cn);
-  const double t = dot(dp, cn) / dn;
+  const double dn = fma(W.z, cn.z, fma(W.x, cn.x, W.y * cn.y));
+  const double t = fma(dp.z, cn.z, fma(dp.y, cn.y, dp.x * cn.x)) / dn;
   const D3 yv = d3(t * W.x - dp.x, t * W.y - dp.y, t * W.z - dp.z);
   const double uc = dot(yv, cu) * sv, vc = dot(yv, cv) * su;   // u, v times |q|^2 s_u s_v
-  const double a = (double)rec.p_sigma.w * exp(-0.5 * ((uc * uc + vc * vc) * (c * c)));
+  const double g = exp(-0.5 * ((uc * uc + vc * vc) * (c * c)));
   HitEval h;
   h.t = t;
-  h.a = a;
+  h.a = (double)rec.p_sigma.w * g;
+  h.om = fma(-(double)rec.p_sigma.w, g, 1.0);
   h.iq2 = dn > 0.0 ? -iq2 : iq2;
   h.cn = cn;
   return h;
@@ -1032,7 +1040,7 @@ __device__ __forceinline__ void blend_hit(const TraceCtx& tc, S& s, const HitEva
   s.R0 += wf * rr.x;
   s.R1 += wf * rr.y;
   s.R2 += wf * rr.z;
-  s.T *= (1.0 - h.a);
+  s.T *= h.om;
   if (s.T < tc.T_min) s.done = true;
 }
 
@@ -1042,7 +1050,7 @@ __device__ __forceinline__ void blend_hit(const TraceCtx& tc, S& s, const HitEva
 // positions of all the round's hits are fetched at once (their latency is
 // paid once a round), and shifted down one entry per hit, which keeps the
 // indexing static.
-// on_hit(record, attributes, t, alpha, w, T_before, O, W) is called for every
+// on_hit(record, attributes, t, 1 - alpha, w, T_before, O, W) is called for every
 // blended hit (its loads would stand between the next hit's and this one); if
 // hit_out is non-null, up to max_hits blended surfel indices are written.
 template <int QMODE, class S, class HitFn>
@@ -1072,15 +1080,18 @@ __device__ __forceinline__ void blend_round(const TraceCtx& tc, S& s, Round& r, 
     const double su = rec.s_idx.x, sv = rec.s_idx.y;
     const double c = 1.0 / ((qw * qw + qx * qx + qy * qy + qz * qz) * (su * sv));
     const double iq2 = c * (su * sv);
-    const D3 cu = d3(qw * qw + qx * qx - qy * qy - qz * qz, 2.0 * (qx * qy + qw * qz), 2.0 * (qx * qz - qw * qy));
-    const D3 cv = d3(2.0 * (qx * qy - qw * qz), qw * qw - qx * qx + qy * qy - qz * qz, 2.0 * (qy * qz + qw * qx));
-    const D3 cn = d3(2.0 * (qx * qz + qw * qy), 2.0 * (qy * qz - qw * qx), qw * qw - qx * qx - qy * qy + qz * qz);
+    constexpr bool adj = HitFn::kHits;
+    const double wx = qw * qx, wy = qw * qy, wz = qw * qz, xz = qx * qz;
+    const D3 cu = d3(qw * qw + qx * qx - qy * qy - qz * qz, 2.0 * fma(qx, qy, wz), 2.0 * (adj ? fma(qx, qz, -wy) : fma(-qw, qy, xz)));
+    const D3 cv = d3(2.0 * fma(qx, qy, -wz), qw * qw - qx * qx + qy * qy - qz * qz, 2.0 * fma(qy, qz, wx));
+    const D3 cn = d3(2.0 * (adj ? fma(qx, qz, wy) : fma(qw, qy, xz)), 2.0 * fma(qy, qz, -wx), qw * qw - qx * qx - qy * qy + qz * qz);
     const D3 dp = d3((double)rec.p_sigma.x - s.O.x, (double)rec.p_sigma.y - s.O.y, (double)rec.p_sigma.z - s.O.z);
-    const double dn = dot(s.W, cn);
-    const double t = dot(dp, cn) / dn;
+    const double dn = fma(s.W.z, cn.z, fma(s.W.x, cn.x, s.W.y * cn.y));
+    const double t = fma(dp.z, cn.z, fma(dp.y, cn.y, dp.x * cn.x)) / dn;
     const D3 yv = d3(t * s.W.x - dp.x, t * s.W.y - dp.y, t * s.W.z - dp.z);
     const double uc = dot(yv, cu) * sv, vc = dot(yv, cv) * su;   // u, v times |q|^2 s_u s_v
-    const double a = (double)rec.p_sigma.w * exp(-0.5 * ((uc * uc + vc * vc) * (c * c)));
+    const double g = exp(-0.5 * ((uc * uc + vc * vc) * (c * c)));
+    const double a = (double)rec.p_sigma.w * g, om = fma(-(double)rec.p_sigma.w, g, 1.0);
     const double w = s.T * a;
     const Acc wf = (Acc)w;
     if (QMODE == Q_ALL) {
@@ -1100,9 +1111,9 @@ __device__ __forceinline__ void blend_round(const TraceCtx& tc, S& s, Round& r, 
     if constexpr (S::kStats) {
       if (hit_out && s.nhits < max_hits) hit_out[s.nhits] = (int32_t)rec_index(rec);
     }
-    if constexpr (HitFn::kHits) on_hit(rec, at, t, a, w, s.T, s.O, s.W);
+    if constexpr (HitFn::kHits) on_hit(rec, at, t, om, w, s.T, s.O, s.W);
     if constexpr (S::kStats) ++s.nhits;
-    s.T *= (1.0 - a);
+    s.T *= om;
     if (s.T < tc.T_min) s.done = true;
     __builtin_amdgcn_sched_barrier(0);   // the next record is not waited for before this one is done
     rec = nrec;
@@ -1141,7 +1152,7 @@ __device__ __forceinline__ void group_blend(const TraceCtx& tc, S& s, const Roun
     const uint32_t pos = (uint32_t)*elem(tc.inv, idx);
     const Attr a0 = *elem(tc.attrs, pos);
     const Record rec = load_record(tc.recs, pos);
-    const HitEval h0 = eval_hit(rec, s.O, s.W);
+    const HitEval h0 = eval_hit<HitFn::kHits>(rec, s.O, s.W);
     double c0 = 0.0, my_T = 0.0, my_prefix = 0.0;
     bool taken = false;
     if constexpr (HitFn::kHits) c0 = src.weight(rec, a0, h0.t, s.W);
@@ -1153,6 +1164,7 @@ __device__ __forceinline__ void group_blend(const TraceCtx& tc, S& s, const Roun
       h.t = h.iq2 = 0.0;
       h.cn = d3(0.0, 0.0, 0.0);
       h.a = __shfl(h0.a, from);
+      h.om = __shfl(h0.om, from);
       rr = make_float4(__shfl(a0.r.x, from), __shfl(a0.r.y, from), __shfl(a0.r.z, from), 0.f);
       if (QMODE == Q_ALL) {
         h.t = __shfl(h0.t, from);
@@ -1181,7 +1193,7 @@ __device__ __forceinline__ void group_blend(const TraceCtx& tc, S& s, const Roun
       }
     }
     if constexpr (HitFn::kHits) {
-      if (taken) src.adjoint(rec, a0, h0.t, h0.a, my_T * h0.a, my_T, c0, my_prefix, s.O, s.W);
+      if (taken) src.adjoint(rec, a0, h0.t, h0.om, my_T * h0.a, my_T, c0, my_prefix, s.O, s.W);
     }
   }
   if (cnt < KBUF) s.done = true;

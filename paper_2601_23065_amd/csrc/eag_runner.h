@@ -26,9 +26,9 @@
 //   bool finish(const Seg<DACC>& s, D3& O, D3& W)
 //       the lane's segment has ended; true with the next segment's ray;
 //   static constexpr bool kHits: whether it has
-//   void operator()(const Record&, const Attr&, double t, double alpha,
+//   void operator()(const Record&, const Attr&, double t, double om,
 //                   double w, double T_before, D3 O, D3 W)
-//       called for every blended hit, in blending order.
+//       called for every blended hit, in blending order (om = 1 - alpha).
 #pragma once
 
 #include "eag_device.h"

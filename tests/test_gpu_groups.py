@@ -116,3 +116,37 @@ def test_single_bounce_small_and_large_batches(cams, size):
     g1 = api.zero_bounce_backward(bvh, gs, [cam], p, d)
     gn = api.zero_bounce_backward(bvh, gs, [cam] * cams, p, d.repeat(cams, 1, 1, 1))
     assert ((gn - cams * g1).abs() <= 1e-5 * cams * g1.abs() + 1e-12).all()
+
+
+@pytest.mark.parametrize("w,h", [(200, 190), (31, 17)])
+def test_flat_wall_rounding_does_not_depend_on_the_form(w, h):
+    """On one flat wall of dark surfels the traced normal and distance do not
+    depend on the opacities: their gradient is rounding alone. Groups (one
+    camera) and lanes (eight cameras at the larger size) round alike: the
+    forward state's doubles are equal bit for bit, and eight cameras give eight
+    times one camera's gradient to float32 (the records' double sums, at most
+    10^5 terms, add 1e-11 of their magnitudes)."""
+    from paper_2601_23065_amd import api
+    rng = np.random.default_rng(7)
+    n, f32 = 500, lambda a: np.ascontiguousarray(a, dtype=np.float32)
+    half = rng.uniform(0, np.pi, n)
+    turn = np.array([np.sqrt(0.5), np.sqrt(0.5), 0.0, 0.0])    # +z to -y: no axis of the frame is exact
+    c, s = np.cos(half), np.sin(half)
+    rot = np.stack([turn[0] * c, turn[1] * c, -turn[1] * s, turn[0] * s])
+    pos = np.stack([rng.uniform(-1, 1, n), np.full(n, 2.3), rng.uniform(-1, 1, n)])
+    scene = sg.Scene(f32(pos), f32(rot), f32(rng.uniform(0.05, 0.1, (2, n))), f32(rng.uniform(0.6, 0.99, n)),
+                     f32(np.full((3, n), 0.5)), f32(np.zeros((3, n))), f32(np.zeros(n)),
+                     bounds=(np.full(3, -3.0), np.full(3, 3.0)))
+    gs = gpu_scene(scene)
+    bvh = api.BVH(gs)
+    cam = sg.Camera((0.1, -0.4, 0.2), (0.0, 2.3, 0.0), (0.0, 0.0, 1.0), 40.0, w, h)
+    p = api.Params()
+    _, st1 = api.render_stage0(bvh, gs, [cam], p)
+    _, st8 = api.render_stage0(bvh, gs, [cam] * 8, p)
+    doubles = lambda s: s.view(-1, w * h, 28)[:, :, :24].contiguous().view(torch.int32)
+    assert torch.equal(doubles(st8), doubles(st1).expand(8, -1, -1))
+    d = torch.randn(1, h, w, 8, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    g1 = api.stage0_backward(bvh, gs, [cam], p, d, st1)
+    g8 = api.stage0_backward(bvh, gs, [cam] * 8, p, d.repeat(8, 1, 1, 1), st8)
+    for k in ("pos", "rot", "scale", "opacity"):
+        assert (g8[k].double() - 8 * g1[k].double()).abs().max() <= 1e-6 * 8 * g1[k].abs().max()
