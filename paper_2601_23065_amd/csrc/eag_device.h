@@ -134,9 +134,10 @@ struct CamDev {
 __device__ __forceinline__ D3 camera_dir(const CamDev& c, int px, int py, double ox, double oy) {
   const double dx = 2.0 * ((double)px + ox) / (double)c.width - 1.0;
   const double dy = 1.0 - 2.0 * ((double)py + oy) / (double)c.height;
-  D3 d = d3(dx * c.right[0] + dy * c.up[0] + c.fwd[0], dx * c.right[1] + dy * c.up[1] + c.fwd[1],
-            dx * c.right[2] + dy * c.up[2] + c.fwd[2]);
-  return (1.0 / sqrt(dot(d, d))) * d;
+  // (fused in one way, written out: a path has the same ray in every kernel)
+  const D3 d = d3(fma(dy, c.up[0], dx * c.right[0]) + c.fwd[0], fma(dx, c.right[1], dy * c.up[1]) + c.fwd[1],
+                  fma(dx, c.right[2], dy * c.up[2]) + c.fwd[2]);
+  return (1.0 / sqrt(fma(d.z, d.z, fma(d.x, d.x, d.y * d.y)))) * d;
 }
 
 // Hemisphere frame: Gram-Schmidt of the fixed helper h = (1,2,3)/sqrt(14)
