@@ -694,59 +694,6 @@ __device__ __forceinline__ float half_area(const float* lo, const float* hi) {
   return dx * dy + dy * dz + dz * dx;
 }
 
-// The node as the traversal reads it, from its children's boxes. The planes
-// lie on or outside the boxes; what the traversal rounds off is a few ulp of
-// the coordinates, inside the pad of the leaf boxes. An axis that is not
-// finite (a surfel at infinity or not a number) bounds nothing.
-__device__ __forceinline__ void write_nodeq(NodeQ* out, const float (&lo)[4][3], const float (&hi)[4][3],
-                                            const int (&ref)[4]) {
-  NodeQ nq;
-  float o[3];
-  nq.exps = 0u;
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    float l = __builtin_inff(), h = -__builtin_inff();
-    for (int k = 0; k < 4; ++k) {
-      if (ref[k] == NODE4_EMPTY) continue;
-      l = fminf(l, lo[k][a]);
-      h = fmaxf(h, hi[k][a]);
-    }
-    uint32_t ql = 0u, qh = 0u;
-    const double ext = (double)h - (double)l;
-    if (fabsf(l) < 1e18f && fabsf(h) < 1e18f && ext >= 0.0) {
-      // the smallest step with ext <= 255 steps (at least 2^-126: a normal float)
-      int e = -126;
-      if (ext > 0.0) {
-        e = ilogb(ext) - 8;
-        while (ldexp(255.0, e) < ext) ++e;
-        if (e < -126) e = -126;
-      }
-      const double inv = ldexp(1.0, -e);
-      for (int k = 0; k < 4; ++k) {
-        // an empty slot, and a box that is not a number, span the node
-        double a0 = floor(((double)lo[k][a] - (double)l) * inv), a1 = ceil(((double)hi[k][a] - (double)l) * inv);
-        if (ref[k] == NODE4_EMPTY || !(a0 >= 0.0 && a0 <= 255.0)) a0 = 0.0;
-        if (ref[k] == NODE4_EMPTY || !(a1 >= 0.0 && a1 <= 255.0)) a1 = 255.0;
-        ql |= (uint32_t)a0 << (8 * k);
-        qh |= (uint32_t)a1 << (8 * k);
-      }
-      o[a] = l;
-      nq.exps |= (uint32_t)(e + 127) << (8 * a);
-    } else {
-      o[a] = 0.0f;
-      nq.exps |= 255u << (8 * a);
-    }
-    nq.q[a] = ql;
-    nq.q[3 + a] = qh;
-  }
-  nq.ox = o[0];
-  nq.oy = o[1];
-  nq.oz = o[2];
-  for (int k = 0; k < 4; ++k) nq.ref[k] = ref[k];
-  nq.pad[0] = nq.pad[1] = 0;
-  *out = nq;
-}
-
 // The children of binary node `node` in the 4-wide tree (cnt of them).
 __device__ __forceinline__ int collapse_children(const Node* bin, int node, int (&ref)[4], float (&lo)[4][3],
                                                  float (&hi)[4][3]) {

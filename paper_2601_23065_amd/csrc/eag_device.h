@@ -45,9 +45,10 @@ struct __align__(16) Node4 {
 };
 
 // What a traversal reads of a 4-wide node, 64 B: the children's boxes as
-// 8-bit steps from the node's lower corner, and their references. Along axis
+// 8-bit steps from the node's lower corner (the compression of Ylitie, Karras
+// and Laine, HPG 2017), and their references. Along axis
 // a, child k spans [o + qlo step, o + qhi step] with step a power of two, which
-// holds its box (rounded outward). q.a holds axis a's lower steps, q.(3 + a)
+// holds its box with a margin (write_nodeq). q.a holds axis a's lower steps, q.(3 + a)
 // its upper ones, child k in byte k. exps has the steps' biased exponents in
 // bytes 0 to 2; 255 (step +inf, all q 0) makes every plane of the axis a NaN,
 // which bounds nothing: an axis on which the box is not finite.
@@ -61,6 +62,69 @@ struct __align__(16) NodeQ {
   int32_t pad[2];
 };
 static_assert(sizeof(NodeQ) == 64, "one node per half cache line");
+
+// The node as the traversal reads it, from its children's boxes. node_test finds
+// a plane as q (step / W) + (o - O) / W, so its error in space is, beside a few
+// ulp of the plane itself and of the ray (inside the pad of the leaf box and the
+// widened exit), one ulp of the corner o: a node that reaches far beyond a leaf
+// would lose hits on the leaf's edge. So every plane lies at least 2^-22 of the
+// node's largest coordinate (four units of rounding) outside its box. Without it
+// 11, 800 and 1711 of 4000 rays through the outermost points of a leaf whose
+// edge lies on a step were lost at corners 10^3, 10^4 and 10^5 away; with it
+// none. An axis that is not finite (a surfel at infinity or not a number) bounds
+// nothing.
+__host__ __device__ __forceinline__ void write_nodeq(NodeQ* out, const float (&lo)[4][3], const float (&hi)[4][3],
+                                                     const int (&ref)[4]) {
+  NodeQ nq;
+  float o[3];
+  nq.exps = 0u;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    float l = __builtin_inff(), h = -__builtin_inff();
+    for (int k = 0; k < 4; ++k) {
+      if (ref[k] == NODE4_EMPTY) continue;
+      l = fminf(l, lo[k][a]);
+      h = fmaxf(h, hi[k][a]);
+    }
+    uint32_t ql = 0u, qh = 0u;
+    if (fabsf(l) < 1e18f && fabsf(h) < 1e18f && h >= l) {
+      const double m = 0x1p-22 * (double)fmaxf(fabsf(l), fabsf(h));
+      const double l_m = (double)l - m;
+      o[a] = (float)l_m;
+      if ((double)o[a] > l_m) o[a] = nextafterf(o[a], -__builtin_inff());
+      const double ext = (double)h + m - (double)o[a];
+      // the smallest step with ext <= 255 steps (at least 2^-126: a normal float)
+      int e = -126;
+      if (ext > 0.0) {
+        e = ilogb(ext) - 8;
+        while (ldexp(255.0, e) < ext) ++e;
+        if (e < -126) e = -126;
+      }
+      const double inv = ldexp(1.0, -e);
+      for (int k = 0; k < 4; ++k) {
+        // an empty slot, and a box that is not a number, span the node
+        double a0 = floor(((double)lo[k][a] - m - (double)o[a]) * inv), a1 = ceil(((double)hi[k][a] + m - (double)o[a]) * inv);
+        if (ref[k] == NODE4_EMPTY || !(a0 >= 0.0 && a0 <= 255.0)) a0 = 0.0;
+        if (ref[k] == NODE4_EMPTY || !(a1 >= 0.0 && a1 <= 255.0)) a1 = 255.0;
+        ql |= (uint32_t)a0 << (8 * k);
+        qh |= (uint32_t)a1 << (8 * k);
+      }
+      nq.exps |= (uint32_t)(e + 127) << (8 * a);
+    } else {
+      o[a] = 0.0f;
+      nq.exps |= 255u << (8 * a);
+    }
+    nq.q[a] = ql;
+    nq.q[3 + a] = qh;
+  }
+  nq.ox = o[0];
+  nq.oy = o[1];
+  nq.oz = o[2];
+  for (int k = 0; k < 4; ++k) nq.ref[k] = ref[k];
+  nq.pad[0] = nq.pad[1] = 0;
+  *out = nq;
+}
+
 
 // Geometry record of one surfel in sorted order, 48 B (three float4 loads):
 //   p.x p.y p.z sigma | q.w q.x q.y q.z | s_u s_v index -
@@ -100,7 +164,7 @@ __device__ __forceinline__ float to_unit(uint32_t w) { return (float)(w >> 8) * 
 // small vector helpers
 // ---------------------------------------------------------------------------
 struct V3 { float x, y, z; };
-__device__ __forceinline__ V3 v3(float x, float y, float z) { return V3{x, y, z}; }
+__host__ __device__ __forceinline__ V3 v3(float x, float y, float z) { return V3{x, y, z}; }
 __device__ __forceinline__ V3 operator+(V3 a, V3 b) { return V3{a.x + b.x, a.y + b.y, a.z + b.z}; }
 __device__ __forceinline__ V3 operator-(V3 a, V3 b) { return V3{a.x - b.x, a.y - b.y, a.z - b.z}; }
 __device__ __forceinline__ V3 operator*(float s, V3 a) { return V3{s * a.x, s * a.y, s * a.z}; }
@@ -111,7 +175,7 @@ __device__ __forceinline__ V3 cross(V3 a, V3 b) {
 
 // double-precision vectors for ray geometry
 struct D3 { double x, y, z; };
-__device__ __forceinline__ D3 d3(double x, double y, double z) { return D3{x, y, z}; }
+__host__ __device__ __forceinline__ D3 d3(double x, double y, double z) { return D3{x, y, z}; }
 __device__ __forceinline__ D3 operator+(D3 a, D3 b) { return D3{a.x + b.x, a.y + b.y, a.z + b.z}; }
 __device__ __forceinline__ D3 operator-(D3 a, D3 b) { return D3{a.x - b.x, a.y - b.y, a.z - b.z}; }
 __device__ __forceinline__ D3 operator*(double s, D3 a) { return D3{s * a.x, s * a.y, s * a.z}; }
@@ -164,7 +228,7 @@ __device__ __forceinline__ D3 cosine_dir(D3 n, double u0, double u1) {
 // most). A 32-bit byte offset beside a uniform base is an addressing mode of
 // its own; a 64-bit one costs each lane its address arithmetic and registers.
 template <class T>
-__device__ __forceinline__ const T* elem(const T* base, uint32_t i) {
+__host__ __device__ __forceinline__ const T* elem(const T* base, uint32_t i) {
   return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (uint32_t)(i * (uint32_t)sizeof(T)));
 }
 
@@ -342,7 +406,7 @@ struct SegOut {
 enum { Q_ALL = 0, Q_RADIANCE = 1 };
 
 // byte k as a float (one conversion instruction)
-__device__ __forceinline__ float q_byte(uint32_t w, int k) { return (float)((w >> (8 * k)) & 255u); }
+__host__ __device__ __forceinline__ float q_byte(uint32_t w, int k) { return (float)((w >> (8 * k)) & 255u); }
 
 // Slab test of a box against [tlo, thi]; returns the entry distance or +inf.
 // (for exact boxes: the light pdf's tree; node_visit has its own over NodeQ)
@@ -527,7 +591,7 @@ struct Round {
 };
 
 template <class S>
-__device__ __forceinline__ void seg_begin(S& s, D3 O, D3 W) {
+__host__ __device__ __forceinline__ void seg_begin(S& s, D3 O, D3 W) {
   s.O = O;
   s.W = W;
   const float wx = (float)W.x, wy = (float)W.y, wz = (float)W.z;
@@ -625,16 +689,16 @@ struct NodeKids {
   int ni;
 };
 template <bool DACC>
-__device__ __forceinline__ NodeKids node_test(const TraceCtx& tc, const Seg<DACC>& s, int ref, float tlo0, float t_cut) {
+__host__ __device__ __forceinline__ NodeKids node_test(const TraceCtx& tc, const Seg<DACC>& s, int ref, float tlo0, float t_cut) {
   const float4* np = reinterpret_cast<const float4*>(elem(tc.nodes, (uint32_t)ref));
   const float4 h = np[0];
   const uint4 u0 = *reinterpret_cast<const uint4*>(np + 1), u1 = *reinterpret_cast<const uint4*>(np + 2);
   const uint2 u2 = *reinterpret_cast<const uint2*>(np + 3);
-  const uint32_t ex = __float_as_uint(h.w);
+  const uint32_t ex = __builtin_bit_cast(uint32_t, h.w);
   // plane distances are q a + b per axis
-  const float ax = __uint_as_float((ex & 255u) << 23) * s.iW.x, bx = fmaf(h.x, s.iW.x, -s.OiW.x);
-  const float ay = __uint_as_float((ex & 0xff00u) << 15) * s.iW.y, by = fmaf(h.y, s.iW.y, -s.OiW.y);
-  const float az = __uint_as_float((ex & 0xff0000u) << 7) * s.iW.z, bz = fmaf(h.z, s.iW.z, -s.OiW.z);
+  const float ax = __builtin_bit_cast(float, (ex & 255u) << 23) * s.iW.x, bx = fmaf(h.x, s.iW.x, -s.OiW.x);
+  const float ay = __builtin_bit_cast(float, (ex & 0xff00u) << 15) * s.iW.y, by = fmaf(h.y, s.iW.y, -s.OiW.y);
+  const float az = __builtin_bit_cast(float, (ex & 0xff0000u) << 7) * s.iW.z, bz = fmaf(h.z, s.iW.z, -s.OiW.z);
   const bool gx = s.iW.x < 0.0f, gy = s.iW.y < 0.0f, gz = s.iW.z < 0.0f;
   // the four children's near and far planes
   const uint32_t nx = gx ? u0.w : u0.x, fx = gx ? u0.x : u0.w;
@@ -657,7 +721,7 @@ __device__ __forceinline__ NodeKids node_test(const TraceCtx& tc, const Seg<DACC
     const bool m = kd.c[k] != NODE4_EMPTY && tn <= tf;
     const bool mi = m && kd.c[k] >= 0;
     kd.leaf[k] = m && kd.c[k] < 0;
-    kd.ek[k] = ((uint64_t)__float_as_uint(mi ? tn : __builtin_inff()) << 32) | (uint32_t)kd.c[k];
+    kd.ek[k] = ((uint64_t)__builtin_bit_cast(uint32_t, mi ? tn : __builtin_inff()) << 32) | (uint32_t)kd.c[k];
     kd.ni += mi ? 1 : 0;
   }
   return kd;
