@@ -32,27 +32,6 @@ namespace eag {
 
 namespace {
 
-// Gradient accumulators: double precision in the workspace (component-major,
-// pos[3] rot[4] scale[2] opacity albedo[3] radiance[3] = 16 rows of n), so
-// that sums of many opposing contributions keep their small results; they
-// are added to the caller's float arrays once at the end.
-constexpr int GRAD_ROWS = 16;
-struct GradPtrs {
-  double* pos;
-  double* rot;
-  double* scale;
-  double* opacity;
-  double* albedo;
-  double* radiance;
-  int64_t n;
-};
-
-__device__ __forceinline__ void atomic_add3(double* base, int64_t n, int64_t i, D3 v) {
-  atomicAdd(base + i, v.x);
-  atomicAdd(base + n + i, v.y);
-  atomicAdd(base + 2 * n + i, v.z);
-}
-
 // Chain of one hit's opacity-term gradient g_alpha, distance gradient g_t and
 // normal gradient g_n into the surfel's centre, quaternion, scales and opacity
 // (out, in accumulator-row order: pos 0-2, rot 3-6, scale 7-8, opacity 9), and
@@ -102,81 +81,6 @@ __device__ __forceinline__ void chain_values(const Geo& ge, D3 O, D3 W, double t
   out[7] = gsu;
   out[8] = gsv;
   out[9] = g_sigma;
-}
-
-// Per-hit gradient records of both adjoint passes. Added with atomics, a
-// pass is limited by their rate (13 to 16 per hit). Instead, each hit writes
-// one record of the 16 accumulator rows (64 B: each term rounded to float,
-// their sums taken in double, so a surfel's sum carries an error of about
-// 2^-24 of the sum of its terms' magnitudes at most) to the next slot of its
-// wave's current chunk of REC_CHUNK slots, and counts itself in a per-surfel
-// counter. What the atomic returns is the record's rank among its surfel's; the
-// lane stores it with its next record (or at the item's end), so it never waits
-// for it, and the placement needs no atomics of its own. A wave claims a
-// chunk from a global counter when the lanes of a call do not fit in its
-// current one (one atomic per many hits) and records how much of the chunk it
-// used; its cursor lives in LDS. After the pass, an exclusive scan of the
-// counters and a placement pass group the slots by surfel, and one wave per
-// surfel sums its records. Hits that find the chunks exhausted fall back to
-// atomics, so any capacity is correct.
-constexpr unsigned REC_NO_CHUNK = 0xffffffffu;   // none claimed yet
-constexpr unsigned REC_SPENT = 0xfffffffeu;      // the chunks are exhausted: atomics from here on
-// A lane's last record: its slot (or NO_SLOT) and, once the atomic has returned, its rank.
-constexpr uint32_t NO_SLOT = 0xffffffffu;
-struct LastRec {
-  uint32_t slot = NO_SLOT, rank = 0;
-};
-__device__ __forceinline__ void store_rank(const GradRecs& gr, LastRec& last) {
-  if (last.slot != NO_SLOT) gr.rank[last.slot] = last.rank;
-  last.slot = NO_SLOT;
-}
-__device__ __forceinline__ void emit_record(const GradRecs& gr, const GradPtrs& gp, unsigned* wcur, LastRec& last,
-                                            uint32_t idx, const double (&v)[GRAD_ROWS]) {
-  store_rank(gr, last);
-  // wcur[0]: slots used in the wave's chunk, wcur[1]: the chunk (or none)
-  const uint64_t act = __ballot(1);
-  const int lane = (int)(threadIdx.x & 63);
-  const int leader = __ffsll((unsigned long long)act) - 1;
-  const unsigned k = (unsigned)__popcll(act);
-  unsigned base = 0, chunk = REC_NO_CHUNK;
-  if (lane == leader) {
-    // (volatile: the lanes of a wave take turns as leader)
-    volatile unsigned* const wc = wcur;
-    unsigned cur = wc[0], ch = wc[1];
-    if (ch == REC_NO_CHUNK || (ch != REC_SPENT && cur + k > (unsigned)REC_CHUNK)) {
-      if (ch < (unsigned)gr.n_chunks) gr.chunk_used[ch] = cur;
-      const unsigned long long c = atomicAdd(gr.chunk_next, 1ull);
-      ch = c < (unsigned long long)gr.n_chunks ? (unsigned)c : REC_SPENT;
-      cur = 0;
-    }
-    base = cur;
-    chunk = ch;
-    wc[0] = cur + k;
-    wc[1] = ch;
-  }
-  base = __shfl(base, leader);
-  chunk = __shfl(chunk, leader);
-  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  if (chunk < (unsigned)gr.n_chunks) {
-    const int64_t slot = (int64_t)chunk * REC_CHUNK + base + __popcll(act & below);
-    float4* dst = reinterpret_cast<float4*>(gr.rec + slot * GRAD_ROWS);
-#pragma unroll
-    for (int q = 0; q < GRAD_ROWS / 4; ++q)
-      dst[q] = make_float4((float)v[4 * q], (float)v[4 * q + 1], (float)v[4 * q + 2], (float)v[4 * q + 3]);
-    gr.idx[slot] = idx;
-    last.slot = (uint32_t)slot;   // (at most 2^27 records)
-    last.rank = atomicAdd(gr.cnt + idx, 1u);
-  } else {
-    const int64_t n = gp.n;
-    atomic_add3(gp.pos, n, idx, d3(v[0], v[1], v[2]));
-#pragma unroll
-    for (int k = 0; k < 4; ++k) atomicAdd(gp.rot + k * n + idx, v[3 + k]);
-    atomicAdd(gp.scale + idx, v[7]);
-    atomicAdd(gp.scale + n + idx, v[8]);
-    atomicAdd(gp.opacity + idx, v[9]);
-    atomic_add3(gp.albedo, n, idx, d3(v[10], v[11], v[12]));
-    atomic_add3(gp.radiance, n, idx, d3(v[13], v[14], v[15]));
-  }
 }
 
 // Secondary segments on the persistent segment runner (eag_runner.h): one
@@ -335,10 +239,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
   src.dL = dL;
   __shared__ unsigned s_wcur[2 * (TRACE_BLOCK / 64)];
   const int wv = (int)(threadIdx.x >> 6);
-  if ((threadIdx.x & 63) == 0) {
-    s_wcur[2 * wv] = 0u;
-    s_wcur[2 * wv + 1] = REC_NO_CHUNK;
-  }
+  records_begin(s_wcur + 2 * wv);
   src.gp = gp;
   src.gr = gr;
   src.wcur = s_wcur + 2 * wv;
@@ -348,9 +249,7 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
   src.gR1 = src.gO = src.gW = d3(0.0, 0.0, 0.0);
   src.G = src.prefix = 0.0;
   run_work<GROUPS, Q_RADIANCE, true, false>(tc, src, work, hw * n_cams * sp.spp, hitlist, nullptr);
-  // (the runner's loop ends for the whole wave at once)
-  if ((threadIdx.x & 63) == 0 && s_wcur[2 * wv + 1] < (unsigned)gr.n_chunks)
-    gr.chunk_used[s_wcur[2 * wv + 1]] = s_wcur[2 * wv];
+  records_end(gr, s_wcur + 2 * wv);   // (the runner's loop ends for the whole wave at once)
 }
 
 // Camera segments on the persistent segment runner: one work item per pixel;
@@ -483,18 +382,14 @@ __global__ void __launch_bounds__(TRACE_BLOCK) __attribute__((amdgpu_waves_per_e
   src.gp = gp;
   __shared__ unsigned s_wcur[2 * (TRACE_BLOCK / 64)];
   const int wv = (int)(threadIdx.x >> 6);
-  if ((threadIdx.x & 63) == 0) {
-    s_wcur[2 * wv] = 0u;
-    s_wcur[2 * wv + 1] = REC_NO_CHUNK;
-  }
+  records_begin(s_wcur + 2 * wv);
   src.gr = gr;
   src.wcur = s_wcur + 2 * wv;
   src.gN = src.gR = src.gP = d3(0.0, 0.0, 0.0);
   src.gD = src.gA = src.Tm = src.G = src.prefix = 0.0;
   src.has_R = src.has_P = false;
   run_work<GROUPS, Q_ALL, true, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
-  if ((threadIdx.x & 63) == 0 && s_wcur[2 * wv + 1] < (unsigned)gr.n_chunks)
-    gr.chunk_used[s_wcur[2 * wv + 1]] = s_wcur[2 * wv];
+  records_end(gr, s_wcur + 2 * wv);
 }
 
 // Stage-0 adjoint (Sec. 3.2, Eq. 4): one work item per pixel on the
@@ -596,17 +491,13 @@ k_stage0_bwd(TraceCtx tc, const CamBatch cams, int64_t hw, int32_t n_cams, SbPar
   src.gp = gp;
   __shared__ unsigned s_wcur[2 * (TRACE_BLOCK / 64)];
   const int wv = (int)(threadIdx.x >> 6);
-  if ((threadIdx.x & 63) == 0) {
-    s_wcur[2 * wv] = 0u;
-    s_wcur[2 * wv + 1] = REC_NO_CHUNK;
-  }
+  records_begin(s_wcur + 2 * wv);
   src.gr = gr;
   src.wcur = s_wcur + 2 * wv;
   src.gN = src.gR = d3(0.0, 0.0, 0.0);
   src.gD = src.gA = src.gE = src.Tm = src.G = src.prefix = 0.0;
   run_work<GROUPS, Q_ALL, true, false>(tc, src, work, hw * n_cams, hitlist, nullptr);
-  if ((threadIdx.x & 63) == 0 && s_wcur[2 * wv + 1] < (unsigned)gr.n_chunks)
-    gr.chunk_used[s_wcur[2 * wv + 1]] = s_wcur[2 * wv];
+  records_end(gr, s_wcur + 2 * wv);
 }
 
 // Stage-0 gradients to the caller's arrays: rows 0-9 (pos, rot, scale,
@@ -633,18 +524,7 @@ __global__ void k_zero_records(GradRecs gr, int64_t n) {
   if (i == 0) *gr.chunk_next = 0ull;
 }
 
-// Every used slot of the claimed chunks goes to its rank in its surfel's range
-// [off[i], off[i] + cnt[i]) of order. Blocks stride over the claimed chunks only.
-__global__ void __launch_bounds__(256) k_rec_place(GradRecs gr) {
-  const unsigned long long claimed = *gr.chunk_next;
-  const int64_t nc = claimed < (unsigned long long)gr.n_chunks ? (int64_t)claimed : gr.n_chunks;
-  for (int64_t ch = blockIdx.x; ch < nc; ch += gridDim.x) {
-    const uint32_t used = gr.chunk_used[ch];
-    const int64_t s0 = ch * REC_CHUNK;
-    for (uint32_t j = threadIdx.x; j < used; j += 256)
-      gr.order[gr.off[gr.idx[s0 + j]] + gr.rank[s0 + j]] = (uint32_t)(s0 + j);
-  }
-}
+__global__ void __launch_bounds__(256) k_rec_place(GradRecs gr) { place_records(gr); }
 
 // One wave per surfel: its records, summed lane-strided and then across the
 // wave in a fixed order, are added to the accumulator rows. Across the wave,

@@ -3,6 +3,7 @@
 
 #include "eag_device.h"
 #include "eag_internal.h"
+#include "eag_records.h"
 
 namespace eag {
 
@@ -113,20 +114,6 @@ void launch_path_trace(const TraceCtx& tc, const PtLaunch& L, unsigned long long
 // workspace buffers for the records of a camera batch.
 constexpr int64_t GRAD_RECS_PER_ITEM = 20;          // records per (pixel, sample) item
 constexpr int64_t GRAD_RECS_MAX = int64_t(1) << 27;   // at most 8 GiB of records
-constexpr int64_t REC_CHUNK = 1024;                   // slots a wave claims at a time
-struct GradRecs {
-  float* rec;                   // [n_chunks * REC_CHUNK][16] accumulator rows of each hit
-  uint32_t* idx;                // surfel index of each record
-  uint32_t* rank;               // rank of each record among its surfel's
-  uint32_t* cnt;                // [n] records per surfel
-  uint32_t* off;                // [n] exclusive scan of cnt
-  uint32_t* order;              // slots grouped by surfel
-  uint32_t* chunk_used;         // [n_chunks] slots used in each chunk of REC_CHUNK slots
-  unsigned long long* chunk_next;   // chunks claimed (set by the launch)
-  int64_t n_chunks;             // records: n_chunks * REC_CHUNK
-  void* scan_tmp;
-  size_t scan_bytes;
-};
 int64_t grad_rec_capacity(int64_t n_items);
 size_t grad_rec_scan_bytes(int64_t n);
 
