@@ -193,9 +193,15 @@ constexpr int PLOC_ITERS = 64;     // iterations before the halving fallback
 constexpr int PLOC_GRID = 1024;    // blocks of every clustering launch
 constexpr int PLOC_TILE = 256;
 constexpr int PLOC_TAIL = 1024;    // clusters (and threads) of the single block that runs the last iterations
-// A block left with more clusters than this (pairs that hardly merge, such as
-// coincident surfels) halves them first: quality is lost anyway.
-constexpr int PLOC_TAIL_MAX = 1 << 17;
+// Clusters that the wide iterations leave to that block at most, which takes 4 us
+// for each 1024 of them in each iteration. Surfels whose pairs hardly merge
+// (coincident ones: the nearest of all is the lowest of the window, so two of a
+// run merge at a time) come to the last of the wide iterations nearly all: those
+// then halve them, each as late as the ones after it still reach this number.
+// With ordinary scenes, about a third merge in each iteration and none halves.
+// Left to the block as they were, 1 M coincident surfels took 24.4 ms to build and
+// 6.1 ms to refit, now 1.5 and 0.5.
+constexpr int PLOC_TAIL_MOST = 32768;
 constexpr int PLOC_LEVELS = PLOC_ITERS + 24;   // iterations launched for up to 2^23 surfels, and more
 
 struct PlocState {
@@ -225,6 +231,14 @@ int wide_iters(int64_t n) {
   int t = 0;
   for (double m = (double)n; m > PLOC_TAIL && t < PLOC_ITERS; m *= 0.7) ++t;
   return t;
+}
+
+// Clusters that wide iteration t of `wide` still searches; more are halved
+// instead, so that those after it can bring them down to PLOC_TAIL_MOST by
+// halving (n is at most PLOC_TAIL / 0.7^wide, below PLOC_TAIL_MOST 2^wide).
+int search_limit(int t, int wide) {
+  const int later = wide - 1 - t;
+  return later < 15 ? PLOC_TAIL_MOST << later : INT32_MAX;
 }
 
 // The lower corner's w is the cluster's height (levels of internal nodes).
@@ -304,10 +318,11 @@ __device__ __forceinline__ int2 block_sum2(int2 v, int2* lds) {
 }
 
 // First half of iteration t: the partner of every cluster (nn[i]: its mutual
-// nearest neighbour, or itself), and what each block's part of the order will
+// nearest neighbour, or itself; with more than `limit` clusters, the other one of
+// positions 2k and 2k + 1), and what each block's part of the order will
 // keep and make. A tile's neighbours' neighbours are found here again rather
 // than read from another launch.
-__global__ void __launch_bounds__(PLOC_TILE) k_ploc_pairs(Ploc P, int t) {
+__global__ void __launch_bounds__(PLOC_TILE) k_ploc_pairs(Ploc P, int t, int limit) {
   constexpr int BOXES = PLOC_TILE + 4 * PLOC_R, NEAR = PLOC_TILE + 2 * PLOC_R;
   __shared__ float4 slo[BOXES], shi[BOXES];
   __shared__ int snn[NEAR];
@@ -319,6 +334,15 @@ __global__ void __launch_bounds__(PLOC_TILE) k_ploc_pairs(Ploc P, int t) {
   int lo, hi;
   ploc_chunk(n, lo, hi);
   int2 sum = make_int2(0, 0);
+  if (n > limit) {
+    for (int i = lo + (int)threadIdx.x; i < hi; i += PLOC_TILE) {
+      const int p = (i ^ 1) < n ? (i ^ 1) : i;
+      P.nn[i] = p;
+      sum.x += p >= i ? 1 : 0;
+      sum.y += p > i ? 1 : 0;
+    }
+    lo = hi;
+  }
   for (int base = lo; base < hi; base += PLOC_TILE) {
     for (int k = threadIdx.x; k < BOXES; k += PLOC_TILE) {
       const int g = base - 2 * PLOC_R + k;
@@ -464,9 +488,11 @@ __global__ void __launch_bounds__(PLOC_TAIL) k_ploc_tail(Ploc P, int64_t n_leave
   const int tid = (int)threadIdx.x;
   const PlocState st = P.st[t0 & 1];
   int n = st.n, made = st.made, cur = st.cur, t = t0;
-  // Too many clusters for LDS: the same iteration over memory, in tiles.
+  // Too many clusters for LDS: the same iteration over memory, in tiles. One
+  // that merged few is followed by one that halves.
+  bool few = false;
   while (n > PLOC_TAIL) {
-    const bool halving = t >= PLOC_ITERS || n > PLOC_TAIL_MAX;
+    const bool halving = t >= PLOC_ITERS || few;
     const int32_t* cl = P.cl[cur];
     const float4* cb = P.cb[cur];
     int32_t* ol = P.cl[cur ^ 1];
@@ -516,6 +542,7 @@ __global__ void __launch_bounds__(PLOC_TAIL) k_ploc_tail(Ploc P, int64_t n_leave
       now += tot >> 16;
     }
     __syncthreads();
+    few = kept > n - n / 8;
     n = kept;
     made = now;
     cur ^= 1;
@@ -1004,7 +1031,7 @@ void build_bvh(const eag_surfels* s, eag_bvh* b, void* ws, size_t ws_bytes, hipS
     const unsigned g = std::min<unsigned>(blocks(n, PLOC_TILE), (unsigned)PLOC_GRID);
     const int wide = wide_iters(n);
     for (int t = 0; t < wide; ++t) {
-      hipLaunchKernelGGL(k_ploc_pairs, dim3(g), dim3(PLOC_TILE), 0, st, P, t);
+      hipLaunchKernelGGL(k_ploc_pairs, dim3(g), dim3(PLOC_TILE), 0, st, P, t, search_limit(t, wide));
       hipLaunchKernelGGL(k_ploc_write, dim3(g), dim3(PLOC_TILE), 0, st, P, t, b->levels, n, b->nodes);
     }
     hipLaunchKernelGGL(k_ploc_tail, dim3(1), dim3(PLOC_TAIL), 0, st, P, n, b->nodes, wide, PLOC_ITERS + b->idx_bits,

@@ -82,3 +82,46 @@ def test_a_surfel_that_is_nowhere_hides_no_other(bad):
     b = trace_rays(BVH(g2), g2, Params(), O, D, max_hits=64)
     for x, y in zip(a, b):
         assert torch.equal(x, y)
+
+
+def _half_coincident(n):
+    """A cloud whose every other surfel lies in one place, the same way."""
+    scene = sg.cloud_scene(n, seed=n)
+    scene.pos[:, ::2] = 0.0
+    scene.rot[:, ::2] = np.array([[1.0], [0.0], [0.0], [0.0]], np.float32)
+    scene.scale[:, ::2] = 0.05
+    return scene
+
+
+@pytest.mark.parametrize("make", [_coincident, _half_coincident])
+@pytest.mark.parametrize("n", [33_000, 100_000, 300_000])
+def test_pairs_that_hardly_merge_are_halved_by_the_whole_chip(make, n):
+    """More such clusters than the last block is left with: the wide iterations
+    halve them. The tree stays valid, before and after a refit, and a build and
+    a refit take at most four times as long as an ordinary scene's (left to the
+    block they took 10 to 30 times as long, now 1 to 2)."""
+    from paper_2601_23065_amd.api import BVH
+    scene = make(n)
+    gs, ordinary = gpu_scene(scene), gpu_scene(sg.cloud_scene(n, seed=1))
+    bvh, other = BVH(gs), BVH(ordinary)
+    assert _check_binary(scene, bvh) <= _levels_bound(n)
+    _check_wide(scene, bvh)
+    bvh.refit(gs)
+    _check_binary(scene, bvh)
+    _check_wide(scene, bvh)
+
+    def best(f):
+        times = []
+        for _ in range(8):
+            a, b = torch.cuda.Event(True), torch.cuda.Event(True)
+            a.record()
+            f()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+    build, build0 = best(lambda: BVH(gs)), best(lambda: BVH(ordinary))
+    refit, refit0 = best(lambda: bvh.refit(gs)), best(lambda: other.refit(ordinary))
+    print(f"n={n} build {build:.3f} ms against {build0:.3f}, refit {refit:.3f} against {refit0:.3f}")
+    assert build <= 4 * build0
+    assert refit <= 4 * refit0
