@@ -286,6 +286,9 @@ struct TraceCtx {
 
 constexpr int HL_CAP = 256;        // entries per lane (a multiple of 8: the list is scanned 8 at a time)
 static_assert(HL_CAP % 8 == 0, "hit-list scan reads 8 contiguous entries");
+// An offset past every hit-list buffer (256 MiB on 256 CUs), and an operand that
+// needs no register: the buffer's size in its place cost path tracing 0.4%.
+constexpr uint32_t HL_DROP = 0x40000000u;
 
 __device__ __forceinline__ void report_key_range(unsigned int* status) {
   if (status) __hip_atomic_fetch_or(status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -293,14 +296,15 @@ __device__ __forceinline__ void report_key_range(unsigned int* status) {
 
 // Write v to entry j of this lane's hit list if `on`. One instruction that
 // every lane issues (a lane that is not on passes an offset past the buffer's
-// end, which the buffer store drops by definition): behind a branch, the
+// end, which the buffer store drops by definition; not one near 2^32, whose
+// second word would rest on how an address wraps): behind a branch, the
 // compiler could not count the stores in flight, and would wait for all of
 // them before it uses a record loaded earlier.
 __device__ __forceinline__ void hl_store(const TraceCtx& tc, int j, uint64_t v, bool on) {
   typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
   const u32x2 w = {(uint32_t)v, (uint32_t)(v >> 32)};
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(tc.hl, 0, (int)tc.hl_bytes, 0x00020000);
-  __builtin_amdgcn_raw_buffer_store_b64(w, rs, (int)(on ? (tc.hl_at + (uint32_t)j) * 8u : 0xffffffffu), 0, 0);
+  __builtin_amdgcn_raw_buffer_store_b64(w, rs, (int)(on ? (tc.hl_at + (uint32_t)j) * 8u : HL_DROP), 0, 0);
 }
 __device__ __forceinline__ uint64_t pack_key(const TraceCtx& tc, uint32_t bucket, uint32_t idx) {
   return ((uint64_t)bucket << tc.idx_bits) | (uint64_t)idx | KEY_BIAS;
