@@ -150,3 +150,47 @@ def test_flat_wall_rounding_does_not_depend_on_the_form(w, h):
     g8 = api.stage0_backward(bvh, gs, [cam] * 8, p, d.repeat(8, 1, 1, 1), st8)
     for k in ("pos", "rot", "scale", "opacity"):
         assert (g8[k].double() - 8 * g1[k].double()).abs().max() <= 1e-6 * 8 * g1[k].abs().max()
+
+
+def test_single_bounce_by_lanes_equals_groups():
+    """Forward and adjoint of the single-bounce render, bounce gradients
+    included: eight cameras in one call (one lane per item) against each
+    camera alone with the stream id it has in the batch (groups). The forward
+    state is equal bit for bit. The adjoints add a ray's gradient in another
+    order (hit by hit, or by lanes and then across them), which moves doubles
+    by 2^-53 of the sum of at most 10^2 terms' magnitudes and a record's float
+    now and then: what is left is the final float rounding of each of the nine
+    sums, and of the terms where they cancel: with N terms of either sign their
+    magnitudes add up to about sqrt(N) times the sum, and N is at most 10^6."""
+    from paper_2601_23065_amd import api
+    scene = sg.cloud_scene(2000, seed=9)
+    scene.radiance[:] = np.random.default_rng(2).uniform(0.1, 2.0, scene.radiance.shape)
+    gs = gpu_scene(scene)
+    bvh = api.BVH(gs)
+    w, h, spp = 200, 170, 4
+    assert 8 * w * h > 262_144 >= w * h * spp    # one lane per item against groups
+    cams = [sg.Camera((0.3 * k - 1.0, 0.2, -3.0), (0.0, 0.0, 0.0), (0.0, 1.0, 0.0), 60.0, w, h) for k in range(8)]
+    g = torch.Generator(device="cuda").manual_seed(1)
+    d = torch.rand(8, h, w, 3, generator=g, device="cuda")
+    rgb, state = api.render_single_bounce(bvh, gs, cams, api.Params(spp=spp, seed=5), keep_state=True)
+    many = api.single_bounce_backward(bvh, gs, cams, api.Params(spp=spp, seed=5), d, state)
+    total = {k: torch.zeros_like(v, dtype=torch.float64) for k, v in many.items()}
+    size = {k: torch.zeros_like(v) for k, v in total.items()}
+    px = w * h
+    pix, r1 = state[:8 * px * 28].view(8, px * 28), state[8 * px * 28:].view(8, px * spp * 6)
+    for c, cam in enumerate(cams):
+        p = api.Params(spp=spp, seed=5, camera_id=c)
+        rgb1, s1 = api.render_single_bounce(bvh, gs, [cam], p, keep_state=True)
+        assert torch.equal(rgb1[0], rgb[c])
+        assert torch.equal(s1[:px * 28].view(px, 28)[:, :26].contiguous().view(torch.int32),
+                           pix[c].view(px, 28)[:, :26].contiguous().view(torch.int32))
+        # (R of a sample that was not traced is not written)
+        traced = pix[c].view(px, 28)[:, 25] == 2.0
+        bits = lambda x: x.view(px, -1)[traced].contiguous().view(torch.int32)   # noqa: E731
+        assert torch.equal(bits(s1[px * 28:]), bits(r1[c]))
+        for k, v in api.single_bounce_backward(bvh, gs, [cam], p, d[c:c + 1].contiguous(), s1).items():
+            total[k] += v.double()
+            size[k] += v.double().abs()
+    for k, v in many.items():
+        assert (v.double() - total[k]).abs().max() <= 2.0 ** -24 * 1e3 * size[k].max(), k
+        assert v.abs().max() > 0
