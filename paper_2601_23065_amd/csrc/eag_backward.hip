@@ -624,12 +624,12 @@ void launch_single_bounce_backward(const TraceCtx& tc, const eag_surfels& s, con
   const unsigned grid = (unsigned)(runner_lanes() / TRACE_BLOCK);
   launch_zero_u64(work, 1, st);
   zero_record_counts(gr, n, st);
-  hipLaunchKernelGGL(by_groups(ONE_SEGMENT, hw * n_cams * sp.spp, runner_lanes()) ? k_sb_bwd_secondary<true> : k_sb_bwd_secondary<false>,
+  hipLaunchKernelGGL(by_groups(ADJOINTS, hw * n_cams * sp.spp, runner_lanes(), tc.idx_bits) ? k_sb_bwd_secondary<true> : k_sb_bwd_secondary<false>,
                      dim3(grid), dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, state, r1, dL, gp, gr, reinterpret_cast<double*>(scratch), work, hitlist);
   reduce_records(gr, gacc, n, st);
   launch_zero_u64(work, 1, st);
   zero_record_counts(gr, n, st);
-  hipLaunchKernelGGL(by_groups(ONE_SEGMENT, hw * n_cams, runner_lanes()) ? k_sb_bwd_camera<true> : k_sb_bwd_camera<false>, dim3(grid),
+  hipLaunchKernelGGL(by_groups(ADJOINTS, hw * n_cams, runner_lanes(), tc.idx_bits) ? k_sb_bwd_camera<true> : k_sb_bwd_camera<false>, dim3(grid),
                      dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, state, r1, reinterpret_cast<const double*>(scratch), dL, gp, gr, work, hitlist);
   reduce_records(gr, gacc, n, st);
   check_hip(hipGetLastError(), "single-bounce backward launch");
@@ -644,7 +644,7 @@ void launch_stage0_backward(const TraceCtx& tc, const eag_surfels& s, const CamB
   gr.chunk_next = work + 1;
   launch_zero_u64(work, 1, st);
   zero_record_counts(gr, n, st);
-  hipLaunchKernelGGL(by_groups(ONE_SEGMENT, hw * n_cams, runner_lanes()) ? k_stage0_bwd<true> : k_stage0_bwd<false>,
+  hipLaunchKernelGGL(by_groups(ADJOINTS, hw * n_cams, runner_lanes(), tc.idx_bits) ? k_stage0_bwd<true> : k_stage0_bwd<false>,
                      dim3((unsigned)(runner_lanes() / TRACE_BLOCK)), dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, state, dimg, gp, gr, work, hitlist);
   reduce_records(gr, gacc, n, st);
   check_hip(hipGetLastError(), "stage-0 backward launch");

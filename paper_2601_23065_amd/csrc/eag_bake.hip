@@ -220,7 +220,7 @@ unsigned blocks_for(int64_t count) { return (unsigned)((count + 255) / 256); }
 void launch_zero_bounce(const TraceCtx& tc, const CamBatch& cams, int64_t hw, int32_t n_cams, const SbParams& sp,
                         float* rgb, unsigned long long* work, uint64_t* hitlist, hipStream_t st) {
   launch_zero_u64(work, 1, st);
-  hipLaunchKernelGGL(by_groups(ONE_SEGMENT, hw * n_cams, runner_lanes()) ? k_zero_bounce<true> : k_zero_bounce<false>,
+  hipLaunchKernelGGL(by_groups(CAMERA, hw * n_cams, runner_lanes(), tc.idx_bits) ? k_zero_bounce<true> : k_zero_bounce<false>,
                      dim3((unsigned)(runner_lanes() / TRACE_BLOCK)), dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, rgb, work, hitlist);
   check_hip(hipGetLastError(), "zero-bounce launch");
 }
@@ -229,7 +229,7 @@ void launch_zero_bounce_adj_r(const TraceCtx& tc, const CamBatch& cams, int64_t 
                               const SbParams& sp, const float* dL, double* gacc, unsigned long long* work,
                               uint64_t* hitlist, hipStream_t st) {
   launch_zero_u64(work, 1, st);
-  hipLaunchKernelGGL(by_groups(ONE_SEGMENT, hw * n_cams, runner_lanes()) ? k_zero_bounce_adj_r<true> : k_zero_bounce_adj_r<false>,
+  hipLaunchKernelGGL(by_groups(ADJOINTS, hw * n_cams, runner_lanes(), tc.idx_bits) ? k_zero_bounce_adj_r<true> : k_zero_bounce_adj_r<false>,
                      dim3((unsigned)(runner_lanes() / TRACE_BLOCK)), dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, dL, gacc, work, hitlist);
   check_hip(hipGetLastError(), "zero-bounce adjoint launch");
 }

@@ -749,7 +749,7 @@ void launch_path_trace_mis(const TraceCtx& tc, const PtLaunch& L, const EmitterD
   Q.cap = queue_entries;
   launch_zero_u64(work_counter, 1, st);
   launch_zero_u64(Q.count, 1, st);
-  const bool groups = by_groups(PATHS, L.n_work, runner_lanes());
+  const bool groups = by_groups(PATHS, L.n_work, runner_lanes(), tc.idx_bits);
   auto* const kernel = counters ? (groups ? k_path_trace_mis<true, true> : k_path_trace_mis<true, false>)
                                 : (groups ? k_path_trace_mis<false, true> : k_path_trace_mis<false, false>);
   hipLaunchKernelGGL(kernel, dim3(blocks), dim3(TRACE_BLOCK), 0, st, tc, L, E, Q, work_counter, counters, hitlist);

@@ -170,7 +170,7 @@ __global__ void k_sb_resolve(int64_t n_pix, SbParams sp, const float* state, con
 void launch_camera_pass(const TraceCtx& tc, const CamBatch& cams, int64_t hw, int32_t n_cams, const SbParams& sp,
                         float* state, float* rgb, unsigned long long* work, uint64_t* hitlist, hipStream_t st) {
   launch_zero_u64(work, 1, st);
-  hipLaunchKernelGGL(by_groups(ONE_SEGMENT, hw * n_cams, runner_lanes()) ? k_sb_camera<true> : k_sb_camera<false>,
+  hipLaunchKernelGGL(by_groups(CAMERA, hw * n_cams, runner_lanes(), tc.idx_bits) ? k_sb_camera<true> : k_sb_camera<false>,
                      dim3((unsigned)(runner_lanes() / TRACE_BLOCK)), dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, state, rgb, work, hitlist);
   check_hip(hipGetLastError(), "camera pass launch");
 }
@@ -181,7 +181,7 @@ void launch_single_bounce(const TraceCtx& tc, const CamBatch& cams, int64_t hw, 
   const int64_t np = hw * n_cams;
   launch_camera_pass(tc, cams, hw, n_cams, sp, state, rgb, work, hitlist, st);
   launch_zero_u64(work, 1, st);
-  hipLaunchKernelGGL(by_groups(ONE_SEGMENT, np * sp.spp, runner_lanes()) ? k_sb_secondary<true> : k_sb_secondary<false>,
+  hipLaunchKernelGGL(by_groups(SECONDARY, np * sp.spp, runner_lanes(), tc.idx_bits) ? k_sb_secondary<true> : k_sb_secondary<false>,
                      dim3((unsigned)(runner_lanes() / TRACE_BLOCK)), dim3(TRACE_BLOCK), 0, st, tc, cams, hw, n_cams, sp, (const float*)state, r1, work, hitlist);
   hipLaunchKernelGGL(k_sb_resolve, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, np, sp,
                      (const float*)state, (const double*)r1, rgb);

@@ -242,9 +242,12 @@ __device__ __forceinline__ void run_segments(const TraceCtx& tc, Src& src, unsig
 //   652 560 669 685, 19 k 1169 927 775 765 976, 50 k 2613 1883 1379 1203 1285,
 //   75 k 3830 2645 1812 1515 1518; Stage-0 step: 10 k pixels 754 692 710 804 808,
 //   19 k 1126 890 834 949 1241, 40 k 2101 1362 1081 1153 1424.
-__host__ __device__ inline int group_items(int64_t n_work, int64_t n_waves) {
+// With at most 2^12 surfels a forward segment ends after few visits, and the
+// claims are most of its cost: there 16 items from 24 on instead of 40 (Stage-0
+// images of 65,536 pixels, sparse rooms of 500 to 4000 surfels: 140 to 97 us).
+__host__ __device__ inline int group_items(int64_t n_work, int64_t n_waves, bool short_items) {
   const int64_t q = (n_work + n_waves - 1) / n_waves;
-  return q >= 40 ? 16 : (q >= 12 ? 8 : (q >= 4 ? 4 : (q >= 2 ? 2 : 1)));
+  return q >= (short_items ? 24 : 40) ? 16 : (q >= 12 ? 8 : (q >= 4 ? 4 : (q >= 2 ? 2 : 1)));
 }
 
 template <int QMODE, bool DACC, bool STATS, class Src>
@@ -261,7 +264,7 @@ __device__ __forceinline__ void run_groups(const TraceCtx& tc, Src& src, unsigne
   int* const pend = s_pend + threadIdx.x;
   const int lane = (int)(threadIdx.x & 63);
   const uint64_t lt_mask = (1ull << lane) - 1ull;
-  const int G = 64 / group_items(n_work, (int64_t)gridDim.x * (TRACE_BLOCK / 64));
+  const int G = 64 / group_items(n_work, (int64_t)gridDim.x * (TRACE_BLOCK / 64), !Src::kHits && tc.idx_bits <= 12);
   const int lead = lane & ~(G - 1);
   const bool first = lane == lead;
   TraceCtx tcl = tc;
@@ -346,15 +349,29 @@ __device__ __forceinline__ void run_groups(const TraceCtx& tc, Src& src, unsigne
 
 // Whether a launch of n_work items runs by groups (the host's choice of
 // kernel: the two ways share nothing but LDS). One lane per item has the higher
-// rate, and waits 2 ms for its longest path at the end; one lane per item
-// against groups (ms, a grid of 131,072 lanes): path tracing 75 k paths 2.37,
-// 1.52, 153 k 2.85, 2.44, 307 k 3.41, 4.14; emitter sampling 75 k 6.84, 6.01,
-// 153 k 8.96, 10.50; with one segment per item, the Stage-0 step, 131 k pixels
-// 2.23, 1.60, 262 k 2.50, 1.98, 524 k 2.88, 2.92; single-bounce step 65 k
-// secondary segments 2.26, 2.01, 262 k 4.03, 3.98.
-enum { ONE_SEGMENT, PATHS };
-inline bool by_groups(int kind, int64_t n_work, int64_t grid_lanes) {
-  return n_work <= (kind == ONE_SEGMENT ? 2 : 1) * grid_lanes;
+// rate, and waits for its longest path at the end, 2 ms in a room. With few
+// surfels there is little to wait for, and with 2^18 or more a group's visits
+// miss the caches as a lane's do. So the line lies by the kind of launch and by
+// the bits of a surfel index, in quarters of the grid's lanes. One lane per item
+// against groups, ms, with 131,072 lanes:
+//   paths, 90 k and 130 k of them: 20,000-surfel room 1.15 0.73, 1.29 0.91; 100,000
+//   3.49 1.84, 3.32 2.30; 300,000 4.15 3.65, 4.43 4.66, with emitter sampling 7.33
+//   7.00, 7.84 9.24; cloud of 2000 1.03 0.55, 1.08 0.75;
+//   camera segments, 131 k, 197 k and 262 k: cloud of 2000 0.39 0.27, 0.40 0.35, 0.43
+//   0.42; 100,000-surfel room 0.95 0.60, 0.98 0.66, 0.98 0.69; 300,000 1.16 1.04, 1.78
+//   1.50, 1.77 1.62; sparse rooms, 65 k, 160 k and 250 k: of 1000 surfels 0.10 0.16,
+//   0.11 0.19, 0.13 0.25, of 4000 0.13 0.16, 0.15 0.19, 0.18 0.26;
+//   secondary segments, 131 k, 197 k and 262 k (whole render): cloud of 4000 1.54 0.84,
+//   1.60 0.97, 1.64 1.09; 300,000-surfel room 2.18 1.98, 2.35 2.57, 2.64 3.17; 1 M 3.49
+//   3.54, 3.57 4.47, 3.86 5.41;
+//   adjoints, 160 k: 100,000-surfel room 1.88 1.59, 300,000 3.70 3.37.
+// Rays that all do the same, through many layers, gain from no group: 200 and 1000
+// coplanar layers by 32 k and 65 k paths 0.90 1.40, 2.6 6.2; their adjoints 49 6.4.
+enum { PATHS, CAMERA, SECONDARY, ADJOINTS };
+inline bool by_groups(int kind, int64_t n_work, int64_t grid_lanes, int idx_bits) {
+  static const int quarters[4][5] = {{1, 4, 4, 4, 3}, {1, 4, 6, 8, 8}, {1, 8, 8, 8, 4}, {8, 8, 8, 8, 8}};
+  const int size = idx_bits <= 10 ? 0 : (idx_bits <= 11 ? 1 : (idx_bits <= 12 ? 2 : (idx_bits <= 17 ? 3 : 4)));
+  return 4 * n_work <= quarters[kind][size] * grid_lanes;
 }
 
 template <bool GROUPS, int QMODE, bool DACC, bool STATS, class Src>

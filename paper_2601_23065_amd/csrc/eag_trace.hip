@@ -6,6 +6,7 @@
 #include "eag_internal.h"
 #include "eag_render.h"
 
+#include <algorithm>
 #include <mutex>
 
 // Scratch of eag_trace_rays_noalloc: the packed attribute records of a scene
@@ -108,9 +109,13 @@ void launch_trace_rays(const eag_bvh* b, const Attr* attrs, const eag_trace_para
                        int32_t* hit_count, int32_t max_hits, int32_t* stats, hipStream_t st) {
   const TraceCtx tc = make_ctx(b, attrs, p, ts);
   // (one wave per set of rays, no queue: at 100,000 rays 64, 32 and 16 rays a
-  // wave took 1.16, 1.12 and 1.07 ms, at 400,000 3.05, 3.33 and 3.56)
+  // wave took 1.16, 1.12 and 1.07 ms, at 400,000 3.05, 3.33 and 3.56. With few
+  // surfels a ray is short, and groups only add waves: 90,000 camera rays of a room
+  // of 2000 by groups 89 us, one lane each 68, of 500 71 and 53; 65,536 of 1000
+  // coplanar layers 3.83 ms and 1.55)
   const int q = lanes_per_wave(n_rays, runner_lanes() / 64);
-  const int lanes = q < 64 && q > 16 ? 16 : q;
+  const int most = ts.idx_bits <= 10 ? 16 : (ts.idx_bits <= 13 ? 32 : 63);
+  const int lanes = q > most ? 64 : std::min(q, 16);
   const int64_t per_block = (int64_t)lanes * (TRACE_BLOCK / 64);
   hipLaunchKernelGGL(k_trace_rays, dim3((unsigned)((n_rays + per_block - 1) / per_block)), dim3(TRACE_BLOCK), 0, st, tc,
                      n_rays, o, d, out, hit_idx, hit_count, max_hits, stats, lanes, group_lanes(lanes));

@@ -72,10 +72,10 @@ def test_rays_of_groups_that_give_up(scene):
 def test_paths_of_groups_that_give_up(scene):
     from paper_2601_23065_amd import api
     gs, bvh = scene
-    cam = sg.Camera((0.0, 0.0, -30.0), (0.0, 0.0, 0.0), (0.0, 1.0, 0.0), 90.0, 330, 300)
+    cam = sg.Camera((0.0, 0.0, -30.0), (0.0, 0.0, 0.0), (0.0, 1.0, 0.0), 90.0, 320, 296)
     p = api.Params(spp=2, max_depth=0, rr_start=0, seed=3)
     cg, cl = (torch.zeros(6, dtype=torch.int64, device="cuda") for _ in range(2))
-    # 99,000 paths a launch: 16 items a wave, four lanes each; 198,000: one lane each
+    # 94,720 paths a launch: 16 items a wave, four lanes each; 189,440: one lane each
     acc = api.path_trace(bvh, gs, cam, p, 0, 1, counters=cg)
     acc = api.path_trace(bvh, gs, cam, p, 1, 1, accum=acc, counters=cg)
     print("groups: visits", cg[5].item(), flush=True)

@@ -194,3 +194,19 @@ def test_single_bounce_by_lanes_equals_groups():
     for k, v in many.items():
         assert (v.double() - total[k]).abs().max() <= 2.0 ** -24 * 1e3 * size[k].max(), k
         assert v.abs().max() > 0
+
+
+@pytest.mark.parametrize("n", [300, 3000])
+@pytest.mark.parametrize("m", [32_768, 32_769, 65_536, 65_537, 131_072])
+def test_rays_at_the_lines_of_small_scenes(n, m):
+    """With few surfels, batches run one lane per ray from smaller sizes on:
+    either side of those lines, hits and values are those of a full batch."""
+    from paper_2601_23065_amd.api import BVH, Params, trace_rays
+    scene = sg.cloud_scene(n, seed=5)
+    gs = gpu_scene(scene)
+    bvh = BVH(gs)
+    O, D = (torch.from_numpy(x).cuda().repeat(1, 35) for x in sg.random_rays(scene, 4096, seed=2))
+    full = trace_rays(bvh, gs, Params(), O, D, max_hits=32)
+    part = trace_rays(bvh, gs, Params(), O[:, :m].contiguous(), D[:, :m].contiguous(), max_hits=32)
+    assert _same(part[0], full[0][:, :m])
+    assert torch.equal(part[1], full[1][:m]) and torch.equal(part[2], full[2][:m])
