@@ -94,12 +94,10 @@ __host__ __device__ __forceinline__ void write_nodeq(NodeQ* out, const float (&l
       if ((double)o[a] > l_m) o[a] = nextafterf(o[a], -__builtin_inff());
       const double ext = (double)h + m - (double)o[a];
       // the smallest step with ext <= 255 steps (at least 2^-126: a normal float)
-      int e = -126;
-      if (ext > 0.0) {
-        e = ilogb(ext) - 8;
-        while (ldexp(255.0, e) < ext) ++e;
-        if (e < -126) e = -126;
-      }
+      int e = 0;
+      const double f = frexp(ext, &e);   // ext = f 2^e, f in [1/2, 1) (0 for 0)
+      e = ext > 0.0 ? e - (f > 255.0 / 256.0 ? 7 : 8) : -126;
+      if (e < -126) e = -126;
       const double inv = ldexp(1.0, -e);
       for (int k = 0; k < 4; ++k) {
         // an empty slot, and a box that is not a number, span the node
