@@ -210,16 +210,16 @@ constexpr double HX = 0.2672612419124244, HY = 0.5345224838248488, HZ = 0.801783
 constexpr double TWO_PI = 6.283185307179586;
 
 __device__ __forceinline__ D3 cosine_dir(D3 n, double u0, double u1) {
-  const double hn = HX * n.x + HY * n.y + HZ * n.z;
-  const D3 m = d3(HX - hn * n.x, HY - hn * n.y, HZ - hn * n.z);
-  const D3 b1 = (1.0 / sqrt(dot(m, m))) * m;
-  const D3 b2 = cross(n, b1);
+  const double hn = fma(HZ, n.z, fma(HX, n.x, HY * n.y));
+  const D3 m = d3(fma(-hn, n.x, HX), fma(-hn, n.y, HY), fma(-hn, n.z, HZ));
+  const D3 b1 = (1.0 / sqrt(fma(m.z, m.z, fma(m.x, m.x, m.y * m.y)))) * m;
+  const D3 b2 = d3(fma(n.y, b1.z, -(n.z * b1.y)), fma(n.z, b1.x, -(n.x * b1.z)), fma(n.x, b1.y, -(n.y * b1.x)));
   const double r = sqrt(u0);
   double s, c;
   sincos(TWO_PI * u1, &s, &c);
   const double z = sqrt(1.0 - u0);
-  return d3(r * c * b1.x + r * s * b2.x + z * n.x, r * c * b1.y + r * s * b2.y + z * n.y,
-            r * c * b1.z + r * s * b2.z + z * n.z);
+  return d3(fma(z, n.x, fma(r * c, b1.x, r * s * b2.x)), fma(z, n.y, fma(r * c, b1.y, r * s * b2.y)),
+            fma(z, n.z, fma(r * c, b1.z, r * s * b2.z)));
 }
 
 // Element i of an array of at most 4 GiB (2^23 surfels: 1 GiB of nodes at
@@ -787,21 +787,24 @@ __device__ __forceinline__ uint64_t leaf_key(const TraceCtx& tc, const Record& r
   // u' = y.(|q|^2 t_u). Its rounding differs from the normalised evaluation
   // by a few ulp, well inside the margins within which rim, t_min and bucket
   // decisions are flagged.
+  // Every fused product is written out: which of two products of a sum is
+  // fused went with the code around it, and t, which decides the bucket, was
+  // another in the kernels for groups than in those for lanes.
   const double w = rec.q.x, x = rec.q.y, y = rec.q.z, z = rec.q.w;
-  const double q2n = w * w + x * x + y * y + z * z;
-  const D3 cu = d3(w * w + x * x - y * y - z * z, 2.0 * (x * y + w * z), 2.0 * (x * z - w * y));
-  const D3 cv = d3(2.0 * (x * y - w * z), w * w - x * x + y * y - z * z, 2.0 * (y * z + w * x));
-  const D3 cn = d3(2.0 * (x * z + w * y), 2.0 * (y * z - w * x), w * w - x * x - y * y + z * z);
+  const double q2n = fma(z, z, fma(y, y, fma(w, w, x * x)));
+  const D3 cu = d3(fma(-z, z, fma(-y, y, fma(w, w, x * x))), 2.0 * fma(x, y, w * z), 2.0 * fma(x, z, -(w * y)));
+  const D3 cv = d3(2.0 * fma(x, y, -(w * z)), fma(-z, z, fma(y, y, fma(w, w, -(x * x)))), 2.0 * fma(y, z, w * x));
+  const D3 cn = d3(2.0 * fma(x, z, w * y), 2.0 * fma(y, z, -(w * x)), fma(z, z, fma(-y, y, fma(w, w, -(x * x)))));
   const D3 d = d3((double)rec.p_sigma.x - O.x, (double)rec.p_sigma.y - O.y, (double)rec.p_sigma.z - O.z);
-  const double den = dot(W, cn);
-  const double t = dot(d, cn) / den;
-  const D3 yv = d3(t * W.x - d.x, t * W.y - d.y, t * W.z - d.z);
+  const double den = fma(W.z, cn.z, fma(W.x, cn.x, W.y * cn.y));
+  const double t = fma(d.z, cn.z, fma(d.y, cn.y, d.x * cn.x)) / den;
+  const D3 yv = d3(fma(t, W.x, -d.x), fma(t, W.y, -d.y), fma(t, W.z, -d.z));
   const double su2 = (double)rec.s_idx.x * rec.s_idx.x, sv2 = (double)rec.s_idx.y * rec.s_idx.y;
-  const double up = dot(yv, cu), vp = dot(yv, cv);
+  const double up = fma(yv.z, cu.z, fma(yv.x, cu.x, yv.y * cu.y)), vp = fma(yv.z, cv.z, fma(yv.x, cv.x, yv.y * cv.y));
   // (multiplied through by s_u^2 s_v^2, all positive: no division)
   // (&, not &&: nothing is skipped, so nothing is branched around)
   const bool hit = (fabs(den) > 1e-12 * q2n) & (rec.p_sigma.w > 0.0f) & (t > tc.t_min) &
-                   (up * up * sv2 + vp * vp * su2 <= tc.k2 * q2n * q2n * su2 * sv2);
+                   (fma(up * up, sv2, vp * vp * su2) <= tc.k2 * q2n * q2n * su2 * sv2);
   const uint64_t key = make_key(tc, t, rec_index(rec));
   const bool qual = hit & (key > floor_key);
   // A hit in the last bucket may stand for a farther one that the key
@@ -1065,18 +1068,18 @@ __device__ __forceinline__ HitEval eval_hit(const Record& rec, D3 O, D3 W) {
   // reciprocal c = 1 / (|q|^2 s_u s_v) for u^2 + v^2 and the normal's scale
   const double qw = rec.q.x, qx = rec.q.y, qy = rec.q.z, qz = rec.q.w;
   const double su = rec.s_idx.x, sv = rec.s_idx.y;
-  const double c = 1.0 / ((qw * qw + qx * qx + qy * qy + qz * qz) * (su * sv));
+  const double c = 1.0 / (fma(qz, qz, fma(qy, qy, fma(qw, qw, qx * qx))) * (su * sv));
   const double iq2 = c * (su * sv);
   const double wx = qw * qx, wy = qw * qy, wz = qw * qz, xz = qx * qz;
-  const D3 cu = d3(qw * qw + qx * qx - qy * qy - qz * qz, 2.0 * fma(qx, qy, wz), 2.0 * (adj ? fma(qx, qz, -wy) : fma(-qw, qy, xz)));
-  const D3 cv = d3(2.0 * fma(qx, qy, -wz), qw * qw - qx * qx + qy * qy - qz * qz, 2.0 * fma(qy, qz, wx));
-  const D3 cn = d3(2.0 * (adj ? fma(qx, qz, wy) : fma(qw, qy, xz)), 2.0 * fma(qy, qz, -wx), qw * qw - qx * qx - qy * qy + qz * qz);
+  const D3 cu = d3(fma(-qz, qz, fma(-qy, qy, fma(qw, qw, qx * qx))), 2.0 * fma(qx, qy, wz), 2.0 * (adj ? fma(qx, qz, -wy) : fma(-qw, qy, xz)));
+  const D3 cv = d3(2.0 * fma(qx, qy, -wz), fma(-qz, qz, fma(qy, qy, fma(qw, qw, -(qx * qx)))), 2.0 * fma(qy, qz, wx));
+  const D3 cn = d3(2.0 * (adj ? fma(qx, qz, wy) : fma(qw, qy, xz)), 2.0 * fma(qy, qz, -wx), fma(qz, qz, fma(-qy, qy, fma(qw, qw, -(qx * qx)))));
   const D3 dp = d3((double)rec.p_sigma.x - O.x, (double)rec.p_sigma.y - O.y, (double)rec.p_sigma.z - O.z);
   const double dn = fma(W.z, cn.z, fma(W.x, cn.x, W.y * cn.y));
   const double t = fma(dp.z, cn.z, fma(dp.y, cn.y, dp.x * cn.x)) / dn;
   const D3 yv = d3(t * W.x - dp.x, t * W.y - dp.y, t * W.z - dp.z);
-  const double uc = dot(yv, cu) * sv, vc = dot(yv, cv) * su;   // u, v times |q|^2 s_u s_v
-  const double g = exp(-0.5 * ((uc * uc + vc * vc) * (c * c)));
+  const double uc = fma(yv.z, cu.z, fma(yv.x, cu.x, yv.y * cu.y)) * sv, vc = fma(yv.z, cv.z, fma(yv.x, cv.x, yv.y * cv.y)) * su;   // u, v times |q|^2 s_u s_v
+  const double g = exp(-0.5 * (fma(uc, uc, vc * vc) * (c * c)));
   HitEval h;
   h.t = t;
   h.a = (double)rec.p_sigma.w * g;
@@ -1145,19 +1148,19 @@ __device__ __forceinline__ void blend_round(const TraceCtx& tc, S& s, Round& r, 
     // reciprocal c = 1 / (|q|^2 s_u s_v) for u^2 + v^2 and the normal's scale
     const double qw = rec.q.x, qx = rec.q.y, qy = rec.q.z, qz = rec.q.w;
     const double su = rec.s_idx.x, sv = rec.s_idx.y;
-    const double c = 1.0 / ((qw * qw + qx * qx + qy * qy + qz * qz) * (su * sv));
+    const double c = 1.0 / (fma(qz, qz, fma(qy, qy, fma(qw, qw, qx * qx))) * (su * sv));
     const double iq2 = c * (su * sv);
     constexpr bool adj = HitFn::kHits;
     const double wx = qw * qx, wy = qw * qy, wz = qw * qz, xz = qx * qz;
-    const D3 cu = d3(qw * qw + qx * qx - qy * qy - qz * qz, 2.0 * fma(qx, qy, wz), 2.0 * (adj ? fma(qx, qz, -wy) : fma(-qw, qy, xz)));
-    const D3 cv = d3(2.0 * fma(qx, qy, -wz), qw * qw - qx * qx + qy * qy - qz * qz, 2.0 * fma(qy, qz, wx));
-    const D3 cn = d3(2.0 * (adj ? fma(qx, qz, wy) : fma(qw, qy, xz)), 2.0 * fma(qy, qz, -wx), qw * qw - qx * qx - qy * qy + qz * qz);
+    const D3 cu = d3(fma(-qz, qz, fma(-qy, qy, fma(qw, qw, qx * qx))), 2.0 * fma(qx, qy, wz), 2.0 * (adj ? fma(qx, qz, -wy) : fma(-qw, qy, xz)));
+    const D3 cv = d3(2.0 * fma(qx, qy, -wz), fma(-qz, qz, fma(qy, qy, fma(qw, qw, -(qx * qx)))), 2.0 * fma(qy, qz, wx));
+    const D3 cn = d3(2.0 * (adj ? fma(qx, qz, wy) : fma(qw, qy, xz)), 2.0 * fma(qy, qz, -wx), fma(qz, qz, fma(-qy, qy, fma(qw, qw, -(qx * qx)))));
     const D3 dp = d3((double)rec.p_sigma.x - s.O.x, (double)rec.p_sigma.y - s.O.y, (double)rec.p_sigma.z - s.O.z);
     const double dn = fma(s.W.z, cn.z, fma(s.W.x, cn.x, s.W.y * cn.y));
     const double t = fma(dp.z, cn.z, fma(dp.y, cn.y, dp.x * cn.x)) / dn;
     const D3 yv = d3(t * s.W.x - dp.x, t * s.W.y - dp.y, t * s.W.z - dp.z);
-    const double uc = dot(yv, cu) * sv, vc = dot(yv, cv) * su;   // u, v times |q|^2 s_u s_v
-    const double g = exp(-0.5 * ((uc * uc + vc * vc) * (c * c)));
+    const double uc = fma(yv.z, cu.z, fma(yv.x, cu.x, yv.y * cu.y)) * sv, vc = fma(yv.z, cv.z, fma(yv.x, cv.x, yv.y * cv.y)) * su;   // u, v times |q|^2 s_u s_v
+    const double g = exp(-0.5 * (fma(uc, uc, vc * vc) * (c * c)));
     const double a = (double)rec.p_sigma.w * g, om = fma(-(double)rec.p_sigma.w, g, 1.0);
     const double w = s.T * a;
     const Acc wf = (Acc)w;

@@ -210,3 +210,32 @@ def test_rays_at_the_lines_of_small_scenes(n, m):
     part = trace_rays(bvh, gs, Params(), O[:, :m].contiguous(), D[:, :m].contiguous(), max_hits=32)
     assert _same(part[0], full[0][:, :m])
     assert torch.equal(part[1], full[1][:m]) and torch.equal(part[2], full[2][:m])
+
+
+def test_distances_at_a_bucket_edge_round_alike():
+    """Rays through surfel centres exactly 2 m away, where a depth bucket
+    begins: the last bit of the distance decides the bucket, and with it
+    whether the surfel comes before or after its companion half a bucket
+    nearer. Groups and lanes round it alike."""
+    from paper_2601_23065_amd.api import BVH, Params, trace_rays
+    rng = np.random.default_rng(12)
+    n, f32 = 4096, lambda a: np.ascontiguousarray(a, dtype=np.float32)
+    z = rng.standard_normal((3, n))
+    far = f32(2.0 * z / np.linalg.norm(z, axis=0))          # 2 W, exactly
+    W = far.astype(np.float64) / 2.0
+    near = f32(W * (2.0 - 2.0 ** -14))
+    rot = f32(rng.standard_normal((4, 2 * n)))
+    scene = sg.Scene(f32(np.concatenate([far, near], 1)), rot, f32(np.full((2, 2 * n), 0.002)),
+                     f32(np.full(2 * n, 0.3)), f32(np.full((3, 2 * n), 0.5)), f32(rng.uniform(1, 9, (3, 2 * n))),
+                     f32(np.ones(2 * n)), bounds=(np.full(3, -2.1), np.full(3, 2.1)))
+    gs = gpu_scene(scene)
+    bvh = BVH(gs)
+    D = torch.from_numpy(W).cuda()
+    O = torch.zeros_like(D)
+    full = trace_rays(bvh, gs, Params(), O.repeat(1, 35), D.repeat(1, 35), max_hits=8)
+    part = trace_rays(bvh, gs, Params(), O, D, max_hits=8)
+    first = full[1][:n, 0] < n
+    both = full[2][:n] >= 2
+    print(f"rays with both {int(both.sum())}, far surfel first {int((first & both).sum())}")
+    assert both.sum() > n // 2 and (first & both).any() and (~first & both).any()   # the last bit does decide
+    assert torch.equal(part[1], full[1][:n]) and torch.equal(part[0], full[0][:, :n])
