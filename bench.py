@@ -163,7 +163,7 @@ def _code_tokens(text):
 KERNEL_SOURCES = ["paper_2601_23065_amd/csrc/eag_pt.hip", "paper_2601_23065_amd/csrc/eag_build.hip",
                   "paper_2601_23065_amd/csrc/eag_prim.hip", "paper_2601_23065_amd/csrc/eag_runner.h",
                   "paper_2601_23065_amd/csrc/eag_device.h", "paper_2601_23065_amd/csrc/eag_render.h",
-                  "paper_2601_23065_amd/csrc/eag_internal.h", "include/eag.h", "paper_2601_23065_amd/build.py"]
+                  "paper_2601_23065_amd/csrc/eag_records.h", "paper_2601_23065_amd/csrc/eag_internal.h", "include/eag.h", "paper_2601_23065_amd/build.py"]
 
 
 def kernel_source_hash():

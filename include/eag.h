@@ -245,15 +245,15 @@ eag_status eag_trace_rays_noalloc(const eag_bvh* bvh, const eag_surfels* s, cons
 int64_t eag_fwd_state_floats(const eag_camera* cams, int32_t n_cams, const eag_trace_params* p);
 /* Workspace of eag_render_single_bounce: packed attributes, forward state,
  * per-sample adjoints, double gradient accumulators, a work counter and the
- * hit list of the persistent secondary passes (1 KiB per lane of the
- * persistent grid, which depends on the current device: 128 MiB on MI355X).
+ * hit list of the persistent secondary passes (2 KiB per lane of the
+ * persistent grid, which depends on the current device: 256 MiB on MI355X).
  * Returns 0 and sets the last error if the device cannot be queried. */
 size_t eag_render_workspace_bytes(int64_t n_surfels, const eag_camera* cams, int32_t n_cams,
                                   const eag_trace_params* p);
 /* Workspace of eag_single_bounce_backward: the render workspace plus the
- * per-hit gradient records of the adjoint passes: 64 B for up to 20 hits
+ * per-hit gradient records of the adjoint passes: 76 B for up to 20 hits
  * per (pixel, sample) of one batch of up to 8 cameras, at most 2^27 records
- * (8 GiB), and per-surfel counters. Hits beyond the records are added with
+ * (9.5 GiB), and per-surfel counters. Hits beyond the records are added with
  * atomics instead, so the result does not depend on the size; the speed
  * does. Returns 0 and sets the last error if the device cannot be queried. */
 size_t eag_backward_workspace_bytes(int64_t n_surfels, const eag_camera* cams, int32_t n_cams,
@@ -295,8 +295,8 @@ eag_status eag_single_bounce_backward(const eag_bvh* bvh, const eag_surfels* s, 
  * ------------------------------------------------------------------------ */
 #define EAG_ACCUM_SCALE 4294967296.0 /* 2^32 */
 /* Workspace of eag_path_trace: packed attributes (32 B per surfel), a work
- * counter, and a hit list of 1 KiB per lane of the persistent grid, which
- * depends on the current device (256 CUs x 512 lanes on MI355X: 128 MiB).
+ * counter, and a hit list of 2 KiB per lane of the persistent grid, which
+ * depends on the current device (256 CUs x 512 lanes on MI355X: 256 MiB).
  * Returns 0 and sets the last error if the device cannot be queried. */
 size_t eag_path_trace_workspace_bytes(int64_t n_surfels);
 eag_status eag_path_trace(const eag_bvh* bvh, const eag_surfels* s, const eag_camera* cam,
@@ -508,7 +508,7 @@ typedef struct {
   float eps;                    /* added to sqrt(v_hat) (1e-15)                  */
 } eag_adam;
 /* Workspace of the calls below for n_cams cameras of one size: packed
- * attributes, the persistent grid's hit list (device dependent: 128 MiB on
+ * attributes, the persistent grid's hit list (device dependent: 256 MiB on
  * MI355X), double radiance-gradient accumulators, and the image and image
  * gradient of eag_bake_step. 0 and the last error if the device cannot be
  * queried. */

@@ -239,3 +239,19 @@ def test_distances_at_a_bucket_edge_round_alike():
     print(f"rays with both {int(both.sum())}, far surfel first {int((first & both).sum())}")
     assert both.sum() > n // 2 and (first & both).any() and (~first & both).any()   # the last bit does decide
     assert torch.equal(part[1], full[1][:n]) and torch.equal(part[0], full[0][:, :n])
+
+
+@pytest.mark.parametrize("which", ["cloud", "room"])
+def test_values_do_not_depend_on_the_form(which):
+    """Every value of a ray, bit for bit, by groups of 64 to four lanes and by
+    one lane each."""
+    from paper_2601_23065_amd.api import BVH, Params, trace_rays
+    scene = sg.cloud_scene(2000, seed=9) if which == "cloud" else sg.perturb(sg.room_scene(20_000, seed=2), seed=3)
+    gs = gpu_scene(scene)
+    bvh = BVH(gs)
+    O, D = (torch.from_numpy(x).cuda().repeat(1, 35) for x in sg.random_rays(scene, 4096, seed=2))
+    full = trace_rays(bvh, gs, Params(), O, D, max_hits=64)
+    for m in (500, 3000, 6000, 12_000, 30_000):
+        part = trace_rays(bvh, gs, Params(), O[:, :m].contiguous(), D[:, :m].contiguous(), max_hits=64)
+        for a, b in zip(part, (full[0][:, :m], full[1][:m], full[2][:m])):
+            assert torch.equal(a, b), m
