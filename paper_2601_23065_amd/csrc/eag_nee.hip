@@ -749,7 +749,9 @@ void launch_path_trace_mis(const TraceCtx& tc, const PtLaunch& L, const EmitterD
   Q.cap = queue_entries;
   launch_zero_u64(work_counter, 1, st);
   launch_zero_u64(Q.count, 1, st);
-  const bool groups = by_groups(PATHS, L.n_work, runner_lanes(), tc.idx_bits);
+  // (one or two rounds do not make up here for the visits' misses: 6.3 ms by lanes, 7.1 by groups)
+  const int kind = path_kind(L.s[0].max_depth, L.s[0].rr_start, 3);
+  const bool groups = by_groups(kind, L.n_work, runner_lanes(), tc.idx_bits);
   auto* const kernel = counters ? (groups ? k_path_trace_mis<true, true> : k_path_trace_mis<true, false>)
                                 : (groups ? k_path_trace_mis<false, true> : k_path_trace_mis<false, false>);
   hipLaunchKernelGGL(kernel, dim3(blocks), dim3(TRACE_BLOCK), 0, st, tc, L, E, Q, work_counter, counters, hitlist);

@@ -145,7 +145,8 @@ void launch_path_trace(const TraceCtx& ctx, const PtLaunch& L, unsigned long lon
   const unsigned blocks = (unsigned)(runner_lanes() / TRACE_BLOCK);
   hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, st, work_counter, 1);
   // the statistics cost registers: kernels of their own without them
-  const bool multi = L.n_slots > 1, groups = !multi && by_groups(PATHS, L.n_work, runner_lanes(), tc.idx_bits);
+  const int kind = path_kind(L.s[0].max_depth, L.s[0].rr_start, 1);
+  const bool multi = L.n_slots > 1, groups = !multi && by_groups(kind, L.n_work, runner_lanes(), tc.idx_bits);
   auto* kernel = counters ? k_path_trace<true, false, true> : k_path_trace<false, false, true>;
   if (groups) kernel = counters ? k_path_trace<true, true, false> : k_path_trace<false, true, false>;
   else if (!multi) kernel = counters ? k_path_trace<true, false, false> : k_path_trace<false, false, false>;

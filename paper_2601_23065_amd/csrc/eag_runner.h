@@ -352,29 +352,43 @@ __device__ __forceinline__ void run_groups(const TraceCtx& tc, Src& src, unsigne
 
 // Whether a launch of n_work items runs by groups (the host's choice of
 // kernel: the two ways share nothing but LDS). One lane per item has the higher
-// rate, and waits for its longest path at the end, 2 ms in a room. With few
-// surfels there is little to wait for, and with 2^18 or more a group's visits
-// miss the caches as a lane's do. So the line lies by the kind of launch and by
-// the bits of a surfel index, in quarters of the grid's lanes. One lane per item
-// against groups, ms, with 131,072 lanes:
+// rate, and waits for its longest path at the end, 2 ms in a room; just above
+// the grid's lanes its second pass is nearly empty. With few surfels there is
+// little to wait for, and with 2^18 or more a group's visits miss the caches as
+// a lane's do, except where roulette ends paths early: then most lanes idle,
+// while a wave's groups take other items. So the line lies by the kind of launch
+// and by the bits of a surfel index, in quarters of the grid's lanes. One lane
+// per item against groups, ms, with 131,072 lanes:
 //   paths, 90 k and 130 k of them: 20,000-surfel room 1.15 0.73, 1.29 0.91; 100,000
 //   3.49 1.84, 3.32 2.30; 300,000 4.15 3.65, 4.43 4.66, with emitter sampling 7.33
 //   7.00, 7.84 9.24; cloud of 2000 1.03 0.55, 1.08 0.75;
-//   camera segments, 131 k, 197 k and 262 k: cloud of 2000 0.39 0.27, 0.40 0.35, 0.43
-//   0.42; 100,000-surfel room 0.95 0.60, 0.98 0.66, 0.98 0.69; 300,000 1.16 1.04, 1.78
-//   1.50, 1.77 1.62; sparse rooms, 65 k, 160 k and 250 k: of 1000 surfels 0.10 0.16,
-//   0.11 0.19, 0.13 0.25, of 4000 0.13 0.16, 0.15 0.19, 0.18 0.26;
+//   paths, 102 k and 124 k in the 500,000-surfel room, without roulette, depth 4: 4.37
+//   5.63, 4.68 6.55, sampled 7.24 9.86, 7.52 11.6; with two rounds of it (depth 4 from 3)
+//   3.59 3.78, 3.87 4.36 (the same room perturbed 5.43 4.25, 5.08 4.89), sampled 6.31
+//   7.05, 6.60 8.23; with five (6 from 2) 4.66 3.59, 4.78 4.08, sampled 8.03 6.67, 8.28
+//   7.47;
+//   camera segments (whole Stage-0 step), 134 k, 215 k, 230 k and 246 k: cloud of 2000
+//   0.82 0.70, 0.90 0.83, 1.09 1.05, 1.14 1.17, of 3800 at 215 k 1.43 1.18, at 230 k 1.72
+//   1.61; 100,000-surfel room, camera pass alone, 131 k and 262 k, 0.95 0.60, 0.98 0.69;
+//   300,000 1.16 1.04, 1.77 1.62; sparse rooms of 1000, 65 k and 250 k, 0.10 0.16, 0.13
+//   0.25 (of 1500, whole step, 134 k and 246 k 0.32 0.44, 0.44 0.63);
 //   secondary segments, 131 k, 197 k and 262 k (whole render): cloud of 4000 1.54 0.84,
 //   1.60 0.97, 1.64 1.09; 300,000-surfel room 2.18 1.98, 2.35 2.57, 2.64 3.17; 1 M 3.49
 //   3.54, 3.57 4.47, 3.86 5.41;
 //   adjoints, 160 k: 100,000-surfel room 1.88 1.59, 300,000 3.70 3.37.
 // Rays that all do the same, through many layers, gain from no group: 200 and 1000
 // coplanar layers by 32 k and 65 k paths 0.90 1.40, 2.6 6.2; their adjoints 49 6.4.
-enum { PATHS, CAMERA, SECONDARY, ADJOINTS };
+enum { PATHS, ENDED_PATHS, CAMERA, SECONDARY, ADJOINTS };
 inline bool by_groups(int kind, int64_t n_work, int64_t grid_lanes, int idx_bits) {
-  static const int quarters[4][5] = {{1, 4, 4, 4, 3}, {1, 4, 6, 8, 8}, {1, 8, 8, 8, 4}, {8, 8, 8, 8, 8}};
+  static const int quarters[5][5] = {{1, 4, 4, 4, 3}, {1, 4, 4, 4, 4}, {1, 7, 8, 8, 8}, {1, 8, 8, 8, 4}, {8, 8, 8, 8, 8}};
   const int size = idx_bits <= 10 ? 0 : (idx_bits <= 11 ? 1 : (idx_bits <= 12 ? 2 : (idx_bits <= 17 ? 3 : 4)));
   return 4 * n_work <= quarters[kind][size] * grid_lanes;
+}
+
+// Paths of at most max_depth bounces are ended early where roulette has at
+// least `rounds` of them to act on.
+inline int path_kind(int32_t max_depth, int32_t rr_start, int32_t rounds) {
+  return rr_start > 0 && max_depth - rr_start >= rounds - 1 ? ENDED_PATHS : PATHS;
 }
 
 template <bool GROUPS, int QMODE, bool DACC, bool STATS, class Src>

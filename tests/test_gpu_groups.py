@@ -255,3 +255,27 @@ def test_values_do_not_depend_on_the_form(which):
         part = trace_rays(bvh, gs, Params(), O[:, :m].contiguous(), D[:, :m].contiguous(), max_hits=64)
         for a, b in zip(part, (full[0][:, :m], full[1][:m], full[2][:m])):
             assert torch.equal(a, b), m
+
+
+@pytest.mark.parametrize("mis", [False, True])
+@pytest.mark.parametrize("depth, rr", [(2, 0), (2, 2), (3, 2), (3, 1)])
+def test_many_surfels_by_groups_where_roulette_ends_paths(depth, rr, mis):
+    """2^18 surfels and 102,400 paths a launch: by groups with enough rounds of
+    roulette, by lanes else; 204,800 by lanes. (A path's float32 value carries
+    about 1e-13 of its directions from one form to the other: 1e-5 of a pixel's
+    sum, in steps of 2^-32, is far above that.)"""
+    from paper_2601_23065_amd import api
+    scene = sg.room_scene(2 ** 18 + 1, seed=2)
+    gs = gpu_scene(scene)
+    bvh = api.BVH(gs)
+    cam = sg.interior_cameras(scene, 1, 320, 320, seed=4)[0]
+    p = api.Params(spp=2, max_depth=depth, rr_start=rr, seed=5)
+    em = api.Emitters(gs, p) if mis else None
+    c = torch.zeros(6, dtype=torch.int64, device="cuda")
+    run = (lambda *a, **k: api.path_trace_mis(bvh, gs, em, cam, p, *a, counters=c, **k)) if mis else \
+        (lambda *a, **k: api.path_trace(bvh, gs, cam, p, *a, counters=c, **k))
+    one = run(0, 2)
+    acc = run(0, 1)
+    acc = run(1, 1, accum=acc)
+    assert c[1] == 4 * 102_400 and one.abs().max() > 0
+    assert ((one - acc).abs().double() <= 1e-5 * one.abs().double() + 2 * 2.0 ** 32 * 1e-9).all()
